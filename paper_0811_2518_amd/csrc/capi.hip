@@ -261,6 +261,7 @@ gabp_status gabp_create(int32_t n, const int32_t* row_ptr, const int32_t* col_id
   if (r == GABP_OK && n > 0 && c->opts.layout == kLayoutSerial) r = apply_colour_order(c, nullptr, 0);
   else if (r == GABP_OK && n > 0 && !(c->opts.flags & GABP_FLAG_NATURAL_ORDER)) r = apply_xcd_order(c);
   if (r == GABP_OK && n > 0) r = alloc_solver(c);
+  if (r == GABP_OK && n > 0) r = setup_resident(c);
   if (r == GABP_OK && n > 0) r = autotune(c);
   if (r == GABP_OK && n > 0) release_unused_layout(c);
   if (r == GABP_OK) {
@@ -292,6 +293,11 @@ gabp_status gabp_solve(gabp_handle h, const double* b, double* x, double* var, d
   if (var && !plain_mode(c)) return fail(c, GABP_E_ARG, "variances are only available in plain FP64 mode");
   if (!plain_mode(c) && !(single_loop_mode(c) && c->opts.precision == GABP_FP64) && !(tol > 0.0))
     return fail(c, GABP_E_ARG, "the correction loop needs tol > 0");
+  if (use_resident(c)) {
+    bool ran = false;
+    const gabp_status r = solve_resident(c, b, x, var, tol, max_iter, info, &ran);
+    if (ran || r != GABP_OK) return r;
+  }
   // renumbered handles solve in their internal numbering
   const bool perm = c->perm_d != nullptr;
   if (perm && !(c->bperm_d && c->xperm_d && c->vperm_d))
@@ -360,15 +366,22 @@ gabp_status gabp_backward(gabp_handle h, const double* x, const double* grad_x, 
   if (c->n == 0) return GABP_OK;
   if (!x || !grad_x || !grad_b) return fail(c, GABP_E_ARG, "NULL x, grad_x or grad_b");
   // A is symmetric: the adjoint system A^T lambda = dL/dx is a second GaBP solve against A
-  const bool perm = c->perm_d != nullptr;
+  bool resident = false;
+  gabp_status r = GABP_OK;
+  if (use_resident(c)) {
+    r = solve_resident(c, grad_x, grad_b, nullptr, tol, max_iter, info, &resident);
+    if (r < 0) return r;
+  }
+  const bool perm = c->perm_d != nullptr && !resident;
   if (perm && !(c->bperm_d && c->xperm_d)) return fail(c, GABP_E_ARG, "internal order buffers missing");
   if (perm) GABP_HIP(c, launch_gather(grad_x, c->inv_d, c->bperm_d, c->n, c->stream));
   const double* gi = perm ? c->bperm_d : grad_x;
   double* li = perm ? c->xperm_d : grad_b;
-  gabp_status r = plain_mode(c)         ? solve_plain(c, gi, li, nullptr, tol, max_iter, info, true)
-                  : single_loop_mode(c) && c->opts.precision == GABP_FP64
-                        ? solve_single_loop(c, gi, li, tol, max_iter, info)
-                                        : solve_outer(c, gi, li, tol, max_iter, info);
+  if (!resident)
+    r = plain_mode(c) ? solve_plain(c, gi, li, nullptr, tol, max_iter, info, true)
+        : single_loop_mode(c) && c->opts.precision == GABP_FP64
+            ? solve_single_loop(c, gi, li, tol, max_iter, info)
+            : solve_outer(c, gi, li, tol, max_iter, info);
   if (r < 0) return r;
   if (perm) {
     GABP_HIP(c, launch_gather(li, c->perm_d, grad_b, c->n, c->stream));

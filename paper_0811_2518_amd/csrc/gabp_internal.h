@@ -269,6 +269,58 @@ hipError_t launch_small(const SmallArgs& a, hipStream_t s);
 // the same with K = 4 slots per lane (E <= 4096, also when E lives on the device)
 hipError_t launch_small_k4(const SmallArgs& a, hipStream_t s);
 
+// Resident solve of a mid-sized system (resident.hip): one workgroup per CU,
+// messages in registers, all sweeps in one launch.
+constexpr int kResLanes = 1024;      // most lanes per workgroup
+constexpr int kResMaxBlocks = 256;   // most workgroups (their partials are summed 4 to a lane)
+constexpr int kResMaxChain = 16;     // most lanes per row
+constexpr uint64_t kResRollMs = 2;     // roll call: longest wait for a workgroup to start
+constexpr uint64_t kResWaitMs = 4000;  // later barriers: every workgroup is running
+struct ResLine {
+  uint64_t v, pad[15];
+};
+// Control block of the grid barrier: zero when a launch starts.
+struct ResCtl {
+  ResLine grp[8], root, rel[8];
+  uint32_t state, pad[31];
+  uint64_t part[2][kResMaxBlocks];  // residual partials, tagged, by check parity
+};
+struct ResArgs {
+  int32_t n, E;
+  const int2* blk;          // [workgroups] {first row, rows}
+  const int2* lane;         // [workgroups][lanes] {row or -1, place in the chain | chain length << 16}
+  int32_t rows_cap;         // most rows of a workgroup
+  const int32_t* off_ptr;   // off-diagonal CSR
+  const int32_t* col;
+  const double* a;
+  const double* diag;       // [n]
+  const int32_t* inv;       // [n] internal row -> caller row of rhs, x and var (nullable)
+  const double* rhs;        // [n] caller order
+  const void* coef;         // frozen precisions: [E] {g_in, g_out}
+  const double* inv_pt;     // ... [n] 1 / P~
+  void* agg[2];             // [n] aggregate records by round parity
+  double tol;               // <= 0: exactly max_iter sweeps
+  int32_t max_iter, check_every;
+  DevStatus* st;            // written once, at the end (done = 0: the roll call failed, nothing was computed)
+  double* x;
+  double* var;              // nullable
+  void* cin_out;            // nullable: [2][E] {P, h} incoming messages by round parity
+  void* agg_out[3];         // nullable: [n] {P~, h~} of the last two rounds by round mod 3
+  ResCtl* ctl;
+  ResCtl* ctl_next;
+  uint64_t roll_limit, wait_limit;  // ticks of the wall clock
+};
+struct ResPlanHost {
+  int K = 0, lanes = 0, rows_cap = 0;
+  std::vector<int2> blk, lane;
+};
+struct ResPlan {
+  int K = 0, lanes = 0, nb = 0, rows_cap = 0, phase = 0, khz = 0;
+  int2* blk_d = nullptr;
+  int2* lane_d = nullptr;
+  ResCtl* ctl_d = nullptr;  // [2], used in turn
+};
+
 constexpr int kLayoutEdge = 1;     // outgoing message records + reverse-slot index
 constexpr int kLayoutNode = 2;     // node broadcast: aggregates published, edge pairs kept in place
 constexpr int kLayoutCompact = 3;  // node broadcast, one incoming message per slot, outgoing recomputed
@@ -388,6 +440,7 @@ struct Ctx {
   double* xperm_d = nullptr;
   double* vperm_d = nullptr;
   double* lsum_d = nullptr;           // [n] residual part of the earlier classes
+  ResPlan res;                        // resident solve (nb = 0: the system does not fit)
 
   // batched
   bool batched = false;
@@ -545,6 +598,19 @@ size_t bcast_state_bytes(int elt);
 size_t bcast_coef_bytes(int elt);
 size_t bcast_lds_bytes(int K, int elt);
 void dev_free(Ctx* c, void* p);
+
+// ---- resident solve (resident.hip) -----------------------------------------
+ResPlanHost plan_resident(const std::vector<int32_t>& off_ptr, int32_t n, int K, int lanes, int max_blocks,
+                          const std::vector<int32_t>& parts);
+// the plan, kept when the handle's solves can take it; before the autotuner,
+// which has nothing to choose then
+gabp_status setup_resident(Ctx* c);
+hipError_t launch_resident(Ctx* c, ResArgs a, bool honly, hipStream_t s);
+bool use_resident(const Ctx* c);
+// as solve_plain, with b, x and var in the caller's row order; *ran is false
+// (and nothing has been written) when the launch could not get the chip
+gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, double tol, int32_t max_iter,
+                           gabp_info* info, bool* ran);
 
 // ---- drivers (solve.hip) ---------------------------------------------------
 gabp_status solve_plain(Ctx* c, const double* b, double* x, double* var, double tol,

@@ -909,6 +909,67 @@ gabp_status solve_plain(Ctx* c, const double* b, double* x, double* var, double 
   return r;
 }
 
+bool use_resident(const Ctx* c) { return c->res.nb > 0 && c->layout == kLayoutCompact && c->gamma_used == 0.0; }
+
+// A plain FP64 solve in one resident launch.  Joint solves of a small system
+// stay with the one-workgroup kernels of small.hip; its mean-only solves on
+// frozen precisions come here.
+gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, double tol, int32_t max_iter,
+                           gabp_info* info, bool* ran) {
+  hipStream_t s = c->stream;
+  const bool exact = tol <= 0.0;
+  const bool reuse = (c->opts.flags & GABP_FLAG_REUSE_PRECISION) != 0;
+  const bool honly = reuse && c->frozen_valid && c->frozen_prec == GABP_FP64 && !exact;
+  *ran = false;
+  if (!honly && (small_fits(c->n, c->E) || small_rows_fit(c->n, c->max_degree))) return GABP_OK;
+  ResArgs a{};
+  a.off_ptr = c->off_ptr_d;
+  a.col = c->off_col_d;
+  a.a = c->a64_d;
+  a.diag = c->din64_d;
+  a.inv = c->perm_d ? c->inv_d : nullptr;
+  a.rhs = b;
+  a.coef = c->gcoef_d;
+  a.inv_pt = (const double*)c->inv_pt_d;
+  a.agg[0] = c->agg_d[0];
+  a.agg[1] = c->agg_d[1];
+  a.tol = tol;
+  a.max_iter = max_iter;
+  a.check_every = c->opts.check_every;
+  a.st = c->st_small_d;
+  a.x = x;
+  a.var = var;
+  if (!honly && (exact || reuse)) {  // read later by gabp_messages or the freeze
+    a.cin_out = c->bstate_d;
+    for (int q = 0; q < 3; ++q) a.agg_out[q] = c->agg_d[q];
+  }
+  *c->st_small_h = DevStatus{};
+  reset_timing(c);
+  GABP_HIP(c, launch_resident(c, a, honly, s));
+  GABP_HIP(c, hipStreamSynchronize(s));
+  const DevStatus st = *c->st_small_h;
+  if (!st.done) return GABP_OK;  // the chip was busy
+  *ran = true;
+  if (st.done != 1) return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
+  gabp_status r = map_status(c, st, exact);
+  if (info) {
+    info->sweeps = st.conv_round >= 0 ? st.conv_round : max_iter;
+    info->outer_iters = 0;
+    info->converged = (st.conv_round >= 0) ? 1 : 0;
+    info->status = r;
+    info->rel_residual = st.last_rel;
+    info->gamma = 0.0;
+    report_timing(c, info);
+  }
+  c->last_msg_round = (exact && r == GABP_OK) ? max_iter : -1;
+  if (r == GABP_OK && !exact && !honly && reuse) {
+    r = freeze<double>(c, held_round(c, st.conv_round, max_iter), c->din64_d, b, GABP_FP64);
+    if (r != GABP_OK) return r;
+    GABP_HIP(c, hipStreamSynchronize(s));
+  }
+  return r;
+}
+
 // Single-loop form of the correction method (Ch. 5 Sec. 5.3): FP64 sweeps of
 // Alg. 2 on A + Gamma whose prior potentials follow the damped feedback
 // h^(t) = b + Gamma ((1 - s) x^(t-2) + s x^(t-1)); the residual of A x = b
@@ -1195,6 +1256,10 @@ gabp_status autotune(Ctx* c) {
   const int epb = c->opts.edges_per_block;
   std::vector<int> layouts, Ks;
   const int req = layout_request(c);
+  if (c->res.nb > 0) {  // sweeps run in the resident launch: nothing to time
+    c->layout = kLayoutCompact;
+    return set_partition(c, epb ? epb / kBlock : 2);
+  }
   if (req) layouts.push_back(req);
   else layouts = {kLayoutEdge, kLayoutNode, kLayoutCompact};
   if (epb) Ks.push_back(epb / kBlock);
