@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libgabp.so")
 # measurement aid for the benchmark (random-gather cost), not part of the library
 PROBE_SOURCE = os.path.join("probe", "gather_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libgabp_probe.so")
-SOURCES = ["ingest.hip", "colour.hip", "partition.hip", "sweep.hip", "bcast.hip", "compact.hip", "serial.hip", "small.hip", "resident.hip", "noalloc.hip", "loading.hip", "solve.hip",
+SOURCES = ["ingest.hip", "colour.hip", "partition.hip", "sweep.hip", "bcast.hip", "compact.hip", "serial.hip", "small.hip", "resident.hip", "resident32.hip", "noalloc.hip", "loading.hip", "solve.hip",
            "batched.hip", "capi.hip"]
 ARCH = os.environ.get("GABP_OFFLOAD_ARCH", "gfx950")
 

@@ -293,9 +293,10 @@ gabp_status gabp_solve(gabp_handle h, const double* b, double* x, double* var, d
   if (var && !plain_mode(c)) return fail(c, GABP_E_ARG, "variances are only available in plain FP64 mode");
   if (!plain_mode(c) && !(single_loop_mode(c) && c->opts.precision == GABP_FP64) && !(tol > 0.0))
     return fail(c, GABP_E_ARG, "the correction loop needs tol > 0");
-  if (use_resident(c)) {
+  gabp_status r;
+  {
     bool ran = false;
-    const gabp_status r = solve_resident(c, b, x, var, tol, max_iter, info, &ran);
+    r = solve_resident(c, b, x, var, tol, max_iter, info, &ran);
     if (ran || r != GABP_OK) return r;
   }
   // renumbered handles solve in their internal numbering
@@ -306,7 +307,6 @@ gabp_status gabp_solve(gabp_handle h, const double* b, double* x, double* var, d
   const double* bi = perm ? c->bperm_d : b;
   double* xi = perm ? c->xperm_d : x;
   double* vi = (perm && var) ? c->vperm_d : var;
-  gabp_status r;
   if (plain_mode(c)) r = solve_plain(c, bi, xi, vi, tol, max_iter, info, true);
   else if (single_loop_mode(c) && c->opts.precision == GABP_FP64) r = solve_single_loop(c, bi, xi, tol, max_iter, info);
   else r = solve_outer(c, bi, xi, tol, max_iter, info);
@@ -367,11 +367,8 @@ gabp_status gabp_backward(gabp_handle h, const double* x, const double* grad_x, 
   if (!x || !grad_x || !grad_b) return fail(c, GABP_E_ARG, "NULL x, grad_x or grad_b");
   // A is symmetric: the adjoint system A^T lambda = dL/dx is a second GaBP solve against A
   bool resident = false;
-  gabp_status r = GABP_OK;
-  if (use_resident(c)) {
-    r = solve_resident(c, grad_x, grad_b, nullptr, tol, max_iter, info, &resident);
-    if (r < 0) return r;
-  }
+  gabp_status r = solve_resident(c, grad_x, grad_b, nullptr, tol, max_iter, info, &resident);
+  if (r < 0) return r;
   const bool perm = c->perm_d != nullptr && !resident;
   if (perm && !(c->bperm_d && c->xperm_d)) return fail(c, GABP_E_ARG, "internal order buffers missing");
   if (perm) GABP_HIP(c, launch_gather(grad_x, c->inv_d, c->bperm_d, c->n, c->stream));

@@ -293,15 +293,29 @@ struct ResArgs {
   const int32_t* off_ptr;   // off-diagonal CSR
   const int32_t* col;
   const double* a;
-  const double* diag;       // [n]
+  const double* d64;        // [n] A_ii
+  const void* diag;         // T [n] the sweeps' diagonal (loaded)
+  const void* chk_diag;     // T [n] single loop: the checked system's diagonal
   const int32_t* inv;       // [n] internal row -> caller row of rhs, x and var (nullable)
   const double* rhs;        // [n] caller order
   const void* coef;         // frozen precisions: [E] {g_in, g_out}
-  const double* inv_pt;     // ... [n] 1 / P~
-  void* agg[2];             // [n] aggregate records by round parity
+  const void* inv_pt;       // ... T [n] 1 / P~
+  void* agg[2];             // T [n] pairs: aggregate records by round parity
   double tol;               // <= 0: exactly max_iter sweeps
   int32_t max_iter, check_every;
-  DevStatus* st;            // written once, at the end (done = 0: the roll call failed, nothing was computed)
+  double damp;              // single loop: feedback step
+  // refinement and loading loops
+  double inner_tol;
+  int32_t inner_max, max_outer;
+  int32_t frozen;           // start from coef and inv_pt
+  int32_t want_freeze;      // freeze the precisions after the first converged inner solve
+  double* xbuf;             // [n] the iterate
+  void* coef_out;           // nullable: the frozen precisions, for later calls
+  void* inv_pt_out;
+  // written once, at the end (done = 0: the roll call failed, nothing was
+  // computed).  Outer loops: conv_round 0 or -1, error of the outer and pad of
+  // the inner solve, ticket: sweeps, last_round: outer steps, pad2: froze
+  DevStatus* st;
   double* x;
   double* var;              // nullable
   void* cin_out;            // nullable: [2][E] {P, h} incoming messages by round parity
@@ -314,8 +328,10 @@ struct ResPlanHost {
   int K = 0, lanes = 0, rows_cap = 0;
   std::vector<int2> blk, lane;
 };
+using ResKernel = void (*)(ResArgs);
+ResKernel res_kernel32(int lanes, int K, int mode);
 struct ResPlan {
-  int K = 0, lanes = 0, nb = 0, rows_cap = 0, phase = 0, khz = 0;
+  int mode = 0, K = 0, lanes = 0, nb = 0, rows_cap = 0, phase = 0, khz = 0;
   int2* blk_d = nullptr;
   int2* lane_d = nullptr;
   ResCtl* ctl_d = nullptr;  // [2], used in turn
@@ -605,10 +621,10 @@ ResPlanHost plan_resident(const std::vector<int32_t>& off_ptr, int32_t n, int K,
 // the plan, kept when the handle's solves can take it; before the autotuner,
 // which has nothing to choose then
 gabp_status setup_resident(Ctx* c);
-hipError_t launch_resident(Ctx* c, ResArgs a, bool honly, hipStream_t s);
-bool use_resident(const Ctx* c);
-// as solve_plain, with b, x and var in the caller's row order; *ran is false
-// (and nothing has been written) when the launch could not get the chip
+hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s);
+// a solve with b, x and var in the caller's row order; *ran is false (and
+// nothing has been written) when it has to take the launch-per-sweep path: no
+// plan, a small system, or a launch that could not get the chip
 gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, double tol, int32_t max_iter,
                            gabp_info* info, bool* ran);
 

@@ -1,0 +1,820 @@
+// Resident solve of a mid-sized system: every sweep, residual check and stop
+// decision of a compact-layout solve in ONE launch whose workgroups stay on the
+// chip, one per CU, with the messages in registers.  The plain FP64 iteration,
+// the single loop of Ch. 5 Sec. 5.3, and the refinement and loading loops with
+// their inner solves (FP32 or FP64), freeze and FP64 residuals.
+//
+// What bounds the launch-per-sweep path on such systems: a sweep launch and
+// its finish kernel cost 10-12 us of dispatch and drain whatever the size, and
+// each sweep streams 44 B per slot (column, A_ij, one message pair in and out)
+// although the chip's registers (128 MB) could hold the whole state.  Here
+//   * a row's slots are dealt K at a time to consecutive lanes of one wave (a
+//     chain; one lane for rows of at most K slots).  A lane keeps its slots'
+//     columns, coefficients and the incoming messages of the last two rounds
+//     in registers (the compact recurrence of compact.hip: in^(t) depends on
+//     in^(t-2) of the same slot alone), so a sweep moves no message at all;
+//   * the chain's lanes add their messages in turn, in CSR order after the
+//     diagonal, so every sum is rounded as the sweep kernels round it; the last
+//     lane of the chain holds the new aggregate and hands it back to the chain;
+//   * only the node aggregates cross workgroups, in two buffers by round
+//     parity.  They are stored with agent scope (written through) and gathered
+//     with agent scope loads (past the L1, coherent across the XCDs), so no
+//     cache is written back or invalidated between sweeps.  Neighbours of the
+//     same workgroup are read from LDS;
+//   * the sweeps are separated by a grid barrier over counters in memory: one
+//     line per group of 8 workgroup ids (the XCD of a round-robin dispatch),
+//     one root, one release line per group.  Measured alone on 256 workgroups:
+//     1.84 us, against 3.76 us with one counter and 3.09 us with a flag per
+//     workgroup polled by all; up to 32 workgroups one counter is the fastest
+//     (1.0 us).
+// The workgroups must all be resident at once for the barrier to end.  The
+// host launches no more of them than the device holds, and the first barrier
+// is a roll call with a time limit: if the device is busy with other work and
+// not every workgroup has started in time, the launch ends without touching
+// its outputs and the host takes the launch-per-sweep path instead.  Once the
+// roll call has succeeded every workgroup is running, so later waits end.
+//
+// Measured against a launch per sweep and its finish kernel, whole solves to
+// 1e-10: 181 x 173 grid with variances 669 -> 286 us, G(n, 4n) with n = 30011
+// on frozen precisions 350 -> 160 us, 64^3 grid forward and adjoint 6.67 ->
+// 1.94 ms (a checked mean-only sweep of its 1.5 M slots takes 6.3 us instead
+// of 24), 29 x 23 grid on frozen precisions 1004 -> 201 us in one workgroup.
+// The loops of inner solves also lose the host's status reads (20-30 us each)
+// and the launches between the phases: FP32 + refinement on G(n, 4n) with n =
+// 130003 596 -> 355 us, the double loop on B^T B + 0.1 I with n = 30000 50.5 ->
+// 27.7 ms.
+//
+// The arithmetic is that of the compact sweep kernels operation for operation
+// (products and sums separately rounded): x, the variances and the messages
+// equal theirs bit for bit; only the residual norm is summed in another order.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "gabp_internal.h"
+
+#pragma clang fp contract(off)
+
+namespace gabp {
+
+namespace {
+
+constexpr int kRL = kResLanes;
+constexpr int kGroups = 8;
+constexpr int kFlatBlocks = 32;  // at most this many workgroups share one counter
+
+template <typename T>
+using vec2 = T __attribute__((ext_vector_type(2)));
+using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
+using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
+
+#define AGENT_LOAD(p) __hip_atomic_load((p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+#define AGENT_STORE(p, v) __hip_atomic_store((p), (v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+#define AGENT_ADD(p, v) __hip_atomic_fetch_add((p), (v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+
+// Cache policy of an agent-scope access (the sc1 bit): loads pass the L1,
+// stores are written through.
+constexpr int kAgentPolicy = 16;
+
+// Lane exchanges on the VALU (DPP); a lane without a source gets `old`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double old, double v) {
+  const uint64_t o = __builtin_bit_cast(uint64_t, old), b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp(float old, float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old),
+                                                               __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false));
+}
+constexpr int kRowShr = 0x110, kBcast15 = 0x142, kBcast31 = 0x143, kWaveShl1 = 0x130, kWaveShr1 = 0x138;
+__device__ __forceinline__ double readlane_r(double v, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double uni_r(double v) { return readlane_r(v, 0); }
+// Sum over the first 16 lanes, over the wave: in scalar registers, in a fixed order.
+__device__ __forceinline__ double sum16(double v) {
+  v += dpp<kRowShr + 1, 0xf>(0.0, v);
+  v += dpp<kRowShr + 2, 0xf>(0.0, v);
+  v += dpp<kRowShr + 4, 0xf>(0.0, v);
+  v += dpp<kRowShr + 8, 0xf>(0.0, v);
+  return v;
+}
+__device__ __forceinline__ double wsum_r(double v) {
+  v = sum16(v);
+  v += dpp<kBcast15, 0xa>(0.0, v);
+  v += dpp<kBcast31, 0xc>(0.0, v);
+  return readlane_r(v, 63);
+}
+
+// Workgroup barrier ordering LDS only.
+__device__ __forceinline__ void lds_barrier_r() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// A buffer of n records that the workgroups share: a node's aggregates or x.
+struct RecBuf {
+  __amdgpu_buffer_rsrc_t r;
+};
+template <typename R>
+__device__ __forceinline__ RecBuf rec_buf(void* base, int32_t n) {
+  return RecBuf{__builtin_amdgcn_make_buffer_rsrc(base, 0, n * (int)sizeof(R), 0x00027000)};
+}
+// off: byte offset; beyond the buffer a load returns zero without an access
+template <typename R>
+__device__ __forceinline__ R ld_rec(const RecBuf& b, uint32_t off) {
+  if constexpr (sizeof(R) == 16)
+    return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b128(b.r, (int)off, 0, kAgentPolicy));
+  else
+    return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(b.r, (int)off, 0, kAgentPolicy));
+}
+template <typename R>
+__device__ __forceinline__ void st_rec(const RecBuf& b, int i, R v) {
+  if constexpr (sizeof(R) == 16)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b.r, i * (int)sizeof(R), 0, kAgentPolicy);
+  else
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b.r, i * (int)sizeof(R), 0, kAgentPolicy);
+}
+constexpr uint32_t kNoRec = 0xfffffff0u;
+__device__ __forceinline__ void st_rec(const RecBuf& b, int i, vec2<double> v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b.r, i * (int)sizeof(vec2<double>), 0,
+                                         kAgentPolicy);
+}
+
+// Partial sums travel without a wait between them and the barrier arrival: the
+// low two bits of a partial's mantissa (2^-50 of its value) carry the check's
+// sequence number mod 4, and a reader waits until they match.  Two sets by the
+// number's parity: a workgroup stores check s + 1 before the barrier that says
+// every other has read check s, and check s + 2 after it.
+__device__ __forceinline__ uint64_t tag_partial(double v, uint32_t seq) {
+  return (__builtin_bit_cast(uint64_t, v) & ~3ull) | (seq & 3u);
+}
+
+enum GridState : int { kGo = 1, kAbort = 2 };
+enum WaitResult : int { kWaitOk = 0, kWaitBad = 1, kWaitEnd = 2 };
+
+// The workgroup's place in the grid barrier.
+struct GridPos {
+  uint32_t nb, grp, gsize, ngrp;
+};
+__device__ __forceinline__ GridPos grid_pos() {
+  GridPos p;
+  p.nb = gridDim.x;
+  if (p.nb <= (uint32_t)kFlatBlocks) {
+    p.grp = 0;
+    p.gsize = p.nb;
+    p.ngrp = 1;
+  } else {
+    p.grp = blockIdx.x % kGroups;
+    p.ngrp = kGroups;
+    p.gsize = (p.nb + kGroups - 1 - p.grp) / kGroups;
+  }
+  return p;
+}
+
+// One lane: arrive at barrier `ep` (1, 2, ...).  Counters hold arrivals in the
+// low 40 bits and raised flags above.  Returns true for the last arrival of
+// the whole grid, with the flags of all in *bad.
+__device__ __forceinline__ bool grid_arrive(ResCtl* c, const GridPos& p, uint32_t ep, bool bad, bool* any_bad) {
+  const uint64_t inc = 1ull + (bad ? (1ull << 40) : 0ull);
+  const uint64_t mask = (1ull << 40) - 1;
+  uint64_t v = AGENT_ADD(&c->grp[p.grp].v, inc) + inc;
+  if ((v & mask) != (uint64_t)ep * p.gsize) return false;
+  bool b = (v >> 40) != 0;
+  if (p.ngrp > 1) {
+    const uint64_t inc2 = 1ull + (b ? (1ull << 40) : 0ull);
+    v = AGENT_ADD(&c->root.v, inc2) + inc2;
+    if ((v & mask) != (uint64_t)ep * p.ngrp) return false;
+    b = (v >> 40) != 0;
+  }
+  *any_bad = b;
+  return true;
+}
+
+// One lane: wait for barrier `ep`.  The release word holds the barrier number
+// and the flags raised before it, so every workgroup leaves it with the same
+// answer.
+__device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t ep, bool last, bool any_bad,
+                                         uint64_t limit) {
+  const uint64_t word = (uint64_t)ep | (any_bad ? (1ull << 63) : 0ull);
+  if (last)
+    for (uint32_t k = 0; k < p.ngrp; ++k) AGENT_STORE(&c->rel[k].v, word);
+  const uint64_t t0 = wall_clock64();
+  for (;;) {
+    const uint64_t v = AGENT_LOAD(&c->rel[p.grp].v);
+    if ((v & ~(1ull << 63)) >= ep) return (v >> 63) ? kWaitBad : kWaitOk;
+    if (wall_clock64() - t0 > limit) return kWaitEnd;
+  }
+}
+
+// The roll call: the last arrival turns the state to kGo, a workgroup that has
+// waited too long to kAbort, whichever comes first.
+__device__ __forceinline__ bool roll_call(ResCtl* c, const GridPos& p, uint64_t limit) {
+  bool any_bad = false;
+  if (grid_arrive(c, p, 1, false, &any_bad)) {
+    uint32_t want = 0;
+    __hip_atomic_compare_exchange_strong(&c->state, &want, (uint32_t)kGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const uint64_t t0 = wall_clock64();
+  for (;;) {
+    const uint32_t s = AGENT_LOAD(&c->state);
+    if (s) return s == kGo;
+    if (wall_clock64() - t0 > limit) {
+      uint32_t want = 0;
+      __hip_atomic_compare_exchange_strong(&c->state, &want, (uint32_t)kAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// What a launch runs.
+enum ResMode : int {
+  kResJoint = 0,   // plain sweeps
+  kResFrozen = 1,  // mean-only sweeps on the handle's frozen precisions
+  kResOuter = 2,   // refinement / loading loop around inner solves
+  kResLoop = 3,    // the single loop: plain sweeps with damped feedback of the means
+  kResOuterLoop = 4,  // refinement around single-loop inner solves
+  kResRefine = 5   // kResOuter without frozen precisions (fewer registers)
+};
+
+// LANES lanes per workgroup, one workgroup per CU: 128 VGPRs at 1024 lanes, of
+// which the FP64 messages of K slots take 8 K, so there A_ij, the neighbours
+// and the rows' prior live in LDS; with fewer lanes they stay in registers too.
+template <typename T, int LANES, int K, int MODE>
+__global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
+  constexpr bool OUTER = MODE == kResOuter || MODE == kResOuterLoop || MODE == kResRefine;
+  constexpr bool FEED = MODE == kResLoop || MODE == kResOuterLoop;
+  constexpr bool REG = LANES < kRL;
+  constexpr int NW = LANES / 64;
+  using V2 = vec2<T>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double s_red[3][16];  // by sweep parity, then the outer residual's
+  __shared__ double s_tot;
+  // non-finite message flags by sweep mod 3: sweep t sets [t % 3] and clears
+  // [(t + 1) % 3], which no lane reads or sets until sweep t + 1
+  __shared__ int s_bad[3];
+  __shared__ int s_res;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = A.n;
+  const int nb = gridDim.x;
+  // workgroup id -> part of the rows, so that consecutive parts share an XCD
+  const int b = (blockIdx.x % kGroups) * (nb / kGroups) + min((int)(blockIdx.x % kGroups), nb % kGroups) +
+                (int)blockIdx.x / kGroups;
+  const int r0 = A.blk[b].x, nrow = A.blk[b].y;
+  const int cap = A.rows_cap;
+  V2* s_agg = (V2*)smem;                       // [2][cap] the workgroup's aggregates by round parity
+  double* s_xo = (double*)(s_agg + 2 * cap);   // [cap] outer loop: the iterate
+  T* s_x = (T*)(s_xo + (OUTER ? cap : 0));     // [2][cap] the means of the last rounds
+  double* s_a = (double*)(s_x + 2 * cap);      // 1024 lanes only: [K][lanes] A_ij of the lane's slots,
+  double* s_d = s_a + K * LANES;               // [lanes] A_ii and b_i of the lane's row,
+  double* s_b = s_d + LANES;
+  int* s_c = (int*)(s_b + LANES);              // [K][lanes] the slots' neighbours
+  ResCtl* ctl = A.ctl;
+  const GridPos gp = grid_pos();
+
+  // ---- set-up: the lane's slots and row ------------------------------------
+  const int2 ld = A.lane[(size_t)b * LANES + tid];
+  const int row = ld.x, pos = ld.y & 0xffff, len = ld.y >> 16;
+  const bool own = row >= 0;
+  const bool tail = own && pos == len - 1;
+  int cnt = 0;
+  int s0 = 0;
+  double d64 = 1.0, b64 = 0.0;  // A_ii and b_i
+  T din = 1, dchk = 1, ip = 0;  // the sweeps' diagonal, the checked one, the frozen 1 / P~
+  if (own) {
+    s0 = A.off_ptr[row] + pos * K;
+    cnt = min(K, A.off_ptr[row + 1] - s0);
+    b64 = A.rhs[A.inv ? A.inv[row] : row];
+    din = ((const T*)A.diag)[row];
+    d64 = OUTER ? A.d64[row] : (double)din;
+    if (FEED) dchk = ((const T*)A.chk_diag)[row];
+    if (MODE == kResFrozen || (MODE == kResOuter && A.frozen)) ip = ((const T*)A.inv_pt)[row];
+  }
+  if (!REG) {
+    s_d[tid] = d64;
+    s_b[tid] = b64;
+  }
+  int wmax = 1;  // longest chain of the wave
+  while (__any(own && len > wmax)) ++wmax;
+  // the slots' neighbours: a row of the same workgroup as ~(LDS index), else
+  // the byte offset of its record; a slot the row does not have reads record 0
+  // of the workgroup and contributes nothing
+  int cc[K];
+  double aa[K];
+  // joint: incoming messages {P, h} of the even and the odd rounds; frozen
+  // precisions: {g_in, g_out} and the h messages of the two parities
+  T mP0[K], mH0[K], mP1[K], mH1[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    int c = ~0;
+    double av = 0.0;
+    mP0[k] = mH0[k] = mP1[k] = mH1[k] = 0;
+    if (k < cnt) {
+      c = A.col[s0 + k];
+      c = (unsigned)(c - r0) < (unsigned)nrow ? ~(c - r0) : c * (int)sizeof(V2);
+      av = A.a[s0 + k];
+      if (MODE == kResFrozen || (MODE == kResOuter && A.frozen)) {
+        const V2 cf = ((const V2*)A.coef)[s0 + k];
+        mP0[k] = cf.x;
+        mP1[k] = cf.y;
+      }
+    }
+    if (REG) {
+      cc[k] = c;
+      aa[k] = av;
+    } else {
+      s_c[k * LANES + tid] = c;
+      s_a[k * LANES + tid] = av;
+    }
+  }
+  auto slot_a = [&](int k) -> double { return REG ? aa[k] : s_a[k * LANES + tid]; };
+  auto row_d = [&]() -> double { return REG ? d64 : s_d[tid]; };
+  auto row_b = [&]() -> double { return REG ? b64 : s_b[tid]; };
+  const RecBuf buf0 = rec_buf<V2>(A.agg[0], n), buf1 = rec_buf<V2>(A.agg[1], n);
+  // own aggregates of the last two rounds, and the means of the last (two)
+  T o1P = 0, o1h = 0, o2P = 0, o2h = 0, x1 = 0, x2 = 0;
+  T rhs = (T)b64;  // right-hand side of the sweeps
+  // round 0, the prior; the record a neighbour gathers is {P~, h~}, or
+  // {mean, h~} with frozen precisions
+  auto publish_prior = [&](bool honly) {
+    o1P = honly ? ip : din;
+    o1h = rhs;
+    o2P = o2h = x2 = 0;
+    x1 = honly ? rhs * ip : rhs / din;
+    if (tail) {
+      const V2 v = {honly ? x1 : din, rhs};
+      if (nb > 1) st_rec<V2>(buf0, row, v);
+      s_agg[row - r0] = v;
+      s_x[row - r0] = x1;
+    }
+  };
+  publish_prior(MODE == kResFrozen || (MODE == kResOuter && A.frozen));
+  if (tid < 3) s_bad[tid] = 0;
+  if (tid == 0) s_res = 0;
+  // the other control block is idle during this launch: cleared for the next one
+  if (blockIdx.x == 0 && nb > 1)
+    for (int i = tid; i < (int)(sizeof(ResCtl) / 8); i += LANES) ((uint64_t*)A.ctl_next)[i] = 0ull;
+  // ||b||, and the roll call
+  {
+    const double v = wsum_r(tail ? b64 * b64 : 0.0);
+    if (lane == 0) s_red[0][wave] = v;
+  }
+  uint32_t seq = 1;  // checks so far (the norm is the first): the partials' tag
+  uint32_t ep = 1;   // grid barriers so far
+  auto block_sum = [&](const double* red) -> double {
+    return readlane_r(sum16(lane < NW ? red[lane] : 0.0), 15);
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (nb > 1) {
+    if (wave == 0) {
+      const double v = block_sum(s_red[0]);
+      if (tid == 0) {
+        AGENT_STORE(&ctl->part[seq & 1][b], tag_partial(v, seq));
+        s_res = roll_call(ctl, gp, A.roll_limit) ? 0 : 1;
+      }
+    }
+    __syncthreads();
+    if (s_res) return;
+  }
+  bool lost = false;
+  // the sum of the workgroups' partials: formed by wave 0, read by all
+  auto total = [&](const double* red) -> double {
+    if (nb == 1) return block_sum(red);
+    if (wave == 0) {
+      constexpr int kPer = kResMaxBlocks / 64;
+      uint64_t u[kPer];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j)
+        u[j] = lane + 64 * j < nb ? AGENT_LOAD(&ctl->part[seq & 1][lane + 64 * j]) : (seq & 3u);
+      const uint64_t t0 = wall_clock64();
+      bool late = false;
+      double v = 0.0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        while ((u[j] & 3u) != (seq & 3u) && !late) {
+          u[j] = AGENT_LOAD(&ctl->part[seq & 1][lane + 64 * j]);
+          late = wall_clock64() - t0 > A.wait_limit;
+        }
+        v += __builtin_bit_cast(double, u[j] & ~3ull);
+      }
+      if (__any(late)) s_res = kWaitEnd;
+      v = wsum_r(v);
+      if (lane == 0) s_tot = v;
+    }
+    lds_barrier_r();
+    if (s_res == kWaitEnd) lost = true;
+    return uni_r(s_tot);
+  };
+  // All workgroups: records stored before it are visible after it.  red
+  // (nullable): the waves' partials of a check, sent along; flag: an LDS word,
+  // nonzero where a message was not finite.  Returns whether any was.
+  auto grid_barrier = [&](const double* red, const int* flag) -> bool {
+    ++ep;
+    if (nb == 1) {
+      lds_barrier_r();
+      return flag && *flag;
+    }
+    // the wave's records have reached memory before the workgroup arrives
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier_r();
+    if (wave == 0) {
+      const double v = red ? block_sum(red) : 0.0;
+      if (tid == 0) {
+        if (red) AGENT_STORE(&ctl->part[seq & 1][b], tag_partial(v, seq));
+        bool any_bad = false;
+        const bool last = grid_arrive(ctl, gp, ep, flag && *flag, &any_bad);
+        s_res = grid_wait(ctl, gp, ep, last, any_bad, A.wait_limit);
+      }
+    }
+    lds_barrier_r();
+    asm volatile("" ::: "memory");
+    if (s_res == kWaitEnd) lost = true;
+    return s_res == kWaitBad;
+  };
+  const double bnorm = uni_r(sqrt(total(s_red[0])));
+
+  const int ce = max(1, A.check_every);
+  // result of a run of sweeps (kept for the caller of the run)
+  double last_rel = -1.0, prev_rel = -1.0;
+  int last_round = -1, prev_round = -1, conv = -1, err = 0;
+
+  // Sweeps on the system with right-hand side `rhs` (round 0 published) to a
+  // relative residual of tol (<= 0: exactly M sweeps): conv, err and the
+  // rounds T = min(conv + 1, M) and T - 1 in the registers.
+  auto run = [&](auto honly_c, const double tol_in, const int M, const double norm) {
+    constexpr bool HONLY = decltype(honly_c)::value;
+    const bool exact = !(tol_in > 0.0);
+    const double tol = exact ? -1.0 : tol_in;
+    auto in_set = [&](int j) { return j == M || (j % ce) == 0; };
+    auto rel_of = [&](double tot) {
+      const double rn = sqrt(tot);
+      return norm > 0.0 ? rn / norm : rn;
+    };
+    // the stop test forms the relative residual only near a threshold: a sum of
+    // squares clearly above (tol |b|)^2 cannot pass, one clearly below
+    // (1e8 |b|)^2 cannot diverge; the decisions are the exact ones
+    const double scale = norm > 0.0 ? norm : 1.0;
+    double conv_pre = tol >= 0.0 ? (tol * scale) * (tol * scale) * (1.0 + 1e-6) : -1.0;
+    if (tol > 0.0 && !(conv_pre > 1e-280 && conv_pre < 1e280)) conv_pre = INFINITY;  // out of range: always exact
+    conv_pre = uni_r(conv_pre);
+    const double div_pre = uni_r((kDivergeLimit * scale) * (kDivergeLimit * scale) * (1.0 - 1e-6));
+    double last_tot = 0.0, prev_tot = 0.0;
+    bool pending = false;  // a check whose partials are on their way
+    conv = last_round = prev_round = -1;
+    err = 0;
+
+    // One sweep: the gathers of round t-1, then the stop decision on the check
+    // that the previous sweep made (round t-2; its partials arrive while the
+    // gathers are in flight), then the update.  Returns true when the run ends.
+    auto sweep = [&](auto odd_c, const int t) -> bool {
+      constexpr bool ODD = decltype(odd_c)::value;
+      const bool upd = t <= M;
+      const bool ck = exact ? (t == M + 1) : (t <= M + 1 && in_set(t - 1));
+      const bool live = upd || ck;
+      const bool ck_next = upd && (exact ? (t == M) : in_set(t));  // sweep t+1 checks round t
+      constexpr int p1 = ODD ? 0 : 1, pn = ODD ? 1 : 0;
+      const bool first = ODD && t == 1;
+      int cr[K];
+      V2 g[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) cr[k] = REG ? cc[k] : s_c[k * LANES + tid];
+      if (nb > 1) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) g[k] = ld_rec<V2>(ODD ? buf0 : buf1, cr[k] < 0 ? kNoRec : (uint32_t)cr[k]);
+      }
+      if (pending) {
+        const double tot = total(s_red[p1]);
+        prev_tot = last_tot;
+        prev_round = last_round;
+        last_tot = tot;
+        last_round = t - 2;
+        pending = false;
+        if (tot <= conv_pre && rel_of(tot) <= tol) conv = t - 2;
+        else if (!(tot < div_pre) && !(rel_of(tot) <= kDivergeLimit)) err |= kErrDiverged;
+      }
+      if (conv >= 0 || err || lost || !live) return true;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const V2 l = s_agg[p1 * cap + (cr[k] < 0 ? ~cr[k] : 0)];
+        if (nb == 1 || cr[k] < 0) g[k] = l;
+      }
+      bool bad = false;
+      T ax[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const T av = (T)slot_a(k);
+        ax[k] = 0;
+        if (ck) {
+          if (HONLY) {
+            ax[k] = av * g[k].x;
+          } else {
+            T xc = s_x[p1 * cap + (cr[k] < 0 ? ~cr[k] : 0)];
+            if (__any(cr[k] >= 0)) {
+              const T q = g[k].y / g[k].x;
+              if (cr[k] >= 0) xc = q;
+            }
+            ax[k] = av * xc;
+          }
+        }
+        if (upd) {
+          const bool has = k < cnt;
+          if (HONLY) {
+            T hout = 0;
+            if (!first) hout = mP1[k] * (o2h - (ODD ? mH1[k] : mH0[k]));
+            const T hn = mP0[k] * (g[k].y - hout);
+            if (ODD) mH1[k] = hn;
+            else mH0[k] = hn;
+            bad |= has && !isfinite(hn);
+          } else {
+            // in^(t) = F(A_c^(t-1), out^(t-1)), out^(t-1) = F(A_own^(t-2), in^(t-2))
+            T Pout = 0, hout = 0;
+            if (!first) {
+              const T inv_out = T(1) / (o2P - (ODD ? mP1[k] : mP0[k]));
+              Pout = -av * av * inv_out;
+              hout = -av * (o2h - (ODD ? mH1[k] : mH0[k])) * inv_out;
+            }
+            const T inv_in = T(1) / (g[k].x - Pout);
+            const T Pn = -av * av * inv_in;
+            const T hn = -av * (g[k].y - hout) * inv_in;
+            if (ODD) {
+              mP1[k] = Pn;
+              mH1[k] = hn;
+            } else {
+              mP0[k] = Pn;
+              mH0[k] = hn;
+            }
+            bad |= has && !(isfinite(Pn) && isfinite(hn));
+          }
+        }
+        // one slot's divisions at a time: interleaved, they would not fit 128 registers
+        if (!REG) __builtin_amdgcn_sched_barrier(0);
+      }
+      // row sums along the chain, in CSR order after the diagonal; the residual
+      // of round t-1
+      T P, h;
+      double acc = 0.0;
+      if (OUTER || FEED) {
+        P = din;
+        h = rhs;
+      } else {
+        P = (T)row_d();
+        h = (T)row_b();
+      }
+      if (ck) acc = (double)h - (double)(FEED ? dchk : P) * (double)x1;
+      if (FEED) h = h + (din - dchk) * ((T(1) - (T)A.damp) * x2 + (T)A.damp * x1);
+      for (int c = 0; c < wmax; ++c) {
+        if (c > 0) {
+          const T Pu = dpp<kWaveShr1, 0xf>(P, P), hu = dpp<kWaveShr1, 0xf>(h, h);
+          const double au = dpp<kWaveShr1, 0xf>(acc, acc);
+          if (pos == c) {
+            P = Pu;
+            h = hu;
+            acc = au;
+          }
+        }
+        if (pos == c) {
+#pragma unroll
+          for (int k = 0; k < K; ++k)
+            if (k < cnt) {
+              if (!HONLY) P += ODD ? mP1[k] : mP0[k];
+              h += ODD ? mH1[k] : mH0[k];
+              if (ck) acc -= (double)ax[k];
+            }
+        }
+      }
+      if (upd) {
+        for (int c = wmax - 2; c >= 0; --c) {  // the sums back to the head of the chain
+          const T Pd = dpp<kWaveShl1, 0xf>(P, P), hd = dpp<kWaveShl1, 0xf>(h, h);
+          if (pos == c && pos < len - 1) {
+            P = Pd;
+            h = hd;
+          }
+        }
+        if (HONLY) P = ip;
+        o2P = o1P;
+        o2h = o1h;
+        o1P = P;
+        o1h = h;
+        if (FEED) x2 = x1;
+        if (HONLY) x1 = h * ip;
+        else if (FEED || ck_next) x1 = h / P;
+        if (tail) {
+          const V2 v = {HONLY ? x1 : P, h};
+          if (nb > 1) st_rec<V2>(ODD ? buf1 : buf0, row, v);
+          s_agg[pn * cap + row - r0] = v;
+          if (!HONLY) s_x[pn * cap + row - r0] = x1;
+        }
+      }
+      if (tid == 0) s_bad[(t + 1) % 3] = 0;
+      if (bad) s_bad[t % 3] = 1;
+      if (ck) {
+        const double v = wsum_r(tail ? acc * acc : 0.0);
+        if (lane == 0) s_red[pn][wave] = v;
+        ++seq;
+        pending = true;
+      }
+      if (grid_barrier(ck ? s_red[pn] : nullptr, &s_bad[t % 3])) err |= kErrNonfinite;
+      return err != 0 || lost;  // a non-finite message ends the solve
+    };
+    for (int t = 1;; t += 2) {
+      if (sweep(std::true_type{}, t)) break;
+      if (sweep(std::false_type{}, t + 1)) break;
+    }
+    last_rel = last_round >= 0 ? rel_of(last_tot) : -1.0;
+    prev_rel = prev_round >= 0 ? rel_of(prev_tot) : -1.0;
+  };
+
+  if constexpr (!OUTER) {
+    constexpr bool HONLY = MODE == kResFrozen;
+    const int M = A.max_iter;
+    run(std::integral_constant<bool, HONLY>{}, A.tol, M, bnorm);
+    // ---- results: the returned round and the state it leaves ---------------
+    // the own aggregates are of rounds T = min(conv + 1, M) and T - 1
+    const int ret = conv >= 0 ? conv : M;
+    const int T1 = min(ret + (conv >= 0 ? 1 : 0), M);
+    const T rP = ret == T1 ? o1P : o2P, rh = ret == T1 ? o1h : o2h;
+    if (tail) {
+      const int out = A.inv ? A.inv[row] : row;
+      A.x[out] = (double)(HONLY ? rh * ip : rh / rP);
+      if (A.var) A.var[out] = (double)(HONLY ? ip : T(1) / rP);
+      if (A.agg_out[0] && !HONLY) {
+        ((V2*)A.agg_out[T1 % 3])[row] = V2{o1P, o1h};
+        if (T1 >= 1) ((V2*)A.agg_out[(T1 - 1) % 3])[row] = V2{o2P, o2h};
+      }
+    }
+    if (A.cin_out && !HONLY) {
+      const int s0 = own ? A.off_ptr[row] + pos * K : 0;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (k < cnt) {
+          ((V2*)A.cin_out)[s0 + k] = V2{mP0[k], mH0[k]};
+          ((V2*)A.cin_out)[(size_t)A.E + s0 + k] = V2{mP1[k], mH1[k]};
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+      DevStatus st{};
+      st.done = lost ? 2 : 1;
+      st.conv_round = conv;
+      st.error = err;
+      st.last_rel = last_rel;
+      st.last_round = last_round;
+      st.prev_rel = prev_rel;
+      st.prev_round = prev_round;
+      *A.st = st;
+    }
+  } else {
+    // ---- the outer loop: x <- x + d, d an inner solve on r = b - A x --------
+    const RecBuf bufx = rec_buf<double>(A.xbuf, n);
+    double x = 0.0;      // the row's iterate
+    double rnorm = bnorm;
+    bool frozen = MODE == kResOuter && A.frozen;  // else false throughout
+    bool froze = false;
+    int outer = 0, sweeps = 0, oconv = -1, ierr = 0, oerr = 0;
+    // step 0 (x = 0, r = b): its residual is relative to itself
+    double orel = bnorm > 0.0 ? 1.0 : bnorm;
+    if (orel <= A.tol) oconv = 0;
+    else if (!(orel <= kDivergeLimit)) oerr = kErrDiverged;
+    while (oconv < 0 && !oerr && !lost && outer < A.max_outer && sweeps < A.max_iter) {
+      const int M = max(0, min(A.inner_max, A.max_iter - sweeps));
+      const bool will_freeze = MODE == kResOuter && A.want_freeze && !frozen;
+      if constexpr (MODE == kResOuter) {
+        if (frozen) run(std::true_type{}, A.inner_tol, M, rnorm);
+        else run(std::false_type{}, A.inner_tol, M, rnorm);
+      } else {
+        run(std::false_type{}, A.inner_tol, M, rnorm);
+      }
+      if (err || lost) {
+        ierr = err;
+        break;
+      }
+      const int ret = conv >= 0 ? conv : M;
+      const int T1 = min(ret + (conv >= 0 ? 1 : 0), M);
+      sweeps += ret;
+      const T rP = ret == T1 ? o1P : o2P, rh = ret == T1 ? o1h : o2h;
+      x += (double)(frozen ? rh * ip : rh / rP);
+      // the frozen coefficients of the messages of round T1 replace the P
+      // messages: g_in = -a / (P~_c - P_out), g_out = -a / (P~_own - P_in)
+      if (MODE == kResOuter && will_freeze && conv >= 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          const T av = (T)slot_a(k);
+          const bool odd = (T1 & 1) != 0;
+          const int c = REG ? cc[k] : s_c[k * LANES + tid];
+          V2 g = s_agg[(T1 & 1) * cap + (c < 0 ? ~c : 0)];  // round T1 of the neighbour
+          if (c >= 0) g = ld_rec<V2>(odd ? buf1 : buf0, (uint32_t)c);
+          const T Pin = odd ? mP1[k] : mP0[k], Pold = odd ? mP0[k] : mP1[k];
+          T Pout = 0;
+          if (T1 > 0) {
+            const T inv_o = T(1) / (o2P - Pold);
+            Pout = -av * av * inv_o;
+          }
+          const T inv_in = T(1) / (g.x - Pout);
+          const T inv_out = T(1) / (o1P - Pin);
+          mP0[k] = k < cnt ? -av * inv_in : T(0);
+          mP1[k] = k < cnt ? -av * inv_out : T(0);
+          if (!REG) __builtin_amdgcn_sched_barrier(0);
+        }
+        ip = T(1) / o1P;
+        frozen = froze = true;
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        mH0[k] = mH1[k] = 0;
+        if (!frozen) mP0[k] = mP1[k] = 0;
+      }
+      if (tail) {
+        if (nb > 1) st_rec<double>(bufx, row, x);
+        s_xo[row - r0] = x;
+      }
+      grid_barrier(nullptr, nullptr);
+      if (lost) break;
+      // r = b - A x in FP64, the products subtracted in CSR order
+      double xg[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const int c = REG ? cc[k] : s_c[k * LANES + tid];
+        xg[k] = 0.0;
+        if (nb > 1)
+          xg[k] = ld_rec<double>(bufx, c < 0 ? kNoRec : (uint32_t)c / (uint32_t)(sizeof(V2) / sizeof(double)));
+        const double l = s_xo[c < 0 ? ~c : 0];
+        if (nb == 1 || c < 0) xg[k] = l;
+      }
+      double acc = __builtin_fma(-row_d(), x, row_b());
+#pragma unroll
+      for (int k = 0; k < K; ++k) xg[k] = slot_a(k) * xg[k];
+      for (int c = 0; c < wmax; ++c) {
+        if (c > 0) {
+          const double au = dpp<kWaveShr1, 0xf>(acc, acc);
+          if (pos == c) acc = au;
+        }
+        if (pos == c) {
+#pragma unroll
+          for (int k = 0; k < K; ++k)
+            if (k < cnt) acc -= xg[k];
+        }
+      }
+      for (int c = wmax - 2; c >= 0; --c) {
+        const double ad = dpp<kWaveShl1, 0xf>(acc, acc);
+        if (pos == c && pos < len - 1) acc = ad;
+      }
+      {
+        const double v = wsum_r(tail ? acc * acc : 0.0);
+        if (lane == 0) s_red[2][wave] = v;
+      }
+      rhs = (T)acc;
+      publish_prior(frozen);
+      ++seq;
+      grid_barrier(s_red[2], nullptr);
+      rnorm = uni_r(sqrt(total(s_red[2])));
+      if (lost) break;
+      ++outer;
+      orel = bnorm > 0.0 ? rnorm / bnorm : rnorm;
+      if (orel <= A.tol) oconv = 0;
+      else if (!(orel <= kDivergeLimit)) oerr = kErrDiverged;
+    }
+    if (tail) A.x[A.inv ? A.inv[row] : row] = x;
+    if (froze && A.coef_out) {  // later calls start from the frozen precisions
+      if (tail) ((T*)A.inv_pt_out)[row] = ip;
+      const int s0 = own ? A.off_ptr[row] + pos * K : 0;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (k < cnt) ((V2*)A.coef_out)[s0 + k] = V2{mP0[k], mP1[k]};
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+      DevStatus st{};
+      st.done = lost ? 2 : 1;
+      st.conv_round = oconv;
+      st.error = oerr;
+      st.pad = ierr;
+      st.last_rel = orel;
+      st.ticket = (uint32_t)sweeps;
+      st.last_round = outer;
+      st.pad2 = froze ? 1 : 0;
+      *A.st = st;
+    }
+  }
+}
+
+// dynamic LDS of a workgroup
+template <typename T>
+uint32_t res_lds(int rows_cap, int lanes, int K, int mode) {
+  size_t b = 2 * (size_t)rows_cap * (sizeof(vec2<T>) + sizeof(T));
+  if (mode == kResOuter || mode == kResOuterLoop || mode == kResRefine) b += sizeof(double) * (size_t)rows_cap;
+  if (lanes == kRL) b += (size_t)lanes * (K * (sizeof(double) + sizeof(int)) + 2 * sizeof(double));
+  return (uint32_t)b;
+}
+
+}  // namespace
+
+}  // namespace gabp

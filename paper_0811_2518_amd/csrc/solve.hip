@@ -909,40 +909,50 @@ gabp_status solve_plain(Ctx* c, const double* b, double* x, double* var, double 
   return r;
 }
 
-bool use_resident(const Ctx* c) { return c->res.nb > 0 && c->layout == kLayoutCompact && c->gamma_used == 0.0; }
-
-// A plain FP64 solve in one resident launch.  Joint solves of a small system
-// stay with the one-workgroup kernels of small.hip; its mean-only solves on
-// frozen precisions come here.
+// A solve in one resident launch.  Joint FP64 solves of a small system stay
+// with the one-workgroup kernels of small.hip; its mean-only solves on frozen
+// precisions come here.
 gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, double tol, int32_t max_iter,
                            gabp_info* info, bool* ran) {
+  *ran = false;
+  if (c->res.nb <= 0 || c->layout != kLayoutCompact) return GABP_OK;
   hipStream_t s = c->stream;
   const bool exact = tol <= 0.0;
+  const bool fp32 = c->opts.precision == GABP_FP32_REFINE;
+  const bool plain = c->opts.precision == GABP_FP64 && c->gamma_used == 0.0 && c->opts.gamma == 0.0;
+  const bool single = (c->opts.flags & GABP_FLAG_SINGLE_LOOP) != 0;
+  const bool loop = !plain && single && !fp32;  // the FP64 single loop
+  const bool outer = !plain && !loop;
   const bool reuse = (c->opts.flags & GABP_FLAG_REUSE_PRECISION) != 0;
-  const bool honly = reuse && c->frozen_valid && c->frozen_prec == GABP_FP64 && !exact;
-  *ran = false;
-  if (!honly && (small_fits(c->n, c->E) || small_rows_fit(c->n, c->max_degree))) return GABP_OK;
+  const bool honly = plain && reuse && c->frozen_valid && c->frozen_prec == GABP_FP64 && !exact;
+  if (plain && !honly && (small_fits(c->n, c->E) || small_rows_fit(c->n, c->max_degree))) return GABP_OK;
   ResArgs a{};
-  a.off_ptr = c->off_ptr_d;
-  a.col = c->off_col_d;
-  a.a = c->a64_d;
-  a.diag = c->din64_d;
-  a.inv = c->perm_d ? c->inv_d : nullptr;
+  a.diag = fp32 ? (const void*)c->din32_d : (const void*)c->din64_d;
+  a.chk_diag = fp32 ? (const void*)(c->d32_d ? c->d32_d : c->din32_d) : (const void*)c->d64_d;
+  a.damp = c->opts.damping;
   a.rhs = b;
-  a.coef = c->gcoef_d;
-  a.inv_pt = (const double*)c->inv_pt_d;
-  a.agg[0] = c->agg_d[0];
-  a.agg[1] = c->agg_d[1];
   a.tol = tol;
   a.max_iter = max_iter;
-  a.check_every = c->opts.check_every;
-  a.st = c->st_small_d;
   a.x = x;
   a.var = var;
-  if (!honly && (exact || reuse)) {  // read later by gabp_messages or the freeze
+  if (plain && !honly && (exact || reuse)) {  // read later by gabp_messages or the freeze
     a.cin_out = c->bstate_d;
     for (int q = 0; q < 3; ++q) a.agg_out[q] = c->agg_d[q];
   }
+  if (outer) {
+    a.inner_tol = c->opts.inner_tol;
+    a.inner_max = c->opts.inner_max_iter;
+    a.max_outer = c->opts.max_outer;
+    if (!reuse) c->frozen_valid = false;
+    a.frozen = c->frozen_valid && c->frozen_prec == c->opts.precision && !(single && c->gamma_used > 0.0);
+    a.want_freeze = reuse || c->gamma_used > 0.0;  // as solve_outer: where later inner solves use it
+    a.xbuf = c->xo_d[0];
+    if (reuse) {
+      a.coef_out = c->gcoef_d;
+      a.inv_pt_out = c->inv_pt_d;
+    }
+  }
+  if (loop) c->frozen_valid = false;
   *c->st_small_h = DevStatus{};
   reset_timing(c);
   GABP_HIP(c, launch_resident(c, a, honly, s));
@@ -951,18 +961,32 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
   if (!st.done) return GABP_OK;  // the chip was busy
   *ran = true;
   if (st.done != 1) return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
-  gabp_status r = map_status(c, st, exact);
+  gabp_status r;
+  if (outer) {
+    if (st.pad2) {
+      c->frozen_valid = reuse;
+      c->frozen_prec = c->opts.precision;
+    }
+    if (st.pad & kErrNonfinite) return fail(c, GABP_E_NONFINITE, "non-finite inner message");
+    if (st.pad & kErrDiverged)
+      r = fail(c, GABP_E_DIVERGED,
+               "inner GaBP diverged (the inner matrix is not walk-summable: use diagonal loading)");
+    else if (st.error) r = fail(c, GABP_E_DIVERGED, "outer residual diverged");
+    else r = st.conv_round >= 0 ? GABP_OK : GABP_NOT_CONVERGED;
+  } else {
+    r = map_status(c, st, exact);
+  }
   if (info) {
-    info->sweeps = st.conv_round >= 0 ? st.conv_round : max_iter;
-    info->outer_iters = 0;
+    info->sweeps = outer ? (int32_t)st.ticket : st.conv_round >= 0 ? st.conv_round : max_iter;
+    info->outer_iters = outer ? st.last_round : loop ? info->sweeps : 0;
     info->converged = (st.conv_round >= 0) ? 1 : 0;
     info->status = r;
     info->rel_residual = st.last_rel;
-    info->gamma = 0.0;
+    info->gamma = plain ? 0.0 : c->gamma_used;
     report_timing(c, info);
   }
-  c->last_msg_round = (exact && r == GABP_OK) ? max_iter : -1;
-  if (r == GABP_OK && !exact && !honly && reuse) {
+  c->last_msg_round = (plain && exact && r == GABP_OK) ? max_iter : -1;
+  if (plain && r == GABP_OK && !exact && !honly && reuse) {
     r = freeze<double>(c, held_round(c, st.conv_round, max_iter), c->din64_d, b, GABP_FP64);
     if (r != GABP_OK) return r;
     GABP_HIP(c, hipStreamSynchronize(s));
@@ -1257,8 +1281,12 @@ gabp_status autotune(Ctx* c) {
   std::vector<int> layouts, Ks;
   const int req = layout_request(c);
   if (c->res.nb > 0) {  // sweeps run in the resident launch: nothing to time
+    int l = kLayoutCompact, k = epb ? epb / kBlock : 2;
+    const std::string key = tune_key(c) + "-resident";
+    const char* path = std::getenv("GABP_AUTOTUNE_CACHE");
+    if (path && *path && c->E >= 200000 && !cache_lookup(path, key, &l, &k)) cache_store(path, key, l, k, "");
     c->layout = kLayoutCompact;
-    return set_partition(c, epb ? epb / kBlock : 2);
+    return set_partition(c, epb ? epb / kBlock : k);
   }
   if (req) layouts.push_back(req);
   else layouts = {kLayoutEdge, kLayoutNode, kLayoutCompact};

@@ -1,6 +1,6 @@
 """The resident solve of mid-sized systems against the launch-per-sweep path.
 
-Plain FP64 compact solves that fit on the chip run every sweep, check and stop
+Compact solves that fit on the chip run every sweep, check, outer step and stop
 decision in one launch of resident workgroups.  It performs the operations of
 the launch-per-sweep path in the same order, so x, the variances, the messages,
 the gradients and the sweep counts must agree bit for bit; the reported
@@ -146,3 +146,67 @@ def test_shared_chip_and_threads():
     for res in got.values():
         for key, x in res:
             assert torch.equal(x, want[key]), key
+
+
+def dense_checks(p, **kw):
+    """The launch-per-sweep path with the inner solves checked every round, as the resident loop checks them."""
+    return g.Solver(p.row_ptr, p.col, p.val, device=DEV, layout="compact", predict_all=True, **kw)
+
+
+OUTER = {
+    "grid_33x32": CASES["grid_33x32"],        # rows of 4 slots
+    "grid3d_24": lambda: workloads.grid3d_problem(24, 79),  # rows of 6
+    "er_3001": CASES["er_3001"],              # chains of 8
+    "er_130003": lambda: workloads.er_problem(130003, 8, 94),  # 1024 lanes
+    "grid_9x7": lambda: workloads.grid2d_problem(9, 7, 8),  # one workgroup
+}
+
+
+@pytest.mark.parametrize("name", sorted(OUTER))
+@pytest.mark.parametrize("reuse", [False, True])
+def test_fp32_refinement_bitwise(name, reuse):
+    p = OUTER[name]()
+    rng = np.random.default_rng(6)
+    for kw in ({}, {"check_every": 3}, {"inner_max_iter": 3, "max_outer": 5000}):
+        one = g.Solver(p.row_ptr, p.col, p.val, device=DEV, precision="fp32", reuse_precision=reuse, **kw)
+        multi = dense_checks(p, precision="fp32", reuse_precision=reuse, **kw)
+        for bv in (dev(p.b), dev(rng.standard_normal(p.n))):  # with reuse, the second starts frozen
+            x1, i1 = one.solve(bv, tol=1e-10, max_iter=100000)
+            x2, i2 = multi.solve(bv, tol=1e-10, max_iter=100000)
+            assert i1["converged"] == 1 and i1["outer_iters"] == i2["outer_iters"]
+            same_info(i1, i2)
+            assert torch.equal(x1, x2), (name, kw)
+        x1, i1 = one.solve(dev(p.b), tol=1e-300, max_iter=7, check=False)
+        x2, i2 = multi.solve(dev(p.b), tol=1e-300, max_iter=7, check=False)
+        same_info(i1, i2)
+        assert torch.equal(x1, x2)
+
+
+@pytest.mark.parametrize("n", [500, 3000])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_loading_loops_bitwise(n, precision):
+    p = workloads.config5(n=n, rows=2 * n)
+    b = dev(p.b)
+    for kw in ({"inner_tol": 1e-2, "reuse_precision": False}, {"inner_tol": 1e-2},
+               {"inner_tol": 1e-3, "single_loop": True, "damping": 0.5},
+               {"inner_tol": 1e-3, "single_loop": True, "damping": 1.0}):
+        kw = dict(kw, precision=precision, gamma=-1.0, max_outer=5000)
+        one = g.Solver(p.row_ptr, p.col, p.val, device=DEV, **kw)
+        multi = dense_checks(p, **kw)
+        for _ in range(2):
+            x1, i1 = one.solve(b, tol=1e-9, max_iter=200000)
+            x2, i2 = multi.solve(b, tol=1e-9, max_iter=200000)
+            assert i1["converged"] == 1 and i1["outer_iters"] == i2["outer_iters"]
+            same_info(i1, i2)
+            assert torch.equal(x1, x2), kw
+
+
+def test_loading_errors_are_reported_alike():
+    p = workloads.config5(n=3000, rows=6000)  # diverges without loading
+    one = g.Solver(p.row_ptr, p.col, p.val, device=DEV, precision="fp32")
+    multi = dense_checks(p, precision="fp32")
+    s1 = one.solve(dev(p.b), tol=1e-9, max_iter=5000, check=False)[1]
+    s2 = multi.solve(dev(p.b), tol=1e-9, max_iter=5000, check=False)[1]
+    assert s1["status"] == s2["status"] < 0
+    x, info = one.solve(torch.zeros(p.n, dtype=torch.float64, device=DEV), tol=1e-9, max_iter=50)
+    assert info["converged"] == 1 and float(x.abs().max()) == 0.0
