@@ -403,17 +403,17 @@ gabp_status gabp_create_batched(int32_t num_sys, const int32_t *sys_row_off,
  *   tol      per-RHS relative residual target (FP64 refinement)
  *   max_iter cap on the inner sweeps of each work item (all its outer steps)
  *   infos    HOST gabp_info [num_sys] (output, nullable)
- * One HIP graph runs two persistent kernels; it is captured when the call's
- * B, X, tol, max_iter, nrhs and rhs_off differ from the last call's and
- * replayed when they repeat.  The
- * first computes each system's precision messages once (FP32 P-only sweeps of
+ * Two persistent kernels run on the handle's stream; the work list is planned
+ * when nrhs differs from the last call's and kept while it repeats.  The first
+ * computes each system's precision messages once (FP32 P-only sweeps of
  * Alg. 2 until P~ settles, at most opts.inner_max_iter sweeps) and freezes the
  * h-update coefficients.  The second takes work items of 1, 2, 4 or 8
  * right-hand sides of one system, all reading that system's frozen
  * coefficients, and runs the FP64 refinement loop on each (FP64 residual,
  * FP32 h-only inner sweeps until the largest change of the correction is at
  * most opts.inner_tol times its largest magnitude, at most opts.max_outer
- * outer steps).  Returns the worst status over systems.  A tighter inner_tol
+ * outer steps).  An item that would outlast an even share of the batch is run
+ * by a team of up to 64 workgroups.  Returns the worst status over systems.  A tighter inner_tol
  * than gabp_default_opts' 1e-5 saves outer steps here: on the 4096-system
  * benchmark batch 2e-6 is the fastest of 1e-4 ... 1e-6.
  */
@@ -428,7 +428,8 @@ typedef struct {
   int32_t workgroups;       /* persistent workgroups of the right-hand sides     */
   double  makespan_ms;      /* first precision item start to last item end       */
                             /* (device clock)                                     */
-  double  busy_ms;          /* sum of the item durations, both phases            */
+  double  busy_ms;          /* sum of the item durations, both phases, each      */
+                            /* times the workgroups that ran the item            */
   double  longest_item_ms;  /* duration of the longest right-hand-side item      */
   int64_t precision_sweeps; /* precision-phase sweeps summed over systems        */
   int64_t inner_sweeps;     /* right-hand-side sweeps summed over items          */

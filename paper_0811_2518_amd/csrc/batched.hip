@@ -1,5 +1,5 @@
 // Batched solves: many independent systems, several right-hand sides each, in
-// one HIP graph of two persistent kernels.
+// two persistent kernels.
 //
 //  1. k_bprec -- the precision phase, once per system: synchronous P-only
 //     sweeps of Alg. 2 (the precision update has no b term, so the precisions
@@ -11,11 +11,24 @@
 //     h-only FP32 sweeps with the system's frozen coefficients on all
 //     right-hand sides of the group at once; x += d; until every right-hand
 //     side of the group reaches the relative residual tolerance.
-// Work items are handed out costliest first through atomic queues; one
-// 512-lane workgroup runs an item from start to finish, so every barrier is a
-// workgroup barrier and no workgroup waits for another.  The second kernel
-// starts when the first has finished (graph order), so the frozen
-// coefficients are complete and visible.
+// Work items are handed out costliest first through atomic queues.  A 512-lane
+// workgroup runs a small item from start to finish.  A sweep of one workgroup
+// is bound by latency (each of its 8 waves walks its slices one after the
+// other), so an item that would outlast an even share of the batch is run by a
+// team of 2, 4, ... 64 workgroups that split its slices: the persistent
+// workgroups go through phases of falling team size, each with its own queue,
+// and a team that finds its queue empty splits into the teams of the next
+// phase.  Members exchange aggregates, means and reductions with agent-scope
+// accesses and wait for each other at team barriers, which end because every
+// workgroup of the launch is resident: a roll call with a time limit finds
+// out, and if it fails (the chip is busy with other work) every item is run by
+// a single workgroup.  The second kernel starts when the first has finished
+// (stream order), so the frozen coefficients are complete and visible.
+// Measured against a workgroup per item (synchronous / colour-serial): 192
+// uneven systems of 64 to 16384 rows with 1 to 16 right-hand sides each 25.4 ->
+// 8.0 / 16.9 -> 9.7 ms (the longest item took 22.8 of the 25.4), 20 such
+// systems 5.0 -> 1.1 ms, 1500 of up to 65536 rows 413 -> 313 / 306 -> 246 ms
+// (precision phase 21.3 -> 5.4 ms).
 //
 // Layout.  At create, each system's rows are renumbered: inside each segment
 // (the whole system; with the colour-serial schedule, each colour class) the
@@ -92,8 +105,37 @@ struct BItem {
 struct ItemInfo {
   int32_t sweeps, outer, converged, status;
   double rel;
-  int32_t psweeps, pad;
+  int32_t psweeps, pad;  // pad: workgroups that ran the item
   uint64_t t0, t1;  // device wall clock at the item's start and end
+};
+
+// Workgroups that run an item together.
+constexpr int kMaxTeam = 64;
+constexpr int kPhases = 7;               // team sizes 64, 32, ... 1
+constexpr int kTeamVals = 2 * kMaxGroup; // values of a team reduction
+constexpr uint64_t kRollMs = 1;          // roll call: longest wait for a workgroup to start
+struct TeamCtl {
+  uint64_t cnt;   // barrier arrivals
+  int32_t item;   // item of the round (-1: the queue is empty)
+  int32_t pad[29];
+};
+// Device control block, zero when a solve starts: [0] precision phase, [1]
+// right-hand sides.
+struct BatchCtl {
+  uint32_t queue[2][8];
+  uint64_t rolled[2];  // roll call arrivals
+  uint32_t state[2];   // 0, kRollGo or kRollAbort
+  uint32_t pad[10];
+};
+constexpr uint32_t kRollGo = 1, kRollAbort = 2;
+// Phases of one kernel: team size, items first .. first + count - 1, and where
+// the teams' control blocks and reduction slots start.
+struct PhaseRec {
+  int32_t team, first, count, ctl;
+};
+struct PhaseList {
+  PhaseRec ph[kPhases];
+  int32_t n, teams;  // phases; whether any has a team
 };
 
 struct BatchArgs {
@@ -122,7 +164,11 @@ struct BatchArgs {
   float* hbuf;
   float* nkbuf;
   double* xbuf;
-  uint32_t* queue;        // [2]: precision, right-hand sides
+  BatchCtl* ctl;
+  TeamCtl* tctl[2];       // precision, right-hand sides: the teams of every phase
+  double* tred;           // [phases][2][workgroups][kTeamVals] reduction slots
+  PhaseList pph, rph;
+  uint64_t roll_limit;    // ticks of the wall clock
   const double* B;
   double* X;
   double tol;
@@ -183,6 +229,48 @@ __device__ View sys_view(const BatchArgs& A, int s) {
   return V;
 }
 
+// A team's view of one workgroup.
+struct Team {
+  int T, m;          // members, and which of them this workgroup is
+  TeamCtl* ctl;
+  double* red;       // [2][T][kTeamVals] by reduction parity
+  size_t stride;     // doubles between the two parities
+  uint32_t ep, rc;   // barriers and reductions so far
+};
+
+// Data that members of a team exchange: agent scope (past the L1, written
+// through); plain accesses inside one workgroup.
+template <bool TEAM, typename V>
+__device__ __forceinline__ V tld(const V* p) {
+  if constexpr (TEAM) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return *p;
+}
+template <bool TEAM, typename V>
+__device__ __forceinline__ void tst(V* p, V v) {
+  if constexpr (TEAM) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+
+// All members: what they stored before is visible after.
+template <bool TEAM>
+__device__ __forceinline__ void team_barrier(Team& tm) {
+  if constexpr (TEAM) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have reached memory
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      ++tm.ep;
+      __hip_atomic_fetch_add(&tm.ctl->cnt, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t want = (uint64_t)tm.ep * tm.T;
+      while (__hip_atomic_load(&tm.ctl->cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want) {
+      }
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");
+  } else {
+    __syncthreads();
+  }
+}
+
 // Per-lane results of a pass.
 struct Red {
   float dmax, xmax;  // h pass: change of d and size of d; P pass: relative change of P~
@@ -195,12 +283,13 @@ struct Red {
 // that a neighbour at or beyond it belongs to a later class).  Each wave walks
 // its own units (slice, part of the right-hand sides); the caller
 // synchronises the workgroup after the pass.
-template <int KIND, bool SER>
-__device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi, int rhi, Red& rd) {
+template <int KIND, bool SER, bool TEAM>
+__device__ void pass(const BatchArgs& A, const View& V, const Team& tm, int t, int slo, int shi, int rhi, Red& rd) {
   constexpr bool MULTI = KIND == kKH || KIND == kKSpmv;
   constexpr int kQ = KIND == kKSpmv ? 4 : kQSlots;  // FP64 slots hold twice the registers
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = uni((int32_t)(threadIdx.x / kWave));
+  const int wave = uni((int32_t)(threadIdx.x / kWave)) + (TEAM ? tm.m * kWaves : 0);
+  const int waves = TEAM ? tm.T * kWaves : kWaves;
   const int lgk = MULTI ? V.lgk : 0;
   const int kgE = 1 << lgk;
   const int R = kWave >> lgk;  // rows per unit
@@ -222,7 +311,7 @@ __device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi,
   float* Ht_ = SER ? V.H0 : V.H(t);
   const float* hg_ = SER ? V.hagg0 : V.hagg(t + 2);
   float* hn_ = SER ? V.hagg0 : V.hagg(t);
-  for (int u = wave; u < units; u += kWaves) {
+  for (int u = wave; u < units; u += waves) {
     const Slice sl = A.slices[slo + (u >> lgk)];
     const int64_t base = uni(sl.base) - V.ss0;
     const int row0 = uni(sl.row0), nrows = uni(sl.nrows), L = uni(sl.L);
@@ -240,29 +329,29 @@ __device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi,
     if (valid) {
       if (KIND == kKP) {
         if (SER) {
-          o1 = first ? d32p[i] : V.Pagg0[i];
+          o1 = first ? d32p[i] : tld<TEAM>(V.Pagg0 + i);
         } else {
-          o1 = first ? d32p[i] : V.Pagg(t + 2)[i];                         // round t-1
-          o2 = second ? d32p[i] : (first ? 0.f : V.Pagg(t + 1)[i]);         // round t-2
+          o1 = first ? d32p[i] : tld<TEAM>(V.Pagg(t + 2) + i);               // round t-1
+          o2 = second ? d32p[i] : (first ? 0.f : tld<TEAM>(V.Pagg(t + 1) + i));  // round t-2
         }
       } else if (KIND == kKFreeze) {
         if (SER) {
-          o1 = V.Pagg0[i];
+          o1 = tld<TEAM>(V.Pagg0 + i);
         } else {
-          o1 = V.Pagg(t)[i];                                                // round T
-          o2 = t >= 2 ? V.Pagg(t + 2)[i] : d32p[i];                         // round T-1
+          o1 = tld<TEAM>(V.Pagg(t) + i);                                      // round T
+          o2 = t >= 2 ? tld<TEAM>(V.Pagg(t + 2) + i) : d32p[i];               // round T-1
         }
       } else if (KIND == kKH) {
-        er = V.r32[qi];
+        er = tld<TEAM>(V.r32 + qi);
         ip = V.invPt[i];
         if (SER) {
-          o1 = first ? 0.f : V.hagg0[qi];
+          o1 = first ? 0.f : tld<TEAM>(V.hagg0 + qi);
         } else {
-          o1 = first ? er : V.hagg(t + 2)[qi];
-          o2 = second ? er : (first ? 0.f : V.hagg(t + 1)[qi]);
+          o1 = first ? er : tld<TEAM>(V.hagg(t + 2) + qi);
+          o2 = second ? er : (first ? 0.f : tld<TEAM>(V.hagg(t + 1) + qi));
         }
       } else {
-        xo = V.xint[qi];
+        xo = tld<TEAM>(V.xint + qi);
         bo = V.B[(int64_t)(A.umap[V.r0 + i] - V.r0) * V.k + V.j0 + jj];
       }
     }
@@ -311,9 +400,9 @@ __device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi,
         if (q < deg) {
           const int cn = c[u8];
           const bool silent = SER && first && cn >= rhi;  // a later class has sent nothing yet
-          if (KIND == kKP || KIND == kKFreeze) vg[u8] = silent ? 0.f : ((first && !SER && KIND == kKP) ? d32p[cn] : Pg_[cn]);
-          else if (KIND == kKH) vg[u8] = silent ? 0.f : ((first && !SER) ? V.r32 : hg_)[cn * kg + jj];
-          else vxd[u8] = V.xint[cn * kg + jj];
+          if (KIND == kKP || KIND == kKFreeze) vg[u8] = silent ? 0.f : ((first && !SER && KIND == kKP) ? d32p[cn] : tld<TEAM>(Pg_ + cn));
+          else if (KIND == kKH) vg[u8] = silent ? 0.f : tld<TEAM>(((first && !SER) ? V.r32 : hg_) + (cn * kg + jj));
+          else vxd[u8] = tld<TEAM>(V.xint + (cn * kg + jj));
         }
       }
       // the slot arithmetic, in the row's slot order
@@ -371,7 +460,7 @@ __device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi,
     // row epilogue
     if (KIND == kKP) {
       const float Pt = d32p[i] + accf;
-      Pn_[i] = Pt;
+      tst<TEAM>(Pn_ + i, Pt);
       rd.dmax = fmaxf(rd.dmax, fabsf(Pt - o1) / fabsf(Pt));
       if (SER)  // the new outgoing messages out_{j->i} = F(P~_j, in_{i->j})
         for (int q = 0; q < deg; ++q) {
@@ -385,7 +474,7 @@ __device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi,
       if (!isfinite(ipt)) rd.bad = 1;
     } else if (KIND == kKH) {
       const float ht = er + accf;
-      hn_[qi] = ht;
+      tst<TEAM>(hn_ + qi, ht);
       const float dn = ht * ip;
       const float dold = first ? 0.f : o1 * ip;
       rd.dmax = fmaxf(rd.dmax, fabsf(dn - dold));
@@ -398,7 +487,7 @@ __device__ void pass(const BatchArgs& A, const View& V, int t, int slo, int shi,
         }
     } else {
       const double r = bo - d64p[i] * xo - accd;
-      V.r32[qi] = (float)r;
+      tst<TEAM>(V.r32 + qi, (float)r);
       rd.r2 += r * r;
     }
   }
@@ -417,10 +506,10 @@ struct Shared {
   double bn[kMaxGroup];
   unsigned fmx[2 * kMaxGroup];
   int item;
-  int bad;
 };
 
-__device__ void reduce_max2(Shared& sh, float a, float b, int kg) {
+template <bool TEAM>
+__device__ void reduce_max2(Shared& sh, Team& tm, float a, float b, int kg) {
   unsigned ka = fkey(a), kb = fkey(b);
   for (int off = kWave / 2; off >= kg; off >>= 1) {
     ka = max(ka, (unsigned)__shfl_xor((int)ka, off, kWave));
@@ -438,13 +527,38 @@ __device__ void reduce_max2(Shared& sh, float a, float b, int kg) {
       ra = max(ra, sh.mx[v][threadIdx.x]);
       rb = max(rb, sh.mx[v][kMaxGroup + threadIdx.x]);
     }
-    sh.fmx[threadIdx.x] = ra;
-    sh.fmx[kMaxGroup + threadIdx.x] = rb;
+    if constexpr (TEAM) {
+      uint64_t* red = (uint64_t*)(tm.red + (tm.rc & 1) * tm.stride) + (size_t)tm.m * kTeamVals;
+      tst<true>(red + threadIdx.x, (uint64_t)ra);
+      tst<true>(red + kMaxGroup + threadIdx.x, (uint64_t)rb);
+    } else {
+      sh.fmx[threadIdx.x] = ra;
+      sh.fmx[kMaxGroup + threadIdx.x] = rb;
+    }
+  }
+  if constexpr (TEAM) {
+    team_barrier<true>(tm);
+    const uint64_t* red = (const uint64_t*)(tm.red + (tm.rc & 1) * tm.stride);
+    ++tm.rc;
+    const int v = threadIdx.x % kTeamVals;
+    unsigned k = 0u;
+    if ((v & (kMaxGroup - 1)) < kg)
+      for (int mm = threadIdx.x / kTeamVals; mm < tm.T; mm += kBT / kTeamVals)
+        k = max(k, (unsigned)tld<true>(red + (size_t)mm * kTeamVals + v));
+    for (int off = kTeamVals; off < kWave; off <<= 1) k = max(k, (unsigned)__shfl_xor((int)k, off, kWave));
+    if (lane < kTeamVals) sh.mx[w][lane] = k;
+    __syncthreads();
+    if (threadIdx.x < kTeamVals) {
+      unsigned r = 0u;
+      for (int q = 0; q < kWaves; ++q) r = max(r, sh.mx[q][threadIdx.x]);
+      sh.fmx[threadIdx.x] = r;
+    }
   }
   __syncthreads();
 }
 
-__device__ void reduce_sum(Shared& sh, double v, int kg) {
+template <bool TEAM>
+__device__ void reduce_sum(Shared& sh, Team& tm, double v, int kg) {
   for (int off = kWave / 2; off >= kg; off >>= 1) v += __shfl_xor(v, off, kWave);
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   if (lane < kg) sh.sm[w][lane] = v;
@@ -452,7 +566,24 @@ __device__ void reduce_sum(Shared& sh, double v, int kg) {
   if ((int)threadIdx.x < kg) {
     double acc = 0.0;
     for (int q = 0; q < kWaves; ++q) acc += sh.sm[q][threadIdx.x];
-    sh.tot[threadIdx.x] = acc;
+    if constexpr (TEAM) tst<true>(tm.red + (tm.rc & 1) * tm.stride + (size_t)tm.m * kTeamVals + threadIdx.x, acc);
+    else sh.tot[threadIdx.x] = acc;
+  }
+  if constexpr (TEAM) {
+    team_barrier<true>(tm);
+    const double* red = tm.red + (tm.rc & 1) * tm.stride;
+    ++tm.rc;
+    static_assert(kBT / kMaxGroup >= kMaxTeam, "one load per lane");
+    const int j = threadIdx.x % kMaxGroup, mm = threadIdx.x / kMaxGroup;
+    double acc = j < kg && mm < tm.T ? tld<true>(red + (size_t)mm * kTeamVals + j) : 0.0;
+    for (int off = kMaxGroup; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+    if (lane < kMaxGroup) sh.sm[w][lane] = acc;
+    __syncthreads();
+    if (threadIdx.x < kMaxGroup) {
+      double tot = 0.0;
+      for (int q = 0; q < kWaves; ++q) tot += sh.sm[q][threadIdx.x];
+      sh.tot[threadIdx.x] = tot;
+    }
   }
   __syncthreads();
 }
@@ -466,8 +597,8 @@ __device__ __forceinline__ void class_range(const BatchArgs& A, int cls0, int q,
 }
 
 // ---- phase 1: the precision phase of one system -----------------------------
-template <bool SER>
-__device__ void precision_item(const BatchArgs& A, int s, Shared& sh) {
+template <bool SER, bool TEAM>
+__device__ void precision_item(const BatchArgs& A, int s, Shared& sh, Team& tm) {
   const View V = sys_view(A, s);
   const SysRec R = A.sys[s];
   const int cls0 = uni(R.cls0), ncls = uni(R.ncls);
@@ -485,13 +616,13 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh) {
       for (int q = 0; q < ncls; ++q) {
         int slo, shi, rhi;
         class_range(A, cls0, q, V, slo, shi, rhi);
-        pass<kKP, true>(A, V, tp, slo, shi, rhi, rd);
-        __syncthreads();
+        pass<kKP, true, TEAM>(A, V, tm, tp, slo, shi, rhi, rd);
+        team_barrier<TEAM>(tm);
       }
     } else {
-      pass<kKP, false>(A, V, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
+      pass<kKP, false, TEAM>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
     }
-    reduce_max2(sh, rd.dmax, 0.f, 1);  // also orders this round's aggregates before the next pass
+    reduce_max2<TEAM>(sh, tm, rd.dmax, 0.f, 1);  // also orders this round's aggregates before the next pass
     const float ch = __uint_as_float(sh.fmx[0]);
     if (ch < 0.5f * best) {
       best = ch;
@@ -503,15 +634,13 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh) {
   }
   // freeze the h-update coefficients from the precisions of round tp
   Red rd{0.f, 0.f, 0.0, 0};
-  pass<kKFreeze, SER>(A, V, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
-  if (threadIdx.x == 0) sh.bad = 0;
-  __syncthreads();
-  if (rd.bad) sh.bad = 1;
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  pass<kKFreeze, SER, TEAM>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
+  reduce_max2<TEAM>(sh, tm, rd.bad ? 1.f : 0.f, 0.f, 1);
+  if (threadIdx.x == 0 && tm.m == 0) {
     ItemInfo inf{};
     inf.psweeps = tp;
-    inf.status = sh.bad ? GABP_E_NONFINITE : GABP_OK;
+    inf.pad = tm.T;
+    inf.status = sh.fmx[0] != 0u ? GABP_E_NONFINITE : GABP_OK;
     inf.t0 = t_start;
     inf.t1 = wall_clock64();
     A.pinfos[s] = inf;
@@ -520,8 +649,8 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh) {
 }
 
 // ---- phase 2: FP64 refinement of one item ----------------------------------
-template <bool SER>
-__device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh) {
+template <bool SER, bool TEAM>
+__device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh, Team& tm) {
   const int tid = threadIdx.x;
   View V = sys_view(A, I.sys);
   const SysRec R = A.sys[I.sys];
@@ -543,15 +672,16 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh)
   const int pstatus = A.pinfos[I.sys].status;
 
   // x = 0, the correction's right-hand side r = b, and ||b|| per right-hand side
+  const int q0 = tid + (TEAM ? tm.m * kBT : 0), qs = TEAM ? tm.T * kBT : kBT;
   double bpart = 0.0;
-  for (int64_t q = tid; q < nk; q += kBT) {
+  for (int64_t q = q0; q < nk; q += qs) {
     const int i = (int)(q >> V.lgk);
     const double bv = V.B[(int64_t)(A.umap[V.r0 + i] - V.r0) * V.k + V.j0 + jj];
-    V.xint[q] = 0.0;
-    V.r32[q] = (float)bv;
+    tst<TEAM>(V.xint + q, 0.0);
+    tst<TEAM>(V.r32 + q, (float)bv);
     bpart += bv * bv;
   }
-  reduce_sum(sh, bpart, kg);
+  reduce_sum<TEAM>(sh, tm, bpart, kg);
   if (tid < kg) sh.bn[tid] = sqrt(sh.tot[tid]);
   __syncthreads();
 
@@ -566,13 +696,13 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh)
         for (int q = 0; q < ncls; ++q) {
           int slo, shi, rhi;
           class_range(A, cls0, q, V, slo, shi, rhi);
-          pass<kKH, true>(A, V, t, slo, shi, rhi, rd);
-          __syncthreads();
+          pass<kKH, true, TEAM>(A, V, tm, t, slo, shi, rhi, rd);
+          team_barrier<TEAM>(tm);
         }
       } else {
-        pass<kKH, false>(A, V, t, V.sl0, V.sl0 + V.nsl, V.n, rd);
+        pass<kKH, false, TEAM>(A, V, tm, t, V.sl0, V.sl0 + V.nsl, V.n, rd);
       }
-      reduce_max2(sh, rd.dmax, rd.xmax, kg);
+      reduce_max2<TEAM>(sh, tm, rd.dmax, rd.xmax, kg);
       bool done = t >= 2;
       for (int j = 0; j < kg; ++j) {
         const float dm = __uint_as_float(sh.fmx[j]), xm = __uint_as_float(sh.fmx[kMaxGroup + j]);
@@ -585,12 +715,13 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh)
     // x += d (FP64) with d = h~ / P~ of the last inner round, then r = b - A x
     {
       const float* hT = SER ? V.hagg0 : V.hagg(t);
-      for (int64_t q = tid; q < nk; q += kBT) V.xint[q] += (double)(hT[q] * V.invPt[q >> V.lgk]);
-      __syncthreads();
+      for (int64_t q = q0; q < nk; q += qs)
+        tst<TEAM>(V.xint + q, tld<TEAM>(V.xint + q) + (double)(tld<TEAM>(hT + q) * V.invPt[q >> V.lgk]));
+      team_barrier<TEAM>(tm);
     }
     Red rd{0.f, 0.f, 0.0, 0};
-    pass<kKSpmv, false>(A, V, 0, V.sl0, V.sl0 + V.nsl, V.n, rd);
-    reduce_sum(sh, rd.r2, kg);
+    pass<kKSpmv, false, TEAM>(A, V, tm, 0, V.sl0, V.sl0 + V.nsl, V.n, rd);
+    reduce_sum<TEAM>(sh, tm, rd.r2, kg);
     ++outer;
     relmax = 0.0;
     for (int j = 0; j < kg; ++j) {
@@ -609,11 +740,11 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh)
     if (outer >= A.max_outer || total >= A.max_iter) break;
   }
   // X in the caller's row order
-  for (int64_t q = tid; q < nk; q += kBT) {
+  for (int64_t q = q0; q < nk; q += qs) {
     const int i = (int)(q >> V.lgk);
-    V.X[(int64_t)(A.umap[V.r0 + i] - V.r0) * V.k + V.j0 + jj] = V.xint[q];
+    V.X[(int64_t)(A.umap[V.r0 + i] - V.r0) * V.k + V.j0 + jj] = tld<TEAM>(V.xint + q);
   }
-  if (tid == 0) {
+  if (tid == 0 && tm.m == 0) {
     ItemInfo inf{};
     inf.sweeps = total;
     inf.outer = outer;
@@ -621,6 +752,7 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh)
     inf.status = status != GABP_OK ? status : (converged ? GABP_OK : GABP_NOT_CONVERGED);
     inf.rel = relmax;
     inf.psweeps = A.pinfos[I.sys].psweeps;
+    inf.pad = tm.T;
     inf.t0 = t_start;
     inf.t1 = wall_clock64();
     A.infos[it] = inf;
@@ -641,7 +773,81 @@ __device__ __forceinline__ BItem uniform_item(const BItem& x) {
   return u;
 }
 
-// Persistent kernels: every workgroup takes items until its queue is empty.
+// Roll call of a kernel with teams (one lane per workgroup): true once every
+// workgroup of the launch is running, false after the time limit.
+__device__ __forceinline__ bool roll_call_b(BatchCtl* c, int k, uint64_t limit) {
+  uint32_t want = 0;
+  if (__hip_atomic_fetch_add(&c->rolled[k], (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x)
+    __hip_atomic_compare_exchange_strong(&c->state[k], &want, kRollGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t t0 = wall_clock64();
+  for (;;) {
+    const uint32_t s = __hip_atomic_load(&c->state[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (s) return s == kRollGo;
+    if (wall_clock64() - t0 > limit) {
+      want = 0;
+      __hip_atomic_compare_exchange_strong(&c->state[k], &want, kRollAbort, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// The persistent loop of kernel k (0: precision, 1: right-hand sides): the
+// phases in turn, items of a phase until its queue is empty.  one(q) and
+// many(q, team) run item q alone and as a member of a team.
+template <typename One, typename Many>
+__device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& P, int k, Shared& sh, One one,
+                                           Many many) {
+  bool teams = false;
+  if (P.teams) {
+    if (threadIdx.x == 0) sh.item = roll_call_b(A.ctl, k, A.roll_limit) ? 1 : 0;
+    __syncthreads();
+    teams = __builtin_amdgcn_readfirstlane(sh.item) != 0;
+    __syncthreads();
+  }
+  // ranks: consecutive ranks (a team) share an XCD of a round-robin dispatch
+  const int G = gridDim.x;
+  const int rank = G % 8 == 0 ? ((int)blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x;
+  for (int p = 0; p < P.n; ++p) {
+    const PhaseRec ph = P.ph[p];
+    uint32_t* queue = &A.ctl->queue[k][p];
+    if (ph.team > 1 && teams) {
+      const int tid_ = rank / ph.team;
+      if ((tid_ + 1) * ph.team > G) continue;  // not a full team
+      Team tm;
+      tm.T = ph.team;
+      tm.m = rank % ph.team;
+      tm.ctl = A.tctl[k] + ph.ctl + tid_;
+      tm.stride = (size_t)G * kTeamVals;
+      tm.red = A.tred + (size_t)p * 2 * tm.stride + (size_t)tid_ * ph.team * kTeamVals;
+      tm.ep = tm.rc = 0;
+      for (;;) {
+        if (tm.m == 0 && threadIdx.x == 0) {
+          const int q = (int)atomicAdd(queue, 1u);
+          tst<true>(&tm.ctl->item, q < ph.count ? ph.first + q : -1);
+        }
+        team_barrier<true>(tm);
+        if (threadIdx.x == 0) sh.item = tld<true>(&tm.ctl->item);
+        __syncthreads();
+        const int q = __builtin_amdgcn_readfirstlane(sh.item);
+        __syncthreads();
+        if (q < 0) break;
+        many(q, tm);
+      }
+    } else {
+      for (;;) {
+        if (threadIdx.x == 0) sh.item = (int)atomicAdd(queue, 1u);
+        __syncthreads();
+        const int q = __builtin_amdgcn_readfirstlane(sh.item);
+        __syncthreads();
+        if (q >= ph.count) break;
+        one(ph.first + q);
+      }
+    }
+  }
+}
+
+// Persistent kernels: every workgroup takes items until the queues are empty.
 // At most 64 VGPRs, so that four 512-lane workgroups reside per CU: measured
 // on the 4096-system batch, 97 VGPRs (two workgroups per CU) took 1.27 s
 // (colour-serial 0.82 s), 80 (three) 1.04 s (0.73 s) and 64 (four) 1.05 s
@@ -651,31 +857,30 @@ __device__ __forceinline__ BItem uniform_item(const BItem& x) {
 template <bool SER>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(8))) void k_bprec(BatchArgs A) {
   __shared__ Shared sh;
-  for (;;) {
-    if (threadIdx.x == 0) sh.item = (int)atomicAdd(&A.queue[0], 1u);
-    __syncthreads();
-    const int q = __builtin_amdgcn_readfirstlane(sh.item);
-    __syncthreads();
-    if (q >= A.num_sys) return;
-    precision_item<SER>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh);
-  }
+  run_phases(
+      A, A.pph, 0, sh,
+      [&](int q) {
+        Team tm{1, 0, nullptr, nullptr, 0, 0, 0};
+        precision_item<SER, false>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
+      },
+      [&](int q, Team& tm) { precision_item<SER, true>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm); });
 }
 
 template <bool SER>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(8))) void k_brhs(BatchArgs A) {
   __shared__ Shared sh;
-  for (;;) {
-    if (threadIdx.x == 0) sh.item = (int)atomicAdd(&A.queue[1], 1u);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(sh.item);
-    __syncthreads();
-    if (it >= A.num_items) return;
-    rhs_item<SER>(A, uniform_item(A.items[it]), it, sh);
-  }
+  run_phases(
+      A, A.rph, 1, sh,
+      [&](int q) {
+        Team tm{1, 0, nullptr, nullptr, 0, 0, 0};
+        rhs_item<SER, false>(A, uniform_item(A.items[q]), q, sh, tm);
+      },
+      [&](int q, Team& tm) { rhs_item<SER, true>(A, uniform_item(A.items[q]), q, sh, tm); });
 }
 
-__global__ void k_reset_queues(uint32_t* q) {
-  if (threadIdx.x < 2) q[threadIdx.x] = 0u;
+__global__ void k_reset_ctl(uint64_t* p, int64_t words) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x)
+    p[i] = 0ull;
 }
 
 // The SELL arrays of every slice: one thread per (slice, lane).  new2cur maps
@@ -819,7 +1024,13 @@ struct BatchState {
   BItem* items_d = nullptr;
   ItemInfo* infos_d = nullptr;
   size_t items_cap = 0;
-  uint32_t* queue_d = nullptr;
+  // control blocks of both kernels (zeroed before every solve) and the teams'
+  // reduction slots
+  BatchCtl* ctl_d = nullptr;
+  TeamCtl* tctl_d[2] = {nullptr, nullptr};
+  int64_t ctl_words = 0;
+  double* tred_d = nullptr;
+  PhaseList pph{}, rph{};
   float* hbuf = nullptr;
   float* nkbuf = nullptr;
   double* xbuf = nullptr;
@@ -827,19 +1038,40 @@ struct BatchState {
   int grid_p = 0, grid_r = 0;
   int launched_grid = 0;
   bool serial = false;
-  hipStream_t gs = nullptr;
   double clock_khz = 0.0;
   gabp_batch_profile prof{};
-  // cached graph of the last solve
-  hipGraphExec_t exec = nullptr;
-  hipGraph_t graph = nullptr;
-  std::vector<int32_t> key_nrhs;
-  std::vector<int64_t> key_off;
-  const double* key_B = nullptr;
-  double* key_X = nullptr;
-  double key_tol = -1.0;
-  int32_t key_iter = -1;
+  std::vector<int32_t> key_nrhs;  // of the work list (empty: none yet)
 };
+
+// Members of the team that runs an item of the given cost, where an even share
+// of the work per workgroup is `share`: enough to bring it to half a share, at
+// most one wave per 64-lane unit of its passes.  Half a share: the items
+// behind the first then even out what the estimates miss (a quarter, half, one
+// share: 192 systems of up to 16384 rows 9.0, 8.0, 8.3 ms; 600 of up to 32768
+// rows 40, 43, 46 ms).  One unit per wave: with at least two or four, the 192
+// systems take 7.7 and 10.0 ms, 20 of them 1.1, 1.5 and 2.1 ms.
+int team_for(double cost, double share, int64_t units) {
+  int T = 1;
+  while (T < kMaxTeam && T * kWaves < units && cost / T > 0.5 * share) T *= 2;
+  return T;
+}
+
+// Phases of falling team size over items whose teams are `team` (sorted).
+PhaseList make_phases(const std::vector<int>& team, int grid) {
+  PhaseList L{};
+  int32_t ctl = 0;
+  for (size_t i = 0; i < team.size();) {
+    size_t j = i;
+    while (j < team.size() && team[j] == team[i]) ++j;
+    L.ph[L.n++] = PhaseRec{team[i], (int32_t)i, (int32_t)(j - i), ctl};
+    if (team[i] > 1) {
+      ctl += grid / team[i];
+      L.teams = 1;
+    }
+    i = j;
+  }
+  return L;
+}
 
 void free_raw(void* p) {
   if (p) (void)hipFree(p);
@@ -901,8 +1133,6 @@ gabp_status batched_create(Ctx* c, int32_t num_sys, const int32_t* sys_row_off) 
     }
     if (!ok) return fail(c, GABP_E_ARG, "internal: invalid colour class lists");
   }
-  GABP_HIP(c, hipMalloc((void**)&bs->queue_d, 2 * sizeof(uint32_t)));
-
   // ---- the new row order and the slices, on the host ----------------------
   const std::vector<int32_t>& op = c->off_ptr_h;
   std::vector<int32_t> new2cur(std::max(N, 1)), cur2new(std::max(N, 1));
@@ -1038,9 +1268,6 @@ gabp_status batched_create(Ctx* c, int32_t num_sys, const int32_t* sys_row_off) 
   int khz = 0;
   GABP_HIP(c, hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
   bs->clock_khz = khz;
-  // the graph is captured and replayed on a stream of the handle's own, ordered
-  // after the caller's stream by synchronisation (capture needs a non-null stream)
-  GABP_HIP(c, hipStreamCreateWithFlags(&bs->gs, hipStreamNonBlocking));
   // per-system spectral radius of R for the work estimate
   bs->sys_weight.assign(num_sys, 1.0);
   if (c->E > 0) {
@@ -1069,15 +1296,37 @@ gabp_status batched_create(Ctx* c, int32_t num_sys, const int32_t* sys_row_off) 
     if (e != hipSuccess) return hip_fail(c, e, "batched work estimate");
     for (int s = 0; s < num_sys; ++s) bs->sys_weight[s] = sweep_weight(rho[s]);
   }
-  // the precision phase's order: largest systems first
+  // the precision phase's order: largest teams, then largest systems first
   {
+    auto cost = [&](int32_t s) { return (double)(bs->sys_h[s].S + bs->sys_h[s].n); };
+    double total = 0.0;
+    for (int s = 0; s < num_sys; ++s) total += cost(s);
+    std::vector<int> team(num_sys);
+    for (int s = 0; s < num_sys; ++s)
+      team[s] = team_for(cost(s), total / bs->grid_p, bs->sys_h[s].nsl / std::max(1, bs->sys_h[s].ncls));
     std::vector<int32_t> order(num_sys);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-      return (double)(bs->sys_h[a].S + bs->sys_h[a].n) > (double)(bs->sys_h[b].S + bs->sys_h[b].n);
+      return team[a] != team[b] ? team[a] > team[b] : cost(a) > cost(b);
     });
+    std::vector<int> sorted(num_sys);
+    for (int s = 0; s < num_sys; ++s) sorted[s] = team[order[s]];
+    bs->pph = make_phases(sorted, bs->grid_p);
     GABP_HIP(c, hipMemcpyAsync(bs->porder_d, order.data(), sizeof(int32_t) * num_sys, hipMemcpyHostToDevice, st));
     GABP_HIP(c, hipStreamSynchronize(st));
+  }
+  // control blocks: fewer than one team of two or more per workgroup and kernel
+  {
+    const int64_t teams = (int64_t)bs->grid_p + bs->grid_r;
+    static_assert(sizeof(BatchCtl) % 128 == 0 && sizeof(TeamCtl) == 128, "control lines");
+    unsigned char* base = nullptr;
+    const int64_t bytes = (int64_t)sizeof(BatchCtl) + teams * (int64_t)sizeof(TeamCtl);
+    BTRY(raw_alloc(c, &base, bytes));
+    bs->ctl_d = (BatchCtl*)base;
+    bs->tctl_d[0] = (TeamCtl*)(base + sizeof(BatchCtl));
+    bs->tctl_d[1] = bs->tctl_d[0] + bs->grid_p;
+    bs->ctl_words = bytes / 8;
+    BTRY(raw_alloc(c, &bs->tred_d, (int64_t)kPhases * 2 * std::max(bs->grid_p, bs->grid_r) * kTeamVals));
   }
   return GABP_OK;
 }
@@ -1094,21 +1343,22 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
     if (rhs_off[s + 1] - rhs_off[s] != ns * nrhs[s]) return fail(c, GABP_E_ARG, "rhs_off does not match n_s * k_s");
   }
   if (rhs_off[S] > 0 && (!B || !X)) return fail(c, GABP_E_ARG, "NULL B or X");
-  const bool same = bs->exec && bs->key_B == B && bs->key_X == X && bs->key_tol == tol &&
-                    bs->key_iter == max_iter &&
-                    bs->key_nrhs == std::vector<int32_t>(nrhs, nrhs + S) &&
-                    bs->key_off == std::vector<int64_t>(rhs_off, rhs_off + S + 1);
-  if (!same) {
-    // Work items, costliest first.  The work of one right-hand side of a
-    // system is taken as (slots + rows) per sweep times the system's relative
-    // sweep count.  A system's right-hand sides are grouped in 8, 4, 2 or 1,
-    // the largest group whose item stays within a third of an even share of
-    // the whole batch per workgroup, so that no item is long next to the
-    // makespan.
+  hipStream_t st = c->stream;
+  if (bs->key_nrhs != std::vector<int32_t>(nrhs, nrhs + S)) {  // rhs_off follows from nrhs
+    bs->key_nrhs.clear();
+    // Work items, largest teams and costliest first.  The work of one
+    // right-hand side of a system is taken as (slots + rows) per sweep times
+    // the system's relative sweep count.  A system's right-hand sides are
+    // grouped in 8, 4, 2 or 1, the largest group whose item, split over the
+    // largest team it can have, stays within a third of an even share of the
+    // whole batch per workgroup, so that no item is long next to the makespan.
     auto unit = [&](int s) { return (double)(bs->sys_h[s].S + bs->sys_h[s].n) * bs->sys_weight[s]; };
+    auto waves = [&](int s, int kg) {  // 64-lane units of a pass (of a colour class)
+      return (int64_t)bs->sys_h[s].nsl * kg / std::max(1, bs->sys_h[s].ncls);
+    };
     double total = 0.0;
     for (int s = 0; s < S; ++s) total += unit(s) * nrhs[s];
-    const double cap = std::max(1.0, total / (3.0 * std::max(1, bs->grid_r)));
+    const double share = std::max(1.0, total / std::max(1, bs->grid_r)), cap = share / 3.0;
     std::vector<BItem> items;
     int64_t oh = 0, onk = 0, ox = 0;
     for (int s = 0; s < S; ++s) {
@@ -1116,7 +1366,7 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
       if (R.n == 0) continue;
       const int32_t k = nrhs[s];
       int32_t gmax = kMaxGroup;
-      while (gmax > 1 && unit(s) * gmax > cap) gmax >>= 1;
+      while (gmax > 1 && unit(s) * gmax / team_for(unit(s) * gmax, 0.0, waves(s, gmax)) > cap) gmax >>= 1;
       for (int32_t j0 = 0; j0 < k;) {
         int32_t kg = gmax;
         while (kg > k - j0) kg >>= 1;
@@ -1136,9 +1386,14 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
         j0 += kg;
       }
     }
+    auto team = [&](const BItem& it) { return team_for(unit(it.sys) * it.kg, share, waves(it.sys, it.kg)); };
     std::stable_sort(items.begin(), items.end(), [&](const BItem& a, const BItem& b) {
-      return unit(a.sys) * a.kg > unit(b.sys) * b.kg;
+      const int ta = team(a), tb = team(b);
+      return ta != tb ? ta > tb : unit(a.sys) * a.kg > unit(b.sys) * b.kg;
     });
+    std::vector<int> teams;
+    for (const BItem& it : items) teams.push_back(team(it));
+    bs->rph = make_phases(teams, bs->grid_r);
     bs->items = items;
     BTRY(grow(c, &bs->hbuf, &bs->hcap, oh));
     BTRY(grow(c, &bs->nkbuf, &bs->nkcap, onk));
@@ -1153,81 +1408,71 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
       BTRY(raw_alloc(c, &bs->infos_d, (int64_t)items.size()));
       bs->items_cap = items.size();
     }
-    if (!items.empty())
-      GABP_HIP(c, hipMemcpyAsync(bs->items_d, items.data(), sizeof(BItem) * items.size(), hipMemcpyHostToDevice,
-                                 c->stream));
-    BatchArgs a{};
-    a.sys = bs->sys_d;
-    a.slices = bs->slices_d;
-    a.cls_sl = bs->cls_sl_d;
-    a.deg = bs->deg_d;
-    a.d32 = bs->d32_d;
-    a.d64 = bs->d64_d;
-    a.umap = bs->umap_d;
-    a.col = bs->col_d;
-    a.a32 = bs->a32_d;
-    a.a64 = bs->a64_d;
-    a.porder = bs->porder_d;
-    a.num_sys = S;
-    a.pP = bs->pP_d;
-    a.pcoef = bs->pcoef_d;
-    a.pagg = bs->pagg_d;
-    a.pinv = bs->pinv_d;
-    a.pinfos = bs->pinfo_d;
-    a.items = bs->items_d;
-    a.num_items = (int32_t)items.size();
-    a.infos = bs->infos_d;
-    a.hbuf = bs->hbuf;
-    a.nkbuf = bs->nkbuf;
-    a.xbuf = bs->xbuf;
-    a.queue = bs->queue_d;
-    a.B = B;
-    a.X = X;
-    a.tol = tol;
-    a.inner_tol = (float)c->opts.inner_tol;
-    a.inner_max = std::max(1, c->opts.inner_max_iter);
-    a.max_outer = std::max(1, c->opts.max_outer);
-    a.max_iter = std::max(1, max_iter);
-    if (bs->exec) {
-      (void)hipGraphExecDestroy(bs->exec);
-      bs->exec = nullptr;
+    if (!items.empty()) {
+      GABP_HIP(c, hipMemcpyAsync(bs->items_d, bs->items.data(), sizeof(BItem) * items.size(), hipMemcpyHostToDevice,
+                                 st));
+      GABP_HIP(c, hipStreamSynchronize(st));
     }
-    if (bs->graph) {
-      (void)hipGraphDestroy(bs->graph);
-      bs->graph = nullptr;
-    }
-    // capture: queue reset (a kernel, not a memset node), the precision phase,
-    // then the right-hand sides
-    GABP_HIP(c, hipStreamSynchronize(c->stream));
-    GABP_HIP(c, hipStreamBeginCapture(bs->gs, hipStreamCaptureModeThreadLocal));
-    hipLaunchKernelGGL(k_reset_queues, dim3(1), dim3(64), 0, bs->gs, bs->queue_d);
-    const int gp = std::max(1, std::min(bs->grid_p, S));
-    const int gr = std::max(1, std::min<int>(bs->grid_r, (int)items.size()));
-    bs->launched_grid = gr;
-    if (bs->serial) {
-      hipLaunchKernelGGL(k_bprec<true>, dim3(gp), dim3(kBT), 0, bs->gs, a);
-      if (!items.empty()) hipLaunchKernelGGL(k_brhs<true>, dim3(gr), dim3(kBT), 0, bs->gs, a);
-    } else {
-      hipLaunchKernelGGL(k_bprec<false>, dim3(gp), dim3(kBT), 0, bs->gs, a);
-      if (!items.empty()) hipLaunchKernelGGL(k_brhs<false>, dim3(gr), dim3(kBT), 0, bs->gs, a);
-    }
-    hipError_t e = hipStreamEndCapture(bs->gs, &bs->graph);
-    if (e != hipSuccess) return hip_fail(c, e, "hipStreamEndCapture");
-    GABP_HIP(c, hipGraphInstantiate(&bs->exec, bs->graph, nullptr, nullptr, 0));
-    bs->key_B = B;
-    bs->key_X = X;
-    bs->key_tol = tol;
-    bs->key_iter = max_iter;
     bs->key_nrhs.assign(nrhs, nrhs + S);
-    bs->key_off.assign(rhs_off, rhs_off + S + 1);
   }
   if (bs->items.empty()) return GABP_OK;
-  GABP_HIP(c, hipStreamSynchronize(c->stream));  // B written by the caller's stream
-  GABP_HIP(c, hipGraphLaunch(bs->exec, bs->gs));
+  BatchArgs a{};
+  a.sys = bs->sys_d;
+  a.slices = bs->slices_d;
+  a.cls_sl = bs->cls_sl_d;
+  a.deg = bs->deg_d;
+  a.d32 = bs->d32_d;
+  a.d64 = bs->d64_d;
+  a.umap = bs->umap_d;
+  a.col = bs->col_d;
+  a.a32 = bs->a32_d;
+  a.a64 = bs->a64_d;
+  a.porder = bs->porder_d;
+  a.num_sys = S;
+  a.pP = bs->pP_d;
+  a.pcoef = bs->pcoef_d;
+  a.pagg = bs->pagg_d;
+  a.pinv = bs->pinv_d;
+  a.pinfos = bs->pinfo_d;
+  a.items = bs->items_d;
+  a.num_items = (int32_t)bs->items.size();
+  a.infos = bs->infos_d;
+  a.hbuf = bs->hbuf;
+  a.nkbuf = bs->nkbuf;
+  a.xbuf = bs->xbuf;
+  a.ctl = bs->ctl_d;
+  a.tctl[0] = bs->tctl_d[0];
+  a.tctl[1] = bs->tctl_d[1];
+  a.tred = bs->tred_d;
+  a.pph = bs->pph;
+  a.rph = bs->rph;
+  a.roll_limit = (uint64_t)bs->clock_khz * kRollMs;
+  a.B = B;
+  a.X = X;
+  a.tol = tol;
+  a.inner_tol = (float)c->opts.inner_tol;
+  a.inner_max = std::max(1, c->opts.inner_max_iter);
+  a.max_outer = std::max(1, c->opts.max_outer);
+  a.max_iter = std::max(1, max_iter);
+  // control blocks cleared (a kernel, not a memset), the precision phase, then
+  // the right-hand sides; with teams every workgroup that can be resident
+  hipLaunchKernelGGL(k_reset_ctl, dim3((unsigned)std::min<int64_t>((bs->ctl_words + 255) / 256, 256)), dim3(256), 0, st,
+                     (uint64_t*)bs->ctl_d, bs->ctl_words);
+  const int gp = bs->pph.teams ? bs->grid_p : std::max(1, std::min(bs->grid_p, S));
+  const int gr = bs->rph.teams ? bs->grid_r : std::max(1, std::min<int>(bs->grid_r, (int)bs->items.size()));
+  bs->launched_grid = gr;
+  if (bs->serial) {
+    hipLaunchKernelGGL(k_bprec<true>, dim3(gp), dim3(kBT), 0, st, a);
+    hipLaunchKernelGGL(k_brhs<true>, dim3(gr), dim3(kBT), 0, st, a);
+  } else {
+    hipLaunchKernelGGL(k_bprec<false>, dim3(gp), dim3(kBT), 0, st, a);
+    hipLaunchKernelGGL(k_brhs<false>, dim3(gr), dim3(kBT), 0, st, a);
+  }
+  GABP_HIP(c, hipGetLastError());
   std::vector<ItemInfo> ii(bs->items.size()), pi(S);
-  GABP_HIP(c, hipMemcpyAsync(ii.data(), bs->infos_d, sizeof(ItemInfo) * ii.size(), hipMemcpyDeviceToHost, bs->gs));
-  GABP_HIP(c, hipMemcpyAsync(pi.data(), bs->pinfo_d, sizeof(ItemInfo) * S, hipMemcpyDeviceToHost, bs->gs));
-  GABP_HIP(c, hipStreamSynchronize(bs->gs));
+  GABP_HIP(c, hipMemcpyAsync(ii.data(), bs->infos_d, sizeof(ItemInfo) * ii.size(), hipMemcpyDeviceToHost, st));
+  GABP_HIP(c, hipMemcpyAsync(pi.data(), bs->pinfo_d, sizeof(ItemInfo) * S, hipMemcpyDeviceToHost, st));
+  GABP_HIP(c, hipStreamSynchronize(st));
   // load-balance profile of the launch
   {
     gabp_batch_profile& pf = bs->prof;
@@ -1241,14 +1486,14 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
       if (bs->sys_h[s].n == 0) continue;
       plo = std::min(plo, pi[s].t0);
       phi = std::max(phi, pi[s].t1);
-      busy += (double)(pi[s].t1 - pi[s].t0) / bs->clock_khz;
+      busy += (double)(pi[s].t1 - pi[s].t0) / bs->clock_khz * std::max(1, pi[s].pad);
       pf.precision_sweeps += pi[s].psweeps;
     }
     for (size_t q = 0; q < ii.size(); ++q) {
       lo = std::min(lo, ii[q].t0);
       hi = std::max(hi, ii[q].t1);
       const double ms = (double)(ii[q].t1 - ii[q].t0) / bs->clock_khz;
-      busy += ms;
+      busy += ms * std::max(1, ii[q].pad);
       if (ms > longest) {
         longest = ms;
         arg = q;
@@ -1306,15 +1551,12 @@ gabp_status batched_profile(Ctx* c, gabp_batch_profile* out) {
 void batched_destroy(Ctx* c) {
   auto* bs = (BatchState*)c->batch;
   if (!bs) return;
-  if (bs->exec) (void)hipGraphExecDestroy(bs->exec);
-  if (bs->graph) (void)hipGraphDestroy(bs->graph);
-  for (void* p : {(void*)bs->items_d, (void*)bs->infos_d, (void*)bs->queue_d, (void*)bs->sys_d,
+  for (void* p : {(void*)bs->items_d, (void*)bs->infos_d, (void*)bs->ctl_d, (void*)bs->tred_d, (void*)bs->sys_d,
                   (void*)bs->slices_d, (void*)bs->cls_sl_d, (void*)bs->deg_d, (void*)bs->d32_d, (void*)bs->d64_d,
                   (void*)bs->umap_d, (void*)bs->col_d, (void*)bs->a32_d, (void*)bs->a64_d, (void*)bs->porder_d,
                   (void*)bs->pP_d, (void*)bs->pcoef_d, (void*)bs->pagg_d, (void*)bs->pinv_d, (void*)bs->pinfo_d,
                   (void*)bs->hbuf, (void*)bs->nkbuf, (void*)bs->xbuf})
     free_raw(p);
-  if (bs->gs) (void)hipStreamDestroy(bs->gs);
   delete bs;
   c->batch = nullptr;
 }
