@@ -170,9 +170,14 @@ typedef struct {
  * Aitken or Steffensen step, no sweep timing) on a compact-layout handle with
  * n <= 1024 rows, and either at most 4096 directed slots or at most 6 slots in
  * every row, runs every sweep, check and stop decision inside one launch of
- * 1024 lanes, with the messages in registers and the aggregates in LDS.  Both
- * paths perform the same operations; x, the variances and the messages agree
- * bit for bit, the reported residual up to its summation order. */
+ * 1024 lanes, with the messages in registers and the aggregates in LDS.  A
+ * larger compact or colour-serial system whose messages fit the registers of
+ * the chip (rows of at most 96 slots) runs the whole solve, with its inner
+ * solves and outer steps if it has any, in one launch of resident workgroups.
+ * All paths perform the same operations; x, the variances and the messages
+ * agree bit for bit, the reported residual up to its summation order.  (Inner
+ * solves of the launch-per-sweep refinement may skip checks of rounds far
+ * above their predicted stop; the resident ones check every round.) */
 #define GABP_FLAG_MULTI_LAUNCH 32
 
 /* Test aid for the compact layout (ignored by the other layouts; implies one

@@ -288,7 +288,12 @@ struct ResCtl {
 struct ResArgs {
   int32_t n, E;
   const int2* blk;          // [workgroups] {first row, rows}
-  const int2* lane;         // [workgroups][lanes] {row or -1, place in the chain | chain length << 16}
+  const int2* lane;         // [workgroups][lanes] {row or -1, place in the chain | chain length << 8 | class << 16}
+  // colour-serial: first row of every class (then n), and the workgroups' rows
+  // of every class, [workgroups][ncls + 1] {first row, LDS index of it}
+  int32_t ncls;
+  const int32_t* cls_start;
+  const int2* cls_tab;
   int32_t rows_cap;         // most rows of a workgroup
   const int32_t* off_ptr;   // off-diagonal CSR
   const int32_t* col;
@@ -326,7 +331,7 @@ struct ResArgs {
 };
 struct ResPlanHost {
   int K = 0, lanes = 0, rows_cap = 0;
-  std::vector<int2> blk, lane;
+  std::vector<int2> blk, lane, cls_tab;
 };
 using ResKernel = void (*)(ResArgs);
 ResKernel res_kernel32(int lanes, int K, int mode);
@@ -334,6 +339,8 @@ struct ResPlan {
   int mode = 0, K = 0, lanes = 0, nb = 0, rows_cap = 0, phase = 0, khz = 0;
   int2* blk_d = nullptr;
   int2* lane_d = nullptr;
+  int2* cls_tab_d = nullptr;
+  int32_t* cls_start_d = nullptr;
   ResCtl* ctl_d = nullptr;  // [2], used in turn
 };
 
@@ -618,6 +625,8 @@ void dev_free(Ctx* c, void* p);
 // ---- resident solve (resident.hip) -----------------------------------------
 ResPlanHost plan_resident(const std::vector<int32_t>& off_ptr, int32_t n, int K, int lanes, int max_blocks,
                           const std::vector<int32_t>& parts);
+ResPlanHost plan_resident_serial(const std::vector<int32_t>& off_ptr, int32_t n, int K, int lanes, int max_blocks,
+                                 const std::vector<int32_t>& classes);
 // the plan, kept when the handle's solves can take it; before the autotuner,
 // which has nothing to choose then
 gabp_status setup_resident(Ctx* c);

@@ -2,7 +2,8 @@
 // decision of a compact-layout solve in ONE launch whose workgroups stay on the
 // chip, one per CU, with the messages in registers.  The plain FP64 iteration,
 // the single loop of Ch. 5 Sec. 5.3, and the refinement and loading loops with
-// their inner solves (FP32 or FP64), freeze and FP64 residuals.
+// their inner solves (FP32 or FP64), freeze and FP64 residuals; synchronous or
+// colour-serial sweeps.
 //
 // What bounds the launch-per-sweep path on such systems: a sweep launch and
 // its finish kernel cost 10-12 us of dispatch and drain whatever the size, and
@@ -25,8 +26,8 @@
 //     line per group of 8 workgroup ids (the XCD of a round-robin dispatch),
 //     one root, one release line per group.  Measured alone on 256 workgroups:
 //     1.84 us, against 3.76 us with one counter and 3.09 us with a flag per
-//     workgroup polled by all; up to 32 workgroups one counter is the fastest
-//     (1.0 us).
+//     workgroup polled by all; up to 64 workgroups one counter is the fastest
+//     (1.0 us at 32 workgroups, 1.4 against 1.5 us at 64).
 // The workgroups must all be resident at once for the barrier to end.  The
 // host launches no more of them than the device holds, and the first barrier
 // is a roll call with a time limit: if the device is busy with other work and
@@ -44,7 +45,10 @@
 // 130003 596 -> 355 us, the double loop on B^T B + 0.1 I with n = 30000 50.5 ->
 // 27.7 ms.
 //
-// The arithmetic is that of the compact sweep kernels operation for operation
+// Colour-serial sweeps end a class with a grid barrier instead of a launch:
+// 47^3 grid to 1e-10 (66 sweeps of 2 classes) 1.33 ms -> 756 us.
+//
+// The arithmetic is that of the compact and serial sweep kernels operation for operation
 // (products and sums separately rounded): x, the variances and the messages
 // equal theirs bit for bit; only the residual norm is summed in another order.
 #pragma once
@@ -63,7 +67,7 @@ namespace {
 
 constexpr int kRL = kResLanes;
 constexpr int kGroups = 8;
-constexpr int kFlatBlocks = 32;  // at most this many workgroups share one counter
+constexpr int kFlatBlocks = 64;  // at most this many workgroups share one counter
 
 template <typename T>
 using vec2 = T __attribute__((ext_vector_type(2)));
@@ -182,33 +186,42 @@ __device__ __forceinline__ GridPos grid_pos() {
 }
 
 // One lane: arrive at barrier `ep` (1, 2, ...).  Counters hold arrivals in the
-// low 40 bits and raised flags above.  Returns true for the last arrival of
-// the whole grid, with the flags of all in *bad.
+// low 40 bits and raised flags above (with one counter, by the parity of ep:
+// the counter itself is what the others wait on, and a workgroup that is
+// already one barrier ahead must not be heard early).  Returns true for the
+// last arrival of the whole grid, with the flags of all in *bad.
+constexpr uint64_t kCountMask = (1ull << 40) - 1;
 __device__ __forceinline__ bool grid_arrive(ResCtl* c, const GridPos& p, uint32_t ep, bool bad, bool* any_bad) {
-  const uint64_t inc = 1ull + (bad ? (1ull << 40) : 0ull);
-  const uint64_t mask = (1ull << 40) - 1;
+  const uint64_t inc = 1ull + (bad ? (1ull << (p.ngrp == 1 && (ep & 1) ? 52 : 40)) : 0ull);
   uint64_t v = AGENT_ADD(&c->grp[p.grp].v, inc) + inc;
-  if ((v & mask) != (uint64_t)ep * p.gsize) return false;
+  if ((v & kCountMask) != (uint64_t)ep * p.gsize) return false;
   bool b = (v >> 40) != 0;
   if (p.ngrp > 1) {
     const uint64_t inc2 = 1ull + (b ? (1ull << 40) : 0ull);
     v = AGENT_ADD(&c->root.v, inc2) + inc2;
-    if ((v & mask) != (uint64_t)ep * p.ngrp) return false;
+    if ((v & kCountMask) != (uint64_t)ep * p.ngrp) return false;
     b = (v >> 40) != 0;
   }
   *any_bad = b;
   return true;
 }
 
-// One lane: wait for barrier `ep`.  The release word holds the barrier number
-// and the flags raised before it, so every workgroup leaves it with the same
-// answer.
+// One lane: wait for barrier `ep`: on the one counter, or on the group's
+// release word, which holds the barrier number and the flags raised before it,
+// so that every workgroup leaves it with the same answer.
 __device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t ep, bool last, bool any_bad,
                                          uint64_t limit) {
+  const uint64_t t0 = wall_clock64();
+  if (p.ngrp == 1) {
+    for (;;) {
+      const uint64_t v = AGENT_LOAD(&c->grp[0].v);
+      if ((v & kCountMask) >= (uint64_t)ep * p.gsize) return ((v >> (ep & 1 ? 52 : 40)) & 0xfff) ? kWaitBad : kWaitOk;
+      if (wall_clock64() - t0 > limit) return kWaitEnd;
+    }
+  }
   const uint64_t word = (uint64_t)ep | (any_bad ? (1ull << 63) : 0ull);
   if (last)
     for (uint32_t k = 0; k < p.ngrp; ++k) AGENT_STORE(&c->rel[k].v, word);
-  const uint64_t t0 = wall_clock64();
   for (;;) {
     const uint64_t v = AGENT_LOAD(&c->rel[p.grp].v);
     if ((v & ~(1ull << 63)) >= ep) return (v >> 63) ? kWaitBad : kWaitOk;
@@ -244,15 +257,21 @@ enum ResMode : int {
   kResOuter = 2,   // refinement / loading loop around inner solves
   kResLoop = 3,    // the single loop: plain sweeps with damped feedback of the means
   kResOuterLoop = 4,  // refinement around single-loop inner solves
-  kResRefine = 5   // kResOuter without frozen precisions (fewer registers)
+  kResRefine = 5,  // kResOuter without frozen precisions (fewer registers)
+  kResSerial = 6,  // colour-serial sweeps: the classes in turn, a grid barrier after each
+  kResSerialOuter = 7  // refinement / loading loop around colour-serial inner solves
 };
+constexpr bool res_outer(int mode) {
+  return mode == kResOuter || mode == kResOuterLoop || mode == kResRefine || mode == kResSerialOuter;
+}
 
 // LANES lanes per workgroup, one workgroup per CU: 128 VGPRs at 1024 lanes, of
 // which the FP64 messages of K slots take 8 K, so there A_ij, the neighbours
 // and the rows' prior live in LDS; with fewer lanes they stay in registers too.
 template <typename T, int LANES, int K, int MODE>
 __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
-  constexpr bool OUTER = MODE == kResOuter || MODE == kResOuterLoop || MODE == kResRefine;
+  constexpr bool OUTER = res_outer(MODE);
+  constexpr bool SERIAL = MODE == kResSerial || MODE == kResSerialOuter;
   constexpr bool FEED = MODE == kResLoop || MODE == kResOuterLoop;
   constexpr bool REG = LANES < kRL;
   constexpr int NW = LANES / 64;
@@ -284,7 +303,8 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
 
   // ---- set-up: the lane's slots and row ------------------------------------
   const int2 ld = A.lane[(size_t)b * LANES + tid];
-  const int row = ld.x, pos = ld.y & 0xffff, len = ld.y >> 16;
+  const int row = ld.x, pos = ld.y & 0xff, len = (ld.y >> 8) & 0xff;
+  const int cls = ld.y >> 16;  // colour class (colour-serial)
   const bool own = row >= 0;
   const bool tail = own && pos == len - 1;
   int cnt = 0;
@@ -311,6 +331,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // of the workgroup and contributes nothing
   int cc[K];
   double aa[K];
+  uint32_t lowmask = 0;  // colour-serial: slots whose neighbour lies in an earlier class
   // joint: incoming messages {P, h} of the even and the odd rounds; frozen
   // precisions: {g_in, g_out} and the h messages of the two parities
   T mP0[K], mH0[K], mP1[K], mH1[K];
@@ -321,7 +342,19 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     mP0[k] = mH0[k] = mP1[k] = mH1[k] = 0;
     if (k < cnt) {
       c = A.col[s0 + k];
-      c = (unsigned)(c - r0) < (unsigned)nrow ? ~(c - r0) : c * (int)sizeof(V2);
+      int local = c - r0;  // colour-serial: the workgroup's rows are a range of every class
+      if constexpr (SERIAL) {
+        int lo = 0, hi = A.ncls - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (A.cls_start[mid] <= c) lo = mid;
+          else hi = mid - 1;
+        }
+        const int2 w = A.cls_tab[(size_t)b * (A.ncls + 1) + lo], w1 = A.cls_tab[(size_t)b * (A.ncls + 1) + lo + 1];
+        local = (unsigned)(c - w.x) < (unsigned)(w1.y - w.y) ? w.y + c - w.x : -1;
+        if (lo < cls) lowmask |= 1u << k;
+      }
+      c = (unsigned)local < (unsigned)nrow ? ~local : c * (int)sizeof(V2);
       av = A.a[s0 + k];
       if (MODE == kResFrozen || (MODE == kResOuter && A.frozen)) {
         const V2 cf = ((const V2*)A.coef)[s0 + k];
@@ -336,6 +369,12 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       s_c[k * LANES + tid] = c;
       s_a[k * LANES + tid] = av;
     }
+  }
+  // LDS index of the lane's row
+  int lrow = row - r0;
+  if constexpr (SERIAL) {
+    const int2 w = own ? A.cls_tab[(size_t)b * (A.ncls + 1) + cls] : int2{0, 0};
+    lrow = w.y + row - w.x;
   }
   auto slot_a = [&](int k) -> double { return REG ? aa[k] : s_a[k * LANES + tid]; };
   auto row_d = [&]() -> double { return REG ? d64 : s_d[tid]; };
@@ -354,8 +393,8 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (tail) {
       const V2 v = {honly ? x1 : din, rhs};
       if (nb > 1) st_rec<V2>(buf0, row, v);
-      s_agg[row - r0] = v;
-      s_x[row - r0] = x1;
+      s_agg[lrow] = v;
+      s_x[lrow] = x1;
     }
   };
   publish_prior(MODE == kResFrozen || (MODE == kResOuter && A.frozen));
@@ -448,6 +487,154 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // result of a run of sweeps (kept for the caller of the run)
   double last_rel = -1.0, prev_rel = -1.0;
   int last_round = -1, prev_round = -1, conv = -1, err = 0;
+
+  // Colour-serial sweeps (serial.hip) on the system with right-hand side `rhs`:
+  // a slot holds the outgoing message of its row's last update (mP0, mH0), the
+  // aggregates are updated in place, class by class.  As `run` below otherwise;
+  // M >= 1.
+  auto run_serial = [&](const double tol_in, const int M, const double norm) {
+    const bool exact = !(tol_in > 0.0);
+    const double tol = exact ? -1.0 : tol_in;
+    auto in_set = [&](int j) { return j == M || (j % ce) == 0; };
+    auto rel_of = [&](double tot) {
+      const double rn = sqrt(tot);
+      return norm > 0.0 ? rn / norm : rn;
+    };
+    bool pending = false;
+    conv = last_round = prev_round = -1;
+    last_rel = prev_rel = -1.0;
+    err = 0;
+    int nbar = 0;        // barriers of this run: the flag word in use
+    double lsum = 0.0;   // the row's residual part of the earlier classes, from the last sweep
+    for (int t = 1;; ++t) {
+      if (pending) {
+        const double rel = uni_r(rel_of(total(s_red[(t - 1) & 1])));
+        prev_rel = last_rel;
+        prev_round = last_round;
+        last_rel = rel;
+        last_round = t - 2;
+        pending = false;
+        if (rel <= tol) conv = t - 2;
+        else if (!(rel <= kDivergeLimit)) err |= kErrDiverged;
+        if (conv >= 0 || err || lost) break;
+      }
+      const bool fin = t == M + 1;  // the residual of sweep M alone, every row at once
+      const bool ck = exact ? fin : (t >= 2 && t <= M + 1 && in_set(t - 1));
+      if (t > M && !ck) break;
+      const bool first = t == 1, wl = !exact && t < M && in_set(t);
+      double res = 0.0;  // the row's residual of round t-1
+      const int ncls = fin ? 1 : A.ncls;
+      for (int q = 0; q < ncls; ++q) {
+        const bool act = own && (fin || cls == q);
+        bool bad = false;
+        if (__any(act)) {
+          int cr[K];
+          V2 g[K];
+#pragma unroll
+          for (int k = 0; k < K; ++k) cr[k] = REG ? cc[k] : s_c[k * LANES + tid];
+          if (nb > 1) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) g[k] = ld_rec<V2>(buf0, cr[k] < 0 || !act ? kNoRec : (uint32_t)cr[k]);
+          }
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            const V2 l = s_agg[cr[k] < 0 ? ~cr[k] : 0];
+            if (nb == 1 || cr[k] < 0) g[k] = l;
+          }
+          T ax[K];
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            const T av = (T)slot_a(k);
+            const bool low = !fin && ((lowmask >> k) & 1u);
+            ax[k] = 0;
+            if (low ? wl : ck) ax[k] = av * (g[k].y / g[k].x);
+            if (act && !fin) {
+              T Pin = 0, hin = 0;  // in the first sweep a later class has sent nothing yet
+              if (!first || low) {
+                const T inv = T(1) / (g[k].x - mP0[k]);
+                Pin = -av * av * inv;
+                hin = -av * (g[k].y - mH0[k]) * inv;
+              }
+              mP0[k] = Pin;  // kept in the slot until the row's aggregate is known
+              mH0[k] = hin;
+              bad |= k < cnt && !(isfinite(Pin) && isfinite(hin));
+            }
+            if (!REG) __builtin_amdgcn_sched_barrier(0);
+          }
+          T P = din, h = rhs;
+          double Ls = 0.0, U = 0.0;
+          for (int c = 0; c < wmax; ++c) {
+            if (c > 0) {
+              const T Pu = dpp<kWaveShr1, 0xf>(P, P), hu = dpp<kWaveShr1, 0xf>(h, h);
+              const double Lu = dpp<kWaveShr1, 0xf>(Ls, Ls), Uu = dpp<kWaveShr1, 0xf>(U, U);
+              if (pos == c) {
+                P = Pu;
+                h = hu;
+                Ls = Lu;
+                U = Uu;
+              }
+            }
+            if (pos == c) {
+#pragma unroll
+              for (int k = 0; k < K; ++k)
+                if (k < cnt) {
+                  if (!fin) {
+                    P += mP0[k];
+                    h += mH0[k];
+                  }
+                  if (!fin && ((lowmask >> k) & 1u)) Ls += (double)ax[k];
+                  else U += (double)ax[k];
+                }
+            }
+          }
+          if (act && ck) res = (double)rhs - (double)din * (double)(o1h / o1P) - (fin ? 0.0 : lsum) - U;
+          if (!fin) {
+            for (int c = wmax - 2; c >= 0; --c) {
+              const T Pd = dpp<kWaveShl1, 0xf>(P, P), hd = dpp<kWaveShl1, 0xf>(h, h);
+              if (pos == c && pos < len - 1) {
+                P = Pd;
+                h = hd;
+              }
+            }
+            if (act) {
+              if (wl) lsum = Ls;
+              o2P = o1P;
+              o2h = o1h;
+              o1P = P;
+              o1h = h;
+              if (tail) {
+                if (nb > 1) st_rec<V2>(buf0, row, V2{P, h});
+                s_agg[lrow] = V2{P, h};
+              }
+#pragma unroll
+              for (int k = 0; k < K; ++k) {  // out_{j->i} = F(agg_j, in_{i->j})
+                const T av = (T)slot_a(k);
+                const T inv = T(1) / (P - mP0[k]);
+                const T Po = -av * av * inv, ho = -av * (h - mH0[k]) * inv;
+                mP0[k] = Po;
+                mH0[k] = ho;
+                bad |= k < cnt && !(isfinite(Po) && isfinite(ho));
+                if (!REG) __builtin_amdgcn_sched_barrier(0);
+              }
+            }
+          }
+        }
+        ++nbar;
+        if (tid == 0) s_bad[(nbar + 1) % 3] = 0;
+        if (bad) s_bad[nbar % 3] = 1;
+        const bool send = ck && q == ncls - 1;
+        if (send) {
+          const double v = wsum_r(tail ? res * res : 0.0);
+          if (lane == 0) s_red[t & 1][wave] = v;
+          ++seq;
+          pending = true;
+        }
+        if (grid_barrier(send ? s_red[t & 1] : nullptr, &s_bad[nbar % 3])) err |= kErrNonfinite;
+        if (err || lost) break;
+      }
+      if (err || lost) break;
+    }
+  };
 
   // Sweeps on the system with right-hand side `rhs` (round 0 published) to a
   // relative residual of tol (<= 0: exactly M sweeps): conv, err and the
@@ -612,8 +799,8 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
         if (tail) {
           const V2 v = {HONLY ? x1 : P, h};
           if (nb > 1) st_rec<V2>(ODD ? buf1 : buf0, row, v);
-          s_agg[pn * cap + row - r0] = v;
-          if (!HONLY) s_x[pn * cap + row - r0] = x1;
+          s_agg[pn * cap + lrow] = v;
+          if (!HONLY) s_x[pn * cap + lrow] = x1;
         }
       }
       if (tid == 0) s_bad[(t + 1) % 3] = 0;
@@ -638,7 +825,8 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   if constexpr (!OUTER) {
     constexpr bool HONLY = MODE == kResFrozen;
     const int M = A.max_iter;
-    run(std::integral_constant<bool, HONLY>{}, A.tol, M, bnorm);
+    if constexpr (SERIAL) run_serial(A.tol, M, bnorm);
+    else run(std::integral_constant<bool, HONLY>{}, A.tol, M, bnorm);
     // ---- results: the returned round and the state it leaves ---------------
     // the own aggregates are of rounds T = min(conv + 1, M) and T - 1
     const int ret = conv >= 0 ? conv : M;
@@ -691,6 +879,8 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       if constexpr (MODE == kResOuter) {
         if (frozen) run(std::true_type{}, A.inner_tol, M, rnorm);
         else run(std::false_type{}, A.inner_tol, M, rnorm);
+      } else if constexpr (SERIAL) {
+        run_serial(A.inner_tol, M, rnorm);
       } else {
         run(std::false_type{}, A.inner_tol, M, rnorm);
       }
@@ -735,7 +925,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       }
       if (tail) {
         if (nb > 1) st_rec<double>(bufx, row, x);
-        s_xo[row - r0] = x;
+        s_xo[lrow] = x;
       }
       grid_barrier(nullptr, nullptr);
       if (lost) break;
@@ -810,7 +1000,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
 template <typename T>
 uint32_t res_lds(int rows_cap, int lanes, int K, int mode) {
   size_t b = 2 * (size_t)rows_cap * (sizeof(vec2<T>) + sizeof(T));
-  if (mode == kResOuter || mode == kResOuterLoop || mode == kResRefine) b += sizeof(double) * (size_t)rows_cap;
+  if (res_outer(mode)) b += sizeof(double) * (size_t)rows_cap;
   if (lanes == kRL) b += (size_t)lanes * (K * (sizeof(double) + sizeof(int)) + 2 * sizeof(double));
   return (uint32_t)b;
 }

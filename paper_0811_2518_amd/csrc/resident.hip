@@ -7,6 +7,8 @@
 
 namespace gabp {
 
+static const int2 kIdleLane{-1, 1 << 8};
+
 // The plan: rows dealt to lanes in order, chains inside one wave, workgroups
 // of `lanes` lanes (with XCD parts: no workgroup spans two of them, and every
 // part gets the same number).  Empty when the system does not fit.
@@ -43,7 +45,7 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
       int2 cur{lo, 0};
       std::vector<int2> ll;
       auto close = [&](int32_t next) {
-        ll.resize(lanes, int2{-1, 1 << 16});
+        ll.resize(lanes, kIdleLane);
         lane[p].insert(lane[p].end(), ll.begin(), ll.end());
         blk[p].push_back(cur);
         ll.clear();
@@ -58,8 +60,8 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
           close(r);
           at = 0;
         }
-        ll.resize(at, int2{-1, 1 << 16});
-        for (int q = 0; q < len; ++q) ll.push_back(int2{r, q | (len << 16)});
+        ll.resize(at, kIdleLane);
+        for (int q = 0; q < len; ++q) ll.push_back(int2{r, q | (len << 8)});
         used = at + len;
         ++cur.y;
       }
@@ -74,7 +76,7 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
     for (size_t p = 0; p < np; ++p) {
       for (; blk[p].size() < q;) {  // empty workgroups keep part p on XCD p
         blk[p].push_back(int2{np > 1 ? parts[p + 1] : n, 0});
-        lane[p].resize(lane[p].size() + lanes, int2{-1, 1 << 16});
+        lane[p].resize(lane[p].size() + lanes, kIdleLane);
       }
       pl.blk.insert(pl.blk.end(), blk[p].begin(), blk[p].end());
       pl.lane.insert(pl.lane.end(), lane[p].begin(), lane[p].end());
@@ -85,14 +87,68 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
   return ResPlanHost{};
 }
 
+// The same for colour-serial sweeps, whose workgroups each take a share of
+// every class (all of them work on the class being swept): rows in order inside
+// a class, so that the shares of a workgroup lie near each other in a grid.
+ResPlanHost plan_resident_serial(const std::vector<int32_t>& op, int32_t n, int K, int lanes, int max_blocks,
+                                 const std::vector<int32_t>& classes) {
+  auto chain = [&](int32_t r) { return std::max(1, (op[r + 1] - op[r] + K - 1) / K); };
+  const int ncls = (int)classes.size() - 1;
+  std::vector<int64_t> total(ncls, 0);
+  int64_t all = 0;
+  for (int q = 0; q < ncls; ++q)
+    for (int32_t r = classes[q]; r < classes[q + 1]; ++r) {
+      if (chain(r) > 64) return ResPlanHost{};
+      total[q] += chain(r);
+    }
+  for (int64_t v : total) all += v;
+  int64_t nb = std::max<int64_t>(1, (all + lanes - 1) / lanes);
+  if (lanes > 256) nb = std::max<int64_t>(nb, max_blocks);
+  for (; nb <= max_blocks; nb += std::max<int64_t>(1, nb / 16)) {
+    ResPlanHost pl;
+    pl.K = K;
+    pl.lanes = lanes;
+    std::vector<int32_t> at(classes.begin(), classes.end() - 1);  // next row of every class
+    std::vector<int64_t> done(ncls, 0);
+    bool fits = true;
+    for (int64_t b = 0; fits && b < nb; ++b) {
+      std::vector<int2> ll;
+      int32_t rows = 0;
+      for (int q = 0; q < ncls; ++q) {
+        pl.cls_tab.push_back(int2{at[q], rows});
+        const int64_t end = total[q] * (b + 1) / nb;
+        while (at[q] < classes[q + 1] && (b == nb - 1 || done[q] < end)) {
+          const int32_t r = at[q]++;
+          const int len = chain(r);
+          if (ll.size() % 64 + len > 64) ll.resize((ll.size() + 63) / 64 * 64, kIdleLane);
+          for (int k = 0; k < len; ++k) ll.push_back(int2{r, k | (len << 8) | (q << 16)});
+          done[q] += len;
+          ++rows;
+        }
+      }
+      pl.cls_tab.push_back(int2{n, rows});
+      fits = (int64_t)ll.size() <= lanes;
+      ll.resize(lanes, kIdleLane);
+      pl.lane.insert(pl.lane.end(), ll.begin(), ll.end());
+      pl.blk.push_back(int2{0, rows});
+      pl.rows_cap = std::max(pl.rows_cap, rows);
+    }
+    if (fits) return pl;
+  }
+  return ResPlanHost{};
+}
+
 namespace {
 
 template <int LANES, int K>
 ResKernel kernel64(int mode) {
   if constexpr (K == 4) {
+    if (mode == kResSerial) return k_resident<double, LANES, 4, kResSerial>;
     return mode == kResFrozen ? k_resident<double, LANES, 4, kResFrozen> : k_resident<double, LANES, 4, kResJoint>;
   } else {
     switch (mode) {
+      case kResSerial: return k_resident<double, LANES, K, kResSerial>;
+      case kResSerialOuter: return k_resident<double, LANES, K, kResSerialOuter>;
       case kResFrozen: return k_resident<double, LANES, K, kResFrozen>;
       case kResOuter: return k_resident<double, LANES, K, kResOuter>;
       case kResLoop: return k_resident<double, LANES, K, kResLoop>;
@@ -121,10 +177,17 @@ uint32_t lds_bytes(const Ctx* c, int rows_cap, int lanes, int K, int mode) {
 // The mode of a handle's first solve, or -1 where an option asks for a step
 // between the sweeps or for another layout.
 int handle_mode(const Ctx* c) {
-  constexpr int32_t kOther = GABP_FLAG_MULTI_LAUNCH | GABP_FLAG_TIME_SWEEPS | GABP_FLAG_POISON_STALE |
-                             GABP_FLAG_PREDICT_ALL | GABP_FLAG_AITKEN | GABP_FLAG_STEFFENSEN;
-  if ((c->opts.flags & kOther) || (c->opts.layout != 0 && c->opts.layout != kLayoutCompact)) return -1;
+  const bool serial = c->opts.layout == kLayoutSerial;
+  constexpr int32_t kOtherSerial = GABP_FLAG_MULTI_LAUNCH | GABP_FLAG_TIME_SWEEPS;
+  constexpr int32_t kOtherSync = GABP_FLAG_POISON_STALE | GABP_FLAG_PREDICT_ALL | GABP_FLAG_AITKEN | GABP_FLAG_STEFFENSEN;
+  const int32_t kOther = kOtherSerial | (serial ? 0 : kOtherSync);
+  if ((c->opts.flags & kOther) || (c->opts.layout != 0 && c->opts.layout != kLayoutCompact && !serial)) return -1;
   const bool fp32 = c->opts.precision == GABP_FP32_REFINE;
+  if (serial) {
+    if (c->ncol < 1 || c->ncol > 0x7fff || (c->opts.flags & GABP_FLAG_SINGLE_LOOP) || c->opts.inner_max_iter < 1)
+      return -1;
+    return !fp32 && c->gamma_used == 0.0 && c->opts.gamma == 0.0 ? kResSerial : kResSerialOuter;
+  }
   if (!fp32 && c->gamma_used == 0.0 && c->opts.gamma == 0.0) return kResJoint;
   const bool single = (c->opts.flags & GABP_FLAG_SINGLE_LOOP) != 0;
   if (single && !fp32) return kResLoop;
@@ -154,19 +217,22 @@ gabp_status setup_resident(Ctx* c) {
   GABP_HIP(c, hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
   int K = 6;
   if (mode == kResOuterLoop && fp32) K = 8;
-  else if (c->max_degree <= 4 && (fp32 || mode == kResJoint)) K = 4;
+  else if (c->max_degree <= 4 && (fp32 || mode == kResJoint || mode == kResSerial)) K = 4;
   else if (c->max_degree > 6 && fp32) K = 8;
   const int max_blocks = std::min(ncu, kResMaxBlocks);
   // rows whose chains the lanes can hold, before the plan walks them
   if (c->max_degree > kResMaxChain * K || c->n > (int64_t)max_blocks * kRL ||
       c->E > (int64_t)max_blocks * kRL * K)
     return GABP_OK;
+  const bool serial = mode == kResSerial || mode == kResSerialOuter;
   const std::vector<int32_t> none;
   ResPlanHost pl;
   for (int blocks : {1, max_blocks})
     for (int lanes : {256, 512, kRL}) {
       if (!pl.blk.empty() || c->E > (int64_t)blocks * lanes * K || c->n > (int64_t)blocks * lanes) continue;
-      pl = plan_resident(c->off_ptr_h, c->n, K, lanes, blocks, blocks == 1 || c->nparts == 0 ? none : c->part_start);
+      pl = serial ? plan_resident_serial(c->off_ptr_h, c->n, K, lanes, blocks, c->colour_start)
+                  : plan_resident(c->off_ptr_h, c->n, K, lanes, blocks,
+                                  blocks == 1 || c->nparts == 0 ? none : c->part_start);
     }
   if (pl.blk.empty()) return GABP_OK;
   for (int m : {mode, (int)kResFrozen}) {
@@ -178,11 +244,16 @@ gabp_status setup_resident(Ctx* c) {
     GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, pl.lanes, lds));
     if ((int64_t)per * ncu < (int64_t)pl.blk.size()) return GABP_OK;
   }
-  // one allocation: control blocks (zero), workgroups, lanes
-  const size_t nblk = pl.blk.size(), head = 2 * sizeof(ResCtl) + sizeof(int2) * nblk;
-  std::vector<unsigned char> img(head + sizeof(int2) * pl.lane.size(), 0);
+  // one allocation: control blocks (zero), workgroups, lanes, class tables
+  const size_t nblk = pl.blk.size(), o_lane = 2 * sizeof(ResCtl) + sizeof(int2) * nblk;
+  const size_t o_tab = o_lane + sizeof(int2) * pl.lane.size(), o_cls = o_tab + sizeof(int2) * pl.cls_tab.size();
+  std::vector<unsigned char> img(o_cls + (serial ? sizeof(int32_t) * c->colour_start.size() : 0), 0);
   std::memcpy(img.data() + 2 * sizeof(ResCtl), pl.blk.data(), sizeof(int2) * nblk);
-  std::memcpy(img.data() + head, pl.lane.data(), sizeof(int2) * pl.lane.size());
+  std::memcpy(img.data() + o_lane, pl.lane.data(), sizeof(int2) * pl.lane.size());
+  if (serial) {
+    std::memcpy(img.data() + o_tab, pl.cls_tab.data(), sizeof(int2) * pl.cls_tab.size());
+    std::memcpy(img.data() + o_cls, c->colour_start.data(), sizeof(int32_t) * c->colour_start.size());
+  }
   void* base = nullptr;
   const gabp_status r = dev_alloc(c, &base, img.size());
   if (r != GABP_OK) return r;
@@ -195,7 +266,9 @@ gabp_status setup_resident(Ctx* c) {
   c->res.rows_cap = pl.rows_cap;
   c->res.ctl_d = (ResCtl*)base;
   c->res.blk_d = (int2*)((char*)base + 2 * sizeof(ResCtl));
-  c->res.lane_d = (int2*)((char*)base + head);
+  c->res.lane_d = (int2*)((char*)base + o_lane);
+  c->res.cls_tab_d = (int2*)((char*)base + o_tab);
+  c->res.cls_start_d = (int32_t*)((char*)base + o_cls);
   c->res.khz = khz;
   return GABP_OK;
 }
@@ -218,6 +291,9 @@ hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s) 
   a.st = c->st_small_d;
   a.blk = p.blk_d;
   a.lane = p.lane_d;
+  a.ncls = c->ncol;
+  a.cls_start = p.cls_start_d;
+  a.cls_tab = p.cls_tab_d;
   a.rows_cap = p.rows_cap;
   a.ctl = p.ctl_d + p.phase;
   a.ctl_next = p.ctl_d + (p.phase ^ 1);

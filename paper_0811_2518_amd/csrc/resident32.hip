@@ -9,6 +9,10 @@ namespace {
 template <int LANES>
 ResKernel kernel32(int K, int mode) {
   if (mode == kResOuterLoop) return k_resident<float, LANES, 8, kResOuterLoop>;
+  if (mode == kResSerialOuter) {
+    if (K == 4) return k_resident<float, LANES, 4, kResSerialOuter>;
+    return K == 6 ? k_resident<float, LANES, 6, kResSerialOuter> : k_resident<float, LANES, 8, kResSerialOuter>;
+  }
   if (mode == kResRefine) {
     if (K == 4) return k_resident<float, LANES, 4, kResRefine>;
     return K == 6 ? k_resident<float, LANES, 6, kResRefine> : k_resident<float, LANES, 8, kResRefine>;

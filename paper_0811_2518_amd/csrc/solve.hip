@@ -915,7 +915,9 @@ gabp_status solve_plain(Ctx* c, const double* b, double* x, double* var, double 
 gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, double tol, int32_t max_iter,
                            gabp_info* info, bool* ran) {
   *ran = false;
-  if (c->res.nb <= 0 || c->layout != kLayoutCompact) return GABP_OK;
+  if (c->res.nb <= 0) return GABP_OK;
+  const bool serial = c->layout == kLayoutSerial;
+  if (serial && max_iter < 1) return GABP_OK;  // the prior alone
   hipStream_t s = c->stream;
   const bool exact = tol <= 0.0;
   const bool fp32 = c->opts.precision == GABP_FP32_REFINE;
@@ -925,7 +927,7 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
   const bool outer = !plain && !loop;
   const bool reuse = (c->opts.flags & GABP_FLAG_REUSE_PRECISION) != 0;
   const bool honly = plain && reuse && c->frozen_valid && c->frozen_prec == GABP_FP64 && !exact;
-  if (plain && !honly && (small_fits(c->n, c->E) || small_rows_fit(c->n, c->max_degree))) return GABP_OK;
+  if (plain && !serial && !honly && (small_fits(c->n, c->E) || small_rows_fit(c->n, c->max_degree))) return GABP_OK;
   ResArgs a{};
   a.diag = fp32 ? (const void*)c->din32_d : (const void*)c->din64_d;
   a.chk_diag = fp32 ? (const void*)(c->d32_d ? c->d32_d : c->din32_d) : (const void*)c->d64_d;
@@ -935,7 +937,7 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
   a.max_iter = max_iter;
   a.x = x;
   a.var = var;
-  if (plain && !honly && (exact || reuse)) {  // read later by gabp_messages or the freeze
+  if (plain && !serial && !honly && (exact || reuse)) {  // read later by gabp_messages or the freeze
     a.cin_out = c->bstate_d;
     for (int q = 0; q < 3; ++q) a.agg_out[q] = c->agg_d[q];
   }
@@ -986,7 +988,7 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
     report_timing(c, info);
   }
   c->last_msg_round = (plain && exact && r == GABP_OK) ? max_iter : -1;
-  if (plain && r == GABP_OK && !exact && !honly && reuse) {
+  if (plain && !serial && r == GABP_OK && !exact && !honly && reuse) {
     r = freeze<double>(c, held_round(c, st.conv_round, max_iter), c->din64_d, b, GABP_FP64);
     if (r != GABP_OK) return r;
     GABP_HIP(c, hipStreamSynchronize(s));
@@ -1281,11 +1283,11 @@ gabp_status autotune(Ctx* c) {
   std::vector<int> layouts, Ks;
   const int req = layout_request(c);
   if (c->res.nb > 0) {  // sweeps run in the resident launch: nothing to time
-    int l = kLayoutCompact, k = epb ? epb / kBlock : 2;
+    int l = req == kLayoutSerial ? kLayoutSerial : kLayoutCompact, k = epb ? epb / kBlock : 2;
     const std::string key = tune_key(c) + "-resident";
     const char* path = std::getenv("GABP_AUTOTUNE_CACHE");
     if (path && *path && c->E >= 200000 && !cache_lookup(path, key, &l, &k)) cache_store(path, key, l, k, "");
-    c->layout = kLayoutCompact;
+    c->layout = req == kLayoutSerial ? kLayoutSerial : kLayoutCompact;
     return set_partition(c, epb ? epb / kBlock : k);
   }
   if (req) layouts.push_back(req);

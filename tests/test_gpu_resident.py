@@ -210,3 +210,41 @@ def test_loading_errors_are_reported_alike():
     assert s1["status"] == s2["status"] < 0
     x, info = one.solve(torch.zeros(p.n, dtype=torch.float64, device=DEV), tol=1e-9, max_iter=50)
     assert info["converged"] == 1 and float(x.abs().max()) == 0.0
+
+
+SERIAL = ["grid_33x32", "grid_181x173", "grid3d_11", "grid3d_64", "er_3001", "er_60000", "er_isolated", "star_96", "tree"]
+
+
+@pytest.mark.parametrize("name", SERIAL)
+@pytest.mark.parametrize("check_every", [1, 3])
+def test_serial_sweeps_bitwise(name, check_every):
+    p = CASES[name]()
+    one, multi = (g.Solver(p.row_ptr, p.col, p.val, device=DEV, layout="serial", check_every=check_every, **kw)
+                  for kw in ({}, {"multi_launch": True}))
+    b = dev(p.b)
+    for tol, M in ((0, 0), (0, 1), (0, 2), (0, 7), (1e-10, 0), (1e-10, 1), (1e-300, 6), (1e-300, 7), (0.5, 5),
+                   (1e-10, 3000)):
+        x1, i1, v1 = one.solve(b, tol=tol, max_iter=M, var=True, check=False)
+        x2, i2, v2 = multi.solve(b, tol=tol, max_iter=M, var=True, check=False)
+        same_info(i1, i2)
+        assert torch.equal(x1, x2) and torch.equal(v1, v2), (name, tol, M)
+    assert i1["converged"] == 1
+    g1, gv1, j1 = one.backward(x1, b, tol=1e-12)
+    g2, gv2, j2 = multi.backward(x2, b, tol=1e-12)
+    assert torch.equal(g1, g2) and torch.equal(gv1, gv2) and j1["sweeps"] == j2["sweeps"]
+
+
+@pytest.mark.parametrize("name", ["grid_33x32", "grid3d_24", "er_3001", "btb"])
+def test_serial_refinement_and_loading_bitwise(name):
+    if name == "btb":
+        p, kw = workloads.config5(n=1500, rows=3000), {"gamma": -1.0, "inner_tol": 1e-2, "max_outer": 5000}
+    else:
+        p, kw = OUTER.get(name, CASES.get(name))(), {}
+    for prec in ("fp32", "fp64") if name == "btb" else ("fp32",):
+        for extra in ({}, {"inner_max_iter": 3}):
+            one, multi = (g.Solver(p.row_ptr, p.col, p.val, device=DEV, layout="serial", precision=prec,
+                                   **dict(kw, max_outer=5000), **extra, **m) for m in ({}, {"multi_launch": True}))
+            x1, i1 = one.solve(dev(p.b), tol=1e-9, max_iter=200000)
+            x2, i2 = multi.solve(dev(p.b), tol=1e-9, max_iter=200000)
+            same_info(i1, i2)
+            assert i1["outer_iters"] == i2["outer_iters"] and torch.equal(x1, x2), (prec, extra)
