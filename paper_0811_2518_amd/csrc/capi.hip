@@ -86,7 +86,7 @@ gabp_status alloc_solver(Ctx* c) {
   const bool fp32 = c->opts.precision == GABP_FP32_REFINE;
   const size_t elt = fp32 ? sizeof(float) : sizeof(double);
   const bool serial = c->opts.layout == kLayoutSerial;
-  const bool edge = !serial && !node_family(c->opts.layout);
+  const bool edge = !serial && !node_family(c->opts.layout) && c->res.nb == 0;
   const bool node = !serial && c->opts.layout != kLayoutEdge;
   if (node)
     for (int i = 0; i < 3; ++i) TRY(dev_alloc(c, &c->agg_d[i], 2 * elt * n));
@@ -260,8 +260,13 @@ gabp_status gabp_create(int32_t n, const int32_t* row_ptr, const int32_t* col_id
   if (r == GABP_OK && n > 0) r = ingest(c, row_ptr, col_idx, vals, nullptr, 0);
   if (r == GABP_OK && n > 0 && c->opts.layout == kLayoutSerial) r = apply_colour_order(c, nullptr, 0);
   else if (r == GABP_OK && n > 0 && !(c->opts.flags & GABP_FLAG_NATURAL_ORDER)) r = apply_xcd_order(c);
+  // the resident plan first where the loading is known: the buffers of the
+  // layouts that it rules out are then never allocated
+  const bool known = c->opts.gamma >= 0.0;
+  if (known) c->gamma_used = c->opts.gamma;
+  if (r == GABP_OK && n > 0 && known) r = setup_resident(c);
   if (r == GABP_OK && n > 0) r = alloc_solver(c);
-  if (r == GABP_OK && n > 0) r = setup_resident(c);
+  if (r == GABP_OK && n > 0 && !known) r = setup_resident(c);
   if (r == GABP_OK && n > 0) r = autotune(c);
   if (r == GABP_OK && n > 0) release_unused_layout(c);
   if (r == GABP_OK) {

@@ -14,7 +14,13 @@ static const int2 kIdleLane{-1, 1 << 8};
 // part gets the same number).  Empty when the system does not fit.
 ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int lanes, int max_blocks,
                           const std::vector<int32_t>& parts) {
-  auto chain = [&](int32_t r) { return std::max(1, (op[r + 1] - op[r] + K - 1) / K); };
+  std::vector<uint8_t> len_of(n);  // lanes of a row
+  for (int32_t r = 0; r < n; ++r) {
+    const int32_t d = op[r + 1] - op[r];
+    const int len = d <= K ? 1 : (d + K - 1) / K;
+    if (len > 64) return ResPlanHost{};
+    len_of[r] = (uint8_t)len;
+  }
   const size_t np = parts.size() > 1 ? parts.size() - 1 : 1;
   // a part's lanes in order, a chain padded to the next wave where it would
   // cross a wave's end
@@ -22,8 +28,7 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
   for (size_t p = 0; p < np; ++p) {
     int64_t total = 0;
     for (int32_t r = np > 1 ? parts[p] : 0; r < (np > 1 ? parts[p + 1] : n); ++r) {
-      const int len = chain(r);
-      if (len > 64) return ResPlanHost{};
+      const int len = len_of[r];
       if (total % 64 + len > 64) total += 64 - total % 64;
       total += len;
     }
@@ -41,31 +46,27 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
     std::vector<std::vector<int2>> blk(np), lane(np);  // {first row, rows} of every workgroup of a part
     for (size_t p = 0; p < np; ++p) {
       const int32_t lo = np > 1 ? parts[p] : 0, hi = np > 1 ? parts[p + 1] : n;
+      std::vector<int2>& ll = lane[p];
+      size_t base = 0;  // first lane of the workgroup being filled
       int used = 0;
       int2 cur{lo, 0};
-      std::vector<int2> ll;
-      auto close = [&](int32_t next) {
-        ll.resize(lanes, kIdleLane);
-        lane[p].insert(lane[p].end(), ll.begin(), ll.end());
-        blk[p].push_back(cur);
-        ll.clear();
-        cur = int2{next, 0};
-        used = 0;
-      };
+      ll.assign(lanes, kIdleLane);
       for (int32_t r = lo; r < hi; ++r) {
-        const int len = chain(r);
+        const int len = len_of[r];
         int at = used;
         if (at % 64 + len > 64) at += 64 - at % 64;
-        if (at + len > per * 64) {
-          close(r);
+        if (at + len > per * 64) {  // the row starts the next workgroup
+          blk[p].push_back(cur);
+          cur = int2{r, 0};
+          base += lanes;
+          ll.resize(base + lanes, kIdleLane);
           at = 0;
         }
-        ll.resize(at, kIdleLane);
-        for (int q = 0; q < len; ++q) ll.push_back(int2{r, q | (len << 8)});
+        for (int q = 0; q < len; ++q) ll[base + at + q] = int2{r, q | (len << 8)};
         used = at + len;
         ++cur.y;
       }
-      if (cur.y > 0 || blk[p].empty()) close(hi);
+      blk[p].push_back(cur);
     }
     size_t q = 0;
     for (auto& v : blk) q = std::max(q, v.size());
