@@ -244,6 +244,7 @@ struct SmallArgs {
   int32_t E;
   const int32_t* off_ptr;   // [n+1] off-diagonal CSR
   const int32_t* col;       // [E]
+  const int32_t* rev;       // [E] mirror slots
   const double* a;          // [E]
   const double* diag;       // [n]
   const double* rhs;        // [n]
@@ -257,17 +258,13 @@ struct SmallArgs {
   double* x_direct;         // nullable: x of the returned round
   double* var_direct;       // nullable: 1 / P~ of the returned round
   void* cin_out;            // nullable: [2][E] {P, h} incoming messages by round parity
-  void* agg_out[3];         // nullable: [n] {P~, h~} aggregates by round mod 3
-  const int32_t* gate;      // nullable: nonzero -> the kernel returns at once
-  const int32_t* E_dev;     // nullable: E read on the device (then E is ignored)
-  int32_t max_deg;          // largest row of the off-diagonal CSR (0: not known on the host)
+  void* agg_out[3];         // nullable: [n] {P~, h~} aggregates by round mod 3 (the last two rounds)
+  int32_t max_deg;          // largest row of the off-diagonal CSR
 };
 bool small_fits(int64_t n, int64_t E);
 // rows of at most 6 slots: a lane per row, any E
 bool small_rows_fit(int64_t n, int32_t max_deg);
 hipError_t launch_small(const SmallArgs& a, hipStream_t s);
-// the same with K = 4 slots per lane (E <= 4096, also when E lives on the device)
-hipError_t launch_small_k4(const SmallArgs& a, hipStream_t s);
 
 // Resident solve of a mid-sized system (resident.hip): one workgroup per CU,
 // messages in registers, all sweeps in one launch.

@@ -3,17 +3,21 @@
 // memory (code under stream capture, tight serving loops, harnesses that
 // forbid allocation).
 //
-// Everything the call needs beyond the caller's inputs and outputs lives in
-// one file-scope device array, `scratch`: the validation flags, the off-
-// diagonal CSR split from the caller's full CSR (Alg. 2's neighbourhoods
-// N(i), Ch. 3 Sec. 3.3) with the diagonal, the size E, and the solver status.
-// The solve itself is the one-workgroup kernel of small.hip, whose messages
-// stay in registers and aggregates in LDS.  Two launches (validate and split,
-// then solve) and one copy of the status back to the host; no hipMalloc,
-// hipFree or allocating library call.  Each device holds its own copy of the
-// array; its address is looked up once per device with
-// hipGetSymbolAddress and kept.  Calls that overlap on one device share that
-// array and race.
+// One launch of one workgroup validates the caller's full CSR, splits it into
+// the off-diagonal CSR of Alg. 2's neighbourhoods N(i) (Ch. 3 Sec. 3.3) and the
+// diagonal, and runs the sweeps of small.h, all of it in LDS and registers;
+// then one copy brings the status back to the host.  No hipMalloc, hipFree or
+// allocating library call.  The status and the validation flags are the only
+// device memory beyond the caller's inputs and outputs: one file-scope array,
+// `scratch`, of which each device holds its own copy; its address is looked up
+// once per device with hipGetSymbolAddress and kept.  Calls that overlap on
+// one device share that array and race.
+//
+// What bounds a call is latency: the launch, the round trip for the inputs, the
+// sweeps (small.h) and the copy.  As two launches that walked the rows and
+// searched the mirror entries in global memory, and sweeps of two divisions a
+// slot, a solve of G(600, 1800) to 1e-10 took 191 us; now 116 us (about 40 us of
+// it outside the sweeps, before 60).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -21,7 +25,9 @@
 #include <mutex>
 #include <string>
 
-#include "gabp_internal.h"
+#include "small.h"
+
+#pragma clang fp contract(off)
 
 namespace gabp {
 
@@ -37,111 +43,144 @@ constexpr int kNaNonfinite = 8;
 constexpr int kNaTooLarge = 16;
 
 struct NaHeader {
-  DevStatus st;        // written by the solve kernel
-  int32_t flags;       // kNa* bits of the validation
-  int32_t gate;        // nonzero: the solve kernel returns at once
-  int32_t E;           // off-diagonal entries
+  DevStatus st;   // of the sweeps, where the validation passed
+  int32_t flags;  // kNa* bits of the validation
   int32_t pad;
 };
 
-struct NaScratch {
-  NaHeader h;
-  int32_t off_ptr[kNaRows + 1];
-  int32_t off_col[kNaSlots];
-  double a[kNaSlots];
-  double d[kNaRows];
-};
+constexpr size_t kScratchBytes = (sizeof(NaHeader) + 255) / 256 * 256;
 
-constexpr size_t kScratchBytes = (sizeof(NaScratch) + 255) / 256 * 256;
+// First of the slots lo .. hi - 1 (sorted by column) whose column is not below r.
+template <typename Col>
+__device__ __forceinline__ int find_slot(int lo, int hi, int r, Col col_of) {
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (col_of(mid) < r) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
 
-// Validation of the caller's full CSR (the checks of gabp_create) and the
-// split into the off-diagonal CSR and the diagonal, by one workgroup: lane r
-// takes row r.  The symmetry check runs only on a sound structure, so every
-// search stays inside the split arrays.
-__global__ __launch_bounds__(kNaRows) void k_na_ingest(int32_t n, const int32_t* __restrict__ row_ptr,
-                                                        const int32_t* __restrict__ col,
-                                                        const double* __restrict__ vals, NaScratch* sc) {
+// Validation of the caller's full CSR (the checks of gabp_create), the split,
+// and the solve.  The caller's CSR is staged in LDS (coalesced, one round trip);
+// lane r then walks row r there, and the slot lanes look up their mirror slots
+// for the symmetry check, which runs only on a sound structure, so every search
+// stays inside the split arrays.
+__global__ __launch_bounds__(kNaRows) void k_noalloc(int32_t n, const int32_t* __restrict__ row_ptr,
+                                                     const int32_t* __restrict__ col,
+                                                     const double* __restrict__ vals, SmallArgs A, NaHeader* out) {
+  constexpr int K = kNaSlots / kNaRows, S = kNaSlots, N = kNaRows;
+  extern __shared__ __align__(16) double sm[];
   __shared__ int s_flags;
   __shared__ unsigned long long s_max;
-  __shared__ int s_nnz;
-  const int r = threadIdx.x;
-  if (r == 0) {
-    const int nnz = row_ptr[n];
-    int f = 0;
-    if (row_ptr[0] != 0 || nnz < n) f |= kNaArg;
-    else if ((int64_t)nnz - n > kNaSlots) f |= kNaTooLarge;
-    s_flags = f;
+  __shared__ int s_bad[3];
+  const int tid = threadIdx.x, lane = tid & 63;
+  // the caller's CSR, in what will hold the messages (S + N entries of 12 bytes in 16 S)
+  static_assert(3 * (S + N) <= 4 * S, "the staged CSR fits in the message buffer");
+  double* s_val = sm;                       // [S + N]
+  int* s_col = (int*)(sm + S + N);          // [S + N]
+  // the split, in what will hold the a x terms, the aggregates and the means
+  double* s_a = sm + 2 * S;                 // [S]
+  uint32_t* s_rc = (uint32_t*)(sm + 3 * S); // [S] row and column, packed
+  int* s_ptr = (int*)(s_rc + S);            // [N + 1]
+  static_assert(4 * S + 4 * (N + 1) <= 24 * N, "the split fits in the rows' part");
+  const int nnz = row_ptr[n];
+  // the caller's arrays are read only where their size makes sense
+  const int size_flag = row_ptr[0] != 0 || nnz < n ? kNaArg : (int64_t)nnz - n > kNaSlots ? kNaTooLarge : 0;
+  if (size_flag) {
+    if (tid == 0) out->flags = size_flag;
+    return;
+  }
+  if (tid == 0) {
+    s_flags = 0;
     s_max = 0ull;
-    s_nnz = nnz;
+  }
+  if (tid < 3) s_bad[tid] = 0;
+  const int E = nnz - n;
+  int lo = 0, hi = 0;
+  double br = 0.0;
+  if (tid < n) {
+    lo = row_ptr[tid];
+    hi = row_ptr[tid + 1];
+    br = A.rhs[tid];
+  }
+  for (int e = tid; e < nnz; e += kNaRows) {
+    s_col[e] = col[e];
+    s_val[e] = vals[e];
   }
   __syncthreads();
-  const int nnz = s_nnz;
   int flags = 0;
-  double maxabs = 0.0;
-  if (r < n && s_flags == 0) {
-    int lo = row_ptr[r], hi = row_ptr[r + 1];
+  double maxabs = 0.0, dv = 0.0;
+  if (tid < n) {
     if (lo < 0 || hi > nnz || hi < lo) {  // never read outside col / vals
       flags |= kNaArg;
       lo = hi = 0;
     }
     int prev = -1, ndiag = 0;
-    double dv = 0.0;
-    int k = lo - r;  // off-diagonal slot of the row's next off-diagonal entry
+    int k = lo - tid;  // off-diagonal slot of the row's next off-diagonal entry
     for (int e = lo; e < hi; ++e) {
-      const int c = col[e];
-      const double v = vals[e];
+      const int c = s_col[e];
+      const double v = s_val[e];
       if (c < 0 || c >= n || c <= prev) flags |= kNaArg;
       prev = c;
       if (!isfinite(v)) flags |= kNaNonfinite;
       maxabs = fmax(maxabs, fabs(v));
-      if (c == r) {
+      if (c == tid) {
         ++ndiag;
         dv = v;
       } else {
         if (k >= 0 && k < kNaSlots) {
-          sc->off_col[k] = c;
-          sc->a[k] = v;
+          s_rc[k] = pack_slot(tid, c & 1023);
+          s_a[k] = v;
         }
         ++k;
       }
     }
     if (ndiag != 1 || dv == 0.0) flags |= kNaZeroDiag;
-    sc->d[r] = dv;
-    sc->off_ptr[r] = lo - r;
-    if (r == n - 1) sc->off_ptr[n] = hi - n;
+    s_ptr[tid] = lo - tid;
+    if (tid == n - 1) s_ptr[n] = hi - n;
   }
   if (flags) atomicOr(&s_flags, flags);
-  if (isfinite(maxabs) && maxabs > 0.0) atomicMax(&s_max, (unsigned long long)__double_as_longlong(maxabs));
+  if (!isfinite(maxabs)) maxabs = 0.0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) maxabs = fmax(maxabs, __shfl_xor(maxabs, off, 64));
+  if (lane == 0 && maxabs > 0.0) atomicMax(&s_max, (unsigned long long)__double_as_longlong(maxabs));
   __syncthreads();
-  if (s_flags == 0 && r < n) {
-    // |A_ij - A_ji| <= 1e-12 max|A| and the mirror entry present: binary search
-    // for column r in row c of the split arrays
-    const double tolv = 1e-12 * __longlong_as_double((long long)s_max);
-    int asym = 0;
-    for (int s = sc->off_ptr[r]; s < sc->off_ptr[r + 1]; ++s) {
-      const int c = sc->off_col[s];
-      int lo = sc->off_ptr[c], hi = sc->off_ptr[c + 1] - 1, found = -1;
-      while (lo <= hi) {
-        const int mid = (lo + hi) >> 1;
-        const int v = sc->off_col[mid];
-        if (v == r) {
-          found = mid;
-          break;
-        }
-        if (v < r) lo = mid + 1;
-        else hi = mid - 1;
+  if (s_flags) {
+    if (tid == 0) out->flags = s_flags;
+    return;
+  }
+  // |A_ij - A_ji| <= 1e-12 max|A| and the mirror entry present
+  const double tolv = 1e-12 * __longlong_as_double((long long)s_max);
+  uint32_t meta[K];
+  double aa[K], am[K];
+  int asym = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int s = tid + k * kNaRows;
+    meta[k] = (uint32_t)s << 20;
+    aa[k] = am[k] = 0.0;
+    if (s < E) {
+      const uint32_t rc = s_rc[s];
+      const int r = slot_row(rc), c = slot_col(rc);
+      aa[k] = s_a[s];
+      const int end = s_ptr[c + 1];
+      const int m = find_slot(s_ptr[c], end, r, [&](int q) { return slot_col(s_rc[q]); });
+      if (m < end && slot_col(s_rc[m]) == r) {
+        am[k] = s_a[m];
+        meta[k] = rc | ((uint32_t)m << 20);
+        if (fabs(aa[k] - am[k]) > tolv) asym = 1;
+      } else {
+        asym = 1;
       }
-      if (found < 0 || fabs(sc->a[s] - sc->a[found]) > tolv) asym = 1;
     }
-    if (asym) atomicOr(&s_flags, kNaAsym);
   }
-  __syncthreads();
-  if (r == 0) {
-    sc->h.flags = s_flags;
-    sc->h.gate = s_flags != 0;
-    sc->h.E = s_flags ? 0 : nnz - n;
-    sc->h.pad = 0;
+  if (__syncthreads_or(asym)) {
+    if (tid == 0) out->flags = kNaAsym;
+    return;
   }
+  if (tid == 0) out->flags = 0;
+  small_loop<K, false>(A, n, E, sm, s_bad, meta, aa, am, lo - tid, hi - tid - 1, tid < n ? dv : 1.0, br);
 }
 
 }  // namespace
@@ -163,7 +202,7 @@ void* g_scratch_ptr[kMaxDevices] = {};
 
 // Device address of `scratch` on the current device, looked up on the first
 // call made with that device current.
-gabp_status scratch_on_current_device(NaScratch** out) {
+gabp_status scratch_on_current_device(NaHeader** out) {
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(nullptr, GABP_E_HIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
@@ -178,7 +217,7 @@ gabp_status scratch_on_current_device(NaScratch** out) {
     }
     g_scratch_ptr[dev] = p;
   }
-  *out = (NaScratch*)g_scratch_ptr[dev];
+  *out = (NaHeader*)g_scratch_ptr[dev];
   return GABP_OK;
 }
 
@@ -203,34 +242,27 @@ extern "C" gabp_status gabp_solve_noalloc(int32_t n, const int32_t* row_ptr, con
     return GABP_OK;
   }
   if (!row_ptr || !col_idx || !vals || !b || !x) return fail(nullptr, GABP_E_ARG, "NULL argument");
-  NaScratch* sc = nullptr;
+  NaHeader* sc = nullptr;
   gabp_status r = scratch_on_current_device(&sc);
   if (r != GABP_OK) return r;
 
-  hipLaunchKernelGGL(k_na_ingest, dim3(1), dim3(kNaRows), 0, stream, n, row_ptr, col_idx, vals, sc);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(nullptr, GABP_E_HIP, std::string("validation launch: ") + hipGetErrorString(e));
   SmallArgs a{};
   a.n = n;
-  a.E = 0;
-  a.E_dev = &sc->h.E;
-  a.gate = &sc->h.gate;
-  a.off_ptr = sc->off_ptr;
-  a.col = sc->off_col;
-  a.a = sc->a;
-  a.diag = sc->d;
   a.rhs = b;
-  a.rhs_norm = nullptr;
   a.tol = tol;
   a.max_iter = max_iter;
   a.check_every = 1;
-  a.st = &sc->h.st;
+  a.st = &sc->st;
   a.x_direct = x;
   a.var_direct = var;
-  e = launch_small_k4(a, stream);
+  // the split needs the LDS of the largest n
+  const uint32_t lds = (uint32_t)small_lds(kNaRows, kNaSlots / kNaRows);
+  (void)hipFuncSetAttribute((const void*)k_noalloc, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(k_noalloc, dim3(1), dim3(kNaRows), lds, stream, n, row_ptr, col_idx, vals, a, sc);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(nullptr, GABP_E_HIP, std::string("solve launch: ") + hipGetErrorString(e));
   NaHeader h{};
-  e = hipMemcpyAsync(&h, &sc->h, sizeof(h), hipMemcpyDeviceToHost, stream);
+  e = hipMemcpyAsync(&h, sc, sizeof(h), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return fail(nullptr, GABP_E_HIP, std::string("status copy: ") + hipGetErrorString(e));
 

@@ -632,6 +632,7 @@ gabp_status run_small(Ctx* c, const RunCfg& cfg, double* x, double* var) {
   a.E = (int32_t)c->E;
   a.off_ptr = c->off_ptr_d;
   a.col = c->off_col_d;
+  a.rev = c->rev_d;
   a.a = c->a64_d;
   a.diag = (const double*)cfg.diag;
   a.rhs = (const double*)cfg.rhs;
