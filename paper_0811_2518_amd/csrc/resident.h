@@ -36,10 +36,10 @@
 // roll call has succeeded every workgroup is running, so later waits end.
 //
 // Measured against a launch per sweep and its finish kernel, whole solves to
-// 1e-10: 181 x 173 grid with variances 669 -> 286 us, G(n, 4n) with n = 30011
-// on frozen precisions 350 -> 160 us, 64^3 grid forward and adjoint 6.67 ->
-// 1.94 ms (a checked mean-only sweep of its 1.5 M slots takes 6.3 us instead
-// of 24), 29 x 23 grid on frozen precisions 1004 -> 201 us in one workgroup.
+// 1e-10: 181 x 173 grid with variances 669 -> 265 us, G(n, 4n) with n = 30011
+// on frozen precisions 350 -> 154 us, 64^3 grid forward and adjoint 6.65 ->
+// 1.71 ms (a checked mean-only sweep of its 1.5 M slots takes 5.4 us instead
+// of 24), 29 x 23 grid on frozen precisions 1004 -> 196 us in one workgroup.
 // The loops of inner solves also lose the host's status reads (20-30 us each)
 // and the launches between the phases: FP32 + refinement on G(n, 4n) with n =
 // 130003 596 -> 355 us, the double loop on B^T B + 0.1 I with n = 30000 50.5 ->
@@ -111,12 +111,13 @@ __device__ __forceinline__ void st_rec(const RecBuf& b, int i, vec2<double> v) {
 }
 
 // Partial sums travel without a wait between them and the barrier arrival: the
-// low two bits of a partial's mantissa (2^-50 of its value) carry the check's
-// sequence number mod 4, and a reader waits until they match.  Two sets by the
-// number's parity: a workgroup stores check s + 1 before the barrier that says
-// every other has read check s, and check s + 2 after it.
+// low three bits of a partial's mantissa (2^-49 of its value) carry the check's
+// sequence number mod 8, and a reader waits until they match.  Four sets by the
+// number mod 4: check s is read until the barrier after the one it was sent
+// with has ended, and a workgroup stores check s + 4 after that.
+constexpr uint32_t kTagMask = 7u;
 __device__ __forceinline__ uint64_t tag_partial(double v, uint32_t seq) {
-  return (__builtin_bit_cast(uint64_t, v) & ~3ull) | (seq & 3u);
+  return (__builtin_bit_cast(uint64_t, v) & ~(uint64_t)kTagMask) | (seq & kTagMask);
 }
 
 enum GridState : int { kGo = 1, kAbort = 2 };
@@ -162,11 +163,17 @@ __device__ __forceinline__ bool grid_arrive(ResCtl* c, const GridPos& p, uint32_
   return true;
 }
 
+// The last arrival of the grid lets the others go.
+__device__ __forceinline__ void grid_release(ResCtl* c, const GridPos& p, uint32_t ep, bool any_bad) {
+  if (p.ngrp == 1) return;
+  const uint64_t word = (uint64_t)ep | (any_bad ? (1ull << 63) : 0ull);
+  for (uint32_t k = 0; k < p.ngrp; ++k) AGENT_STORE(&c->rel[k].v, word);
+}
+
 // One lane: wait for barrier `ep`: on the one counter, or on the group's
 // release word, which holds the barrier number and the flags raised before it,
 // so that every workgroup leaves it with the same answer.
-__device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t ep, bool last, bool any_bad,
-                                         uint64_t limit) {
+__device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t ep, uint64_t limit) {
   const uint64_t t0 = wall_clock64();
   if (p.ngrp == 1) {
     for (;;) {
@@ -175,9 +182,6 @@ __device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t e
       if (wall_clock64() - t0 > limit) return kWaitEnd;
     }
   }
-  const uint64_t word = (uint64_t)ep | (any_bad ? (1ull << 63) : 0ull);
-  if (last)
-    for (uint32_t k = 0; k < p.ngrp; ++k) AGENT_STORE(&c->rel[k].v, word);
   for (;;) {
     const uint64_t v = AGENT_LOAD(&c->rel[p.grp].v);
     if ((v & ~(1ull << 63)) >= ep) return (v >> 63) ? kWaitBad : kWaitOk;
@@ -221,6 +225,13 @@ constexpr bool res_outer(int mode) {
   return mode == kResOuter || mode == kResOuterLoop || mode == kResRefine || mode == kResSerialOuter;
 }
 
+// Kernels whose stop decisions may fall a sweep late (see `run`): not with 1024
+// lanes, whose 128 VGPRs the code for it overruns (64^3 grid, a checked sweep
+// 9.2 us without it, 9.7 with it).
+constexpr bool res_late(int mode, int lanes) {
+  return lanes < kRL && (mode == kResJoint || mode == kResFrozen || mode == kResLoop);
+}
+
 // LANES lanes per workgroup, one workgroup per CU: 128 VGPRs at 1024 lanes, of
 // which the FP64 messages of K slots take 8 K, so there A_ij, the neighbours
 // and the rows' prior live in LDS; with fewer lanes they stay in registers too.
@@ -229,6 +240,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   constexpr bool OUTER = res_outer(MODE);
   constexpr bool SERIAL = MODE == kResSerial || MODE == kResSerialOuter;
   constexpr bool FEED = MODE == kResLoop || MODE == kResOuterLoop;
+  constexpr bool LATE = res_late(MODE, LANES);
   constexpr bool REG = LANES < kRL;
   constexpr int NW = LANES / 64;
   using V2 = vec2<T>;
@@ -239,6 +251,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // [(t + 1) % 3], which no lane reads or sets until sweep t + 1
   __shared__ int s_bad[3];
   __shared__ int s_res;
+  __shared__ __align__(16) uint64_t s_part[kResMaxBlocks];  // a check's partials, staged for a late decision
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = A.n;
   const int nb = gridDim.x;
@@ -250,7 +263,8 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   V2* s_agg = (V2*)smem;                       // [2][cap] the workgroup's aggregates by round parity
   double* s_xo = (double*)(s_agg + 2 * cap);   // [cap] outer loop: the iterate
   T* s_x = (T*)(s_xo + (OUTER ? cap : 0));     // [2][cap] the means of the last rounds
-  double* s_a = (double*)(s_x + 2 * cap);      // 1024 lanes only: [K][lanes] A_ij of the lane's slots,
+  V2* s_o3 = (V2*)(s_x + 2 * cap);             // [cap] late decisions: the aggregates of round t-2
+  double* s_a = (double*)(s_o3 + (LATE ? cap : 0));  // 1024 lanes only: [K][lanes] A_ij of the lane's slots,
   double* s_d = s_a + K * LANES;               // [lanes] A_ii and b_i of the lane's row,
   double* s_b = s_d + LANES;
   int* s_c = (int*)(s_b + LANES);              // [K][lanes] the slots' neighbours
@@ -375,7 +389,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (wave == 0) {
       const double v = block_sum(s_red[0]);
       if (tid == 0) {
-        AGENT_STORE(&ctl->part[seq & 1][b], tag_partial(v, seq));
+        AGENT_STORE(&ctl->part[seq & 3][b], tag_partial(v, seq));
         s_res = roll_call(ctl, gp, A.roll_limit) ? 0 : 1;
       }
     }
@@ -383,38 +397,46 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (s_res) return;
   }
   bool lost = false;
-  // the sum of the workgroups' partials: formed by wave 0, read by all
+  // the sum of check q's partials, formed by wave 0 and left in s_tot: from
+  // memory, or from the copy in s_part where `staged`.  True: a wait ran out.
+  auto sum_partials = [&](const uint32_t q, const bool staged) -> bool {
+    constexpr int kPer = kResMaxBlocks / 64;
+    const uint64_t* part = ctl->part[q & 3];
+    uint64_t u[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int i = lane + 64 * j;
+      u[j] = i >= nb ? (q & kTagMask) : staged ? s_part[i] : AGENT_LOAD(&part[i]);
+    }
+    const uint64_t t0 = wall_clock64();
+    bool late = false;
+    double v = 0.0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      while ((u[j] & kTagMask) != (q & kTagMask) && !late) {
+        u[j] = AGENT_LOAD(&part[lane + 64 * j]);
+        late = wall_clock64() - t0 > A.wait_limit;
+      }
+      v += __builtin_bit_cast(double, u[j] & ~(uint64_t)kTagMask);
+    }
+    v = wsum_r(v);
+    if (lane == 0) s_tot = v;
+    return __any(late);
+  };
+  // the sum of the last check's partials (red: the waves' of one workgroup)
   auto total = [&](const double* red) -> double {
     if (nb == 1) return block_sum(red);
-    if (wave == 0) {
-      constexpr int kPer = kResMaxBlocks / 64;
-      uint64_t u[kPer];
-#pragma unroll
-      for (int j = 0; j < kPer; ++j)
-        u[j] = lane + 64 * j < nb ? AGENT_LOAD(&ctl->part[seq & 1][lane + 64 * j]) : (seq & 3u);
-      const uint64_t t0 = wall_clock64();
-      bool late = false;
-      double v = 0.0;
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        while ((u[j] & 3u) != (seq & 3u) && !late) {
-          u[j] = AGENT_LOAD(&ctl->part[seq & 1][lane + 64 * j]);
-          late = wall_clock64() - t0 > A.wait_limit;
-        }
-        v += __builtin_bit_cast(double, u[j] & ~3ull);
-      }
-      if (__any(late)) s_res = kWaitEnd;
-      v = wsum_r(v);
-      if (lane == 0) s_tot = v;
-    }
+    if (wave == 0 && sum_partials(seq, false)) s_res = kWaitEnd;
     lds_barrier_r();
     if (s_res == kWaitEnd) lost = true;
     return uni_r(s_tot);
   };
   // All workgroups: records stored before it are visible after it.  red
   // (nullable): the waves' partials of a check, sent along; flag: an LDS word,
-  // nonzero where a message was not finite.  Returns whether any was.
-  auto grid_barrier = [&](const double* red, const int* flag) -> bool {
+  // nonzero where a message was not finite.  Returns whether any was.  sum
+  // (nonzero): the check whose staged partials are added up meanwhile, into
+  // s_tot.
+  auto grid_barrier = [&](const double* red, const int* flag, const uint32_t sum = 0) -> bool {
     ++ep;
     if (nb == 1) {
       lds_barrier_r();
@@ -426,10 +448,15 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (wave == 0) {
       const double v = red ? block_sum(red) : 0.0;
       if (tid == 0) {
-        if (red) AGENT_STORE(&ctl->part[seq & 1][b], tag_partial(v, seq));
+        if (red) AGENT_STORE(&ctl->part[seq & 3][b], tag_partial(v, seq));
         bool any_bad = false;
-        const bool last = grid_arrive(ctl, gp, ep, flag && *flag, &any_bad);
-        s_res = grid_wait(ctl, gp, ep, last, any_bad, A.wait_limit);
+        // (with one counter too the answer is awaited: polling at once delays the others' arrivals)
+        if (grid_arrive(ctl, gp, ep, flag && *flag, &any_bad)) grid_release(ctl, gp, ep, any_bad);
+      }
+      const bool late = LATE && sum && sum_partials(sum, true);
+      if (tid == 0) {
+        const int r = grid_wait(ctl, gp, ep, A.wait_limit);
+        s_res = late ? (int)kWaitEnd : r;
       }
     }
     lds_barrier_r();
@@ -616,6 +643,28 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     bool pending = false;  // a check whose partials are on their way
     conv = last_round = prev_round = -1;
     err = 0;
+    // Early or late decisions.  Adding up the partials before the update makes
+    // every wave wait for one; while no stop is in sight wave 0 only stages
+    // them in LDS, adds them up while the barrier of the same sweep is under
+    // way, and the decision on round t-2 falls at the end of sweep t.  If it
+    // ends the run after all, the sweep is taken back: the aggregates of the
+    // last three rounds are at hand (not the messages, so a run that leaves its
+    // state behind decides early).  In sight: the next check would meet the
+    // tolerance with a factor of 4 to spare if the residual kept its last rate.
+    // Checked sweeps, early / late: 181 x 173 grid 4.3 / 4.0 us, on frozen
+    // precisions 3.6 / 3.3; G(n, 4n) with n = 30011 6.8 / 6.3, frozen 5.6 / 5.1;
+    // 24^3 grid 4.5 / 4.25; no gain on 16 workgroups (64 x 64 grid 3.5 / 3.55).
+    const bool may_late = LATE && nb > 1 && (HONLY || (!A.cin_out && !A.agg_out[0]));
+    bool far = false;
+    auto decide = [&](const double tot, const int round) {
+      prev_tot = last_tot;
+      prev_round = last_round;
+      last_tot = tot;
+      last_round = round;
+      if (tot <= conv_pre && rel_of(tot) <= tol) conv = round;
+      else if (!(tot < div_pre) && !(rel_of(tot) <= kDivergeLimit)) err |= kErrDiverged;
+      if (LATE) far = prev_round < 0 ? tot > 1e4 * conv_pre : tot * tot > 16.0 * conv_pre * prev_tot;
+    };
 
     // One sweep: the gathers of round t-1, then the stop decision on the check
     // that the previous sweep made (round t-2; its partials arrive while the
@@ -636,15 +685,22 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
 #pragma unroll
         for (int k = 0; k < K; ++k) g[k] = ld_rec<V2>(ODD ? buf0 : buf1, cr[k] < 0 ? kNoRec : (uint32_t)cr[k]);
       }
+      uint32_t late = 0;  // the check decided at the end of this sweep
       if (pending) {
-        const double tot = total(s_red[p1]);
-        prev_tot = last_tot;
-        prev_round = last_round;
-        last_tot = tot;
-        last_round = t - 2;
         pending = false;
-        if (tot <= conv_pre && rel_of(tot) <= tol) conv = t - 2;
-        else if (!(tot < div_pre) && !(rel_of(tot) <= kDivergeLimit)) err |= kErrDiverged;
+        if (LATE && may_late && far && live) {
+          late = seq;
+          if (wave == 0) {
+            const __amdgpu_buffer_rsrc_t r =
+                __builtin_amdgcn_make_buffer_rsrc(ctl->part, 0, (int)sizeof(ctl->part), 0x00027000);
+            const int at = (int)((seq & 3) * sizeof(ctl->part[0]));
+            for (int i = 0; i < nb; i += 128)
+              __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(s_part + i), 16,
+                                                       lane * 16, at + i * 8, 0, kAgentPolicy);
+          }
+        } else {
+          decide(total(s_red[p1]), t - 2);
+        }
       }
       if (conv >= 0 || err || lost || !live) return true;
 #pragma unroll
@@ -745,6 +801,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
           }
         }
         if (HONLY) P = ip;
+        if (LATE && late && tail) s_o3[lrow] = V2{o2P, o2h};
         o2P = o1P;
         o2h = o1h;
         o1P = P;
@@ -767,7 +824,22 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
         ++seq;
         pending = true;
       }
-      if (grid_barrier(ck ? s_red[pn] : nullptr, &s_bad[t % 3])) err |= kErrNonfinite;
+      const bool any_bad = grid_barrier(ck ? s_red[pn] : nullptr, &s_bad[t % 3], late);
+      if (LATE && late) {
+        if (lost) return true;
+        decide(uni_r(s_tot), t - 2);
+        if (conv >= 0 || err) {
+          if (upd && tail) {  // the sweep taken back
+            o1P = o2P;
+            o1h = o2h;
+            const V2 v = s_o3[lrow];
+            o2P = v.x;
+            o2h = v.y;
+          }
+          return true;
+        }
+      }
+      if (any_bad) err |= kErrNonfinite;
       return err != 0 || lost;  // a non-finite message ends the solve
     };
     for (int t = 1;; t += 2) {
@@ -957,6 +1029,7 @@ template <typename T>
 uint32_t res_lds(int rows_cap, int lanes, int K, int mode) {
   size_t b = 2 * (size_t)rows_cap * (sizeof(vec2<T>) + sizeof(T));
   if (res_outer(mode)) b += sizeof(double) * (size_t)rows_cap;
+  if (res_late(mode, lanes)) b += sizeof(vec2<T>) * (size_t)rows_cap;
   if (lanes == kRL) b += (size_t)lanes * (K * (sizeof(double) + sizeof(int)) + 2 * sizeof(double));
   return (uint32_t)b;
 }
