@@ -205,7 +205,8 @@ int handle_mode(const Ctx* c) {
 // barrier: the 29 x 23 grid's mean-only sweep takes 2.05 us in one workgroup,
 // 3.09 us in three); else as small as the CU count allows, since a sweep of few
 // waves per CU is bound by the latency of its dependent divisions and exchanges
-// (measured at 256 / 512 / 1024 lanes, checked FP64 sweeps: 181 x 173 grid 4.58
+// (measured at 256 / 512 / 1024 lanes, checked FP64 sweeps whose stop decision
+// falls before the update: 181 x 173 grid 4.58
 // / 4.93 / 5.65 us, G(n, 4n) with n = 30011 6.94 / 8.27 / 12.5 us).
 gabp_status setup_resident(Ctx* c) {
   c->res = ResPlan{};
