@@ -515,8 +515,8 @@ gabp_status gabp_plan_rows(int32_t n, const int32_t *row_ptr, const int32_t *col
  * Validation errors are those of gabp_create; solve statuses those of
  * gabp_solve.  The results equal those of gabp_create + gabp_solve bit for
  * bit.  Instead of allocating, the call uses a static device buffer of the
- * library (61.7 KB per device, held until the process ends) for the
- * validation flags, the split off-diagonal CSR and the status: calls that
+ * library (256 bytes per device, held until the process ends) for the
+ * validation flags and the status, and one launch: calls that
  * overlap on one device share that buffer and race, so serialise them.  Blocks
  * until the stream has finished the solve.  gabp_last_error(NULL) describes a
  * failure.

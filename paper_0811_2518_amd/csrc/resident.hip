@@ -50,6 +50,7 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
       size_t base = 0;  // first lane of the workgroup being filled
       int used = 0;
       int2 cur{lo, 0};
+      ll.reserve((size_t)room * lanes);  // grown a workgroup at a time
       ll.assign(lanes, kIdleLane);
       for (int32_t r = lo; r < hi; ++r) {
         const int len = len_of[r];
@@ -80,7 +81,8 @@ ResPlanHost plan_resident(const std::vector<int32_t>& op, int32_t n, int K, int 
         lane[p].resize(lane[p].size() + lanes, kIdleLane);
       }
       pl.blk.insert(pl.blk.end(), blk[p].begin(), blk[p].end());
-      pl.lane.insert(pl.lane.end(), lane[p].begin(), lane[p].end());
+      if (np == 1) pl.lane = std::move(lane[p]);
+      else pl.lane.insert(pl.lane.end(), lane[p].begin(), lane[p].end());
     }
     for (const int2& v : pl.blk) pl.rows_cap = std::max(pl.rows_cap, v.y);
     return pl;
