@@ -58,6 +58,7 @@
 #include <type_traits>
 
 #include "gabp_internal.h"
+#include "rules.h"
 #include "wave.h"
 
 #pragma clang fp contract(off)
@@ -246,7 +247,9 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   using V2 = vec2<T>;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double s_red[3][16];  // by sweep parity, then the outer residual's
-  __shared__ double s_tot;
+  // check sums by check number: the word that a late decision reads behind the
+  // sweep's last barrier is not the one that the next sum is written to
+  __shared__ double s_tot[kSumWords];
   // non-finite message flags by sweep mod 3: sweep t sets [t % 3] and clears
   // [(t + 1) % 3], which no lane reads or sets until sweep t + 1
   __shared__ int s_bad[3];
@@ -397,8 +400,9 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (s_res) return;
   }
   bool lost = false;
-  // the sum of check q's partials, formed by wave 0 and left in s_tot: from
-  // memory, or from the copy in s_part where `staged`.  True: a wait ran out.
+  // the sum of check q's partials, formed by wave 0 and left in its word of
+  // s_tot: from memory, or from the copy in s_part where `staged`.  True: a
+  // wait ran out.
   auto sum_partials = [&](const uint32_t q, const bool staged) -> bool {
     constexpr int kPer = kResMaxBlocks / 64;
     const uint64_t* part = ctl->part[q & 3];
@@ -420,7 +424,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       v += __builtin_bit_cast(double, u[j] & ~(uint64_t)kTagMask);
     }
     v = wsum_r(v);
-    if (lane == 0) s_tot = v;
+    if (lane == 0) s_tot[sum_word(q)] = v;
     return __any(late);
   };
   // the sum of the last check's partials (red: the waves' of one workgroup)
@@ -429,13 +433,13 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (wave == 0 && sum_partials(seq, false)) s_res = kWaitEnd;
     lds_barrier_r();
     if (s_res == kWaitEnd) lost = true;
-    return uni_r(s_tot);
+    return uni_r(s_tot[sum_word(seq)]);
   };
   // All workgroups: records stored before it are visible after it.  red
   // (nullable): the waves' partials of a check, sent along; flag: an LDS word,
   // nonzero where a message was not finite.  Returns whether any was.  sum
   // (nonzero): the check whose staged partials are added up meanwhile, into
-  // s_tot.
+  // its word of s_tot.
   auto grid_barrier = [&](const double* red, const int* flag, const uint32_t sum = 0) -> bool {
     ++ep;
     if (nb == 1) {
@@ -827,7 +831,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       const bool any_bad = grid_barrier(ck ? s_red[pn] : nullptr, &s_bad[t % 3], late);
       if (LATE && late) {
         if (lost) return true;
-        decide(uni_r(s_tot), t - 2);
+        decide(uni_r(s_tot[sum_word(late)]), t - 2);
         if (conv >= 0 || err) {
           if (upd && tail) {  // the sweep taken back
             o1P = o2P;

@@ -1,0 +1,65 @@
+// Checks of the rules in csrc/rules.h, on the CPU.  One check per command-line
+// name; exits 0 when it holds.
+#include <cstdio>
+#include <cstring>
+#include <vector>
+
+#include "rules.h"
+
+using namespace gabp;
+
+namespace {
+
+// The LDS words of the check sums of a resident solve, as its waves touch them.
+// Between two workgroup barriers (an epoch) nothing orders the waves, so a word
+// that wave 0 writes in an epoch must not be read in it by another wave.
+// A decision on check q is early or late:
+//   early: wave 0 writes q's word; barrier; every wave reads it; the sweep
+//          follows, with two barriers in it;
+//   late:  the sweep's first barrier; wave 0 writes; its second barrier; every
+//          wave reads.
+// Either kind may follow either.  All sequences of `len` decisions are tried.
+int sum_words() {
+  const int len = 12;
+  for (unsigned kinds = 0; kinds < (1u << len); ++kinds) {
+    for (uint32_t q0 : {1u, 2u, 0xfffffffau}) {
+      std::vector<uint32_t> wr, rd;  // words written by wave 0 and read by the others in the current epoch
+      bool ok = true;
+      auto barrier = [&] {
+        for (uint32_t w : wr)
+          for (uint32_t r : rd) ok = ok && w != r;
+        wr.clear();
+        rd.clear();
+      };
+      for (int k = 0; k < len; ++k) {
+        const uint32_t w = sum_word(q0 + (uint32_t)k);
+        if (w >= (uint32_t)kSumWords) return 1;
+        const bool late = (kinds >> k) & 1u;
+        if (late) barrier();
+        wr.push_back(w);
+        barrier();
+        rd.push_back(w);
+        if (!late) {
+          barrier();
+          barrier();
+        }
+      }
+      barrier();
+      if (!ok) {
+        std::printf("a word is written while it may still be read: decisions %03x (bit k: check k late)\n", kinds);
+        return 1;
+      }
+    }
+  }
+  return 0;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const char* name = argc > 1 ? argv[1] : "";
+  int bad = 2;
+  if (!std::strcmp(name, "sum_words")) bad = sum_words();
+  if (!bad) std::printf("ok: %s\n", name);
+  return bad;
+}
