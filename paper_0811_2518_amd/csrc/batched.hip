@@ -169,6 +169,7 @@ struct BatchArgs {
   double* tred;           // [phases][2][workgroups][kTeamVals] reduction slots
   PhaseList pph, rph;
   uint64_t roll_limit;    // ticks of the wall clock
+  int32_t spread;         // test aid: the members of a team on different XCDs
   const double* B;
   double* X;
   double tol;
@@ -632,9 +633,21 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh, Team& tm) 
     if (tp - tbest >= kPrecStallSweeps && best <= kPrecStall) break;
     if (tp >= A.inner_max || !(ch <= 1e30f)) break;
   }
-  // freeze the h-update coefficients from the precisions of round tp
+  // freeze the h-update coefficients from the precisions of round tp.  The
+  // slots' messages are plain stores of the wave that swept them (only the
+  // aggregates cross workgroups), so the freeze walks the slices as the sweeps
+  // did: colour-serial, class by class.  Every aggregate is complete, so no
+  // barrier is needed in between.
   Red rd{0.f, 0.f, 0.0, 0};
-  pass<kKFreeze, SER, TEAM>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
+  if (SER) {
+    for (int q = 0; q < ncls; ++q) {
+      int slo, shi, rhi;
+      class_range(A, cls0, q, V, slo, shi, rhi);
+      pass<kKFreeze, true, TEAM>(A, V, tm, tp, slo, shi, V.n, rd);
+    }
+  } else {
+    pass<kKFreeze, false, TEAM>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
+  }
   reduce_max2<TEAM>(sh, tm, rd.bad ? 1.f : 0.f, 0.f, 1);
   if (threadIdx.x == 0 && tm.m == 0) {
     ItemInfo inf{};
@@ -805,9 +818,11 @@ __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& 
     teams = __builtin_amdgcn_readfirstlane(sh.item) != 0;
     __syncthreads();
   }
-  // ranks: consecutive ranks (a team) share an XCD of a round-robin dispatch
+  // ranks: consecutive ranks (a team) share an XCD of a round-robin dispatch.
+  // That is for speed alone: nothing that one workgroup writes and another
+  // reads in this launch relies on a shared L2.
   const int G = gridDim.x;
-  const int rank = G % 8 == 0 ? ((int)blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x;
+  const int rank = G % 8 == 0 && !A.spread ? ((int)blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x;
   for (int p = 0; p < P.n; ++p) {
     const PhaseRec ph = P.ph[p];
     uint32_t* queue = &A.ctl->queue[k][p];
@@ -1447,6 +1462,7 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   a.pph = bs->pph;
   a.rph = bs->rph;
   a.roll_limit = (uint64_t)bs->clock_khz * kRollMs;
+  a.spread = (int32_t)c->aid[kAidSpreadTeams];
   a.B = B;
   a.X = X;
   a.tol = tol;

@@ -673,6 +673,12 @@ gabp_status gabp_get_props(gabp_handle h, gabp_props* p) {
   return GABP_OK;
 }
 
+gabp_status gabp_set_test_aid(gabp_handle h, int32_t which, int64_t value) {
+  if (!h || which < 0 || which >= kAids) return fail(h, GABP_E_ARG, "test aid");
+  h->aid[which] = value;
+  return GABP_OK;
+}
+
 void gabp_destroy(gabp_handle h) {
   if (!h) return;
   gabp_ctx* c = h;

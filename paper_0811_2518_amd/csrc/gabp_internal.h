@@ -347,6 +347,13 @@ constexpr int kLayoutCompact = 3;  // node broadcast, one incoming message per s
 constexpr int kLayoutSerial = 4;   // serial scheduling over colour classes, rows stored in colour order
 inline bool node_family(int layout) { return layout == kLayoutNode || layout == kLayoutCompact; }
 
+// Test aids of a handle (gabp_set_test_aid): conditions that a program cannot
+// bring about at will.
+enum TestAid : int {
+  kAidSpreadTeams = 0,  // nonzero: a batch's teams take their members from different XCDs
+  kAids = 1
+};
+
 // Everything a handle owns.  Device arrays are suffixed _d.
 struct Ctx {
   int32_t n = 0;
@@ -461,6 +468,8 @@ struct Ctx {
   double* vperm_d = nullptr;
   double* lsum_d = nullptr;           // [n] residual part of the earlier classes
   ResPlan res;                        // resident solve (nb = 0: the system does not fit)
+
+  int64_t aid[kAids] = {0};           // test aids
 
   // batched
   bool batched = false;
@@ -655,3 +664,6 @@ gabp_status batched_profile(Ctx* c, gabp_batch_profile* out);
 
 // The opaque handle type of the C ABI.
 struct gabp_ctx : public gabp::Ctx {};
+
+// For the tests alone, so not in gabp.h: sets a gabp::TestAid of a handle.
+extern "C" gabp_status gabp_set_test_aid(gabp_handle h, int32_t which, int64_t value);

@@ -1,0 +1,12 @@
+"""Test aids of a handle (gabp_set_test_aid): conditions that a program cannot bring about at will."""
+import ctypes
+
+from paper_0811_2518_amd import binding
+
+SPREAD_TEAMS = 0  # nonzero: a batch's teams take their members from different XCDs
+
+
+def set_aid(solver, which, value):
+    f = binding.lib().gabp_set_test_aid
+    f.argtypes, f.restype = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64], ctypes.c_int32
+    assert f(solver._h, which, value) == binding.OK
