@@ -338,7 +338,8 @@ struct ResPlan {
   int2* lane_d = nullptr;
   int2* cls_tab_d = nullptr;
   int32_t* cls_start_d = nullptr;
-  ResCtl* ctl_d = nullptr;  // [2], used in turn
+  ResCtl* ctl_d = nullptr;  // [2], used in turn: a launch clears the next one's
+  bool clean = true;        // the next launch's block is known to be zero
 };
 
 constexpr int kLayoutEdge = 1;     // outgoing message records + reverse-slot index

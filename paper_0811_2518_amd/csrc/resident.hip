@@ -299,9 +299,17 @@ hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s) 
   a.cls_start = p.cls_start_d;
   a.cls_tab = p.cls_tab_d;
   a.rows_cap = p.rows_cap;
+  // The launch before cleared this one's control block, if it ran: one that was
+  // refused, or recorded into a capture, did not, and left counters behind that
+  // would let this one's barriers through.
+  if (!p.clean) {
+    const hipError_t e = launch_fill((double*)p.ctl_d, 2 * sizeof(ResCtl) / sizeof(double), 0.0, s);
+    if (e != hipSuccess) return e;
+  }
+  p.clean = false;  // until solve_resident has seen the launch's status
+  p.phase ^= 1;
   a.ctl = p.ctl_d + p.phase;
   a.ctl_next = p.ctl_d + (p.phase ^ 1);
-  p.phase ^= 1;
   a.roll_limit = (uint64_t)p.khz * kResRollMs;
   a.wait_limit = (uint64_t)p.khz * kResWaitMs;
   const bool fp32 = c->opts.precision == GABP_FP32_REFINE;

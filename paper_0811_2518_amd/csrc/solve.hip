@@ -961,6 +961,7 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
   GABP_HIP(c, launch_resident(c, a, honly, s));
   GABP_HIP(c, hipStreamSynchronize(s));
   const DevStatus st = *c->st_small_h;
+  c->res.clean = st.done == 1;
   if (!st.done) return GABP_OK;  // the chip was busy
   *ran = true;
   if (st.done != 1) return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
