@@ -64,7 +64,7 @@ gabp_status check_opts(Ctx* c, const gabp_opts& o) {
 
 gabp_status common_setup(Ctx* c) {
   GABP_HIP(c, hipHostMalloc((void**)&c->st_h, 4 * sizeof(DevStatus), hipHostMallocDefault));
-  GABP_HIP(c, hipHostMalloc((void**)&c->st_small_h, sizeof(DevStatus), hipHostMallocMapped | hipHostMallocCoherent));
+  GABP_HIP(c, hipHostMalloc((void**)&c->st_small_h, 2 * sizeof(DevStatus), hipHostMallocMapped | hipHostMallocCoherent));
   GABP_HIP(c, hipHostGetDevicePointer((void**)&c->st_small_d, c->st_small_h, 0));
   GABP_HIP(c, hipHostMalloc((void**)&c->st_mir_h, 3 * sizeof(DevStatus), hipHostMallocMapped | hipHostMallocCoherent));
   GABP_HIP(c, hipHostGetDevicePointer((void**)&c->st_mir_d, c->st_mir_h, 0));

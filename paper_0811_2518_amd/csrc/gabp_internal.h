@@ -318,6 +318,7 @@ struct ResArgs {
   // computed).  Outer loops: conv_round 0 or -1, error of the outer and pad of
   // the inner solve, ticket: sweeps, last_round: outer steps, pad2: froze
   DevStatus* st;
+  int32_t* lost;            // set to 1 by a workgroup whose wait ran out; it stores no results
   double* x;
   double* var;              // nullable
   void* cin_out;            // nullable: [2][E] {P, h} incoming messages by round parity
@@ -352,7 +353,8 @@ inline bool node_family(int layout) { return layout == kLayoutNode || layout == 
 // bring about at will.
 enum TestAid : int {
   kAidSpreadTeams = 0,  // nonzero: a batch's teams take their members from different XCDs
-  kAids = 1
+  kAidWaitLimit = 1,    // nonzero: limit of the resident solve's waits, in clock ticks plus one
+  kAids = 2
 };
 
 // Everything a handle owns.  Device arrays are suffixed _d.
@@ -427,7 +429,8 @@ struct Ctx {
   double* norms_d = nullptr;              // [4]: ||b||, ||r_outer||, spare
   DevStatus* st_d = nullptr;              // [2]: inner / outer
   DevStatus* st_h = nullptr;              // pinned host mirror [4]
-  DevStatus* st_small_h = nullptr;        // pinned, coherent: written by the one-launch solve itself
+  DevStatus* st_small_h = nullptr;        // pinned, coherent: written by the one-launch solve itself;
+                                          // behind it the resident solve's "a wait ran out" word
   DevStatus* st_small_d = nullptr;        // ... its device address
   // pinned, coherent: copies of the device status written by finish kernels
   // (two slots for the chunks of a compact run, one for the outer step), so

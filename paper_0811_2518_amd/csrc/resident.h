@@ -173,20 +173,21 @@ __device__ __forceinline__ void grid_release(ResCtl* c, const GridPos& p, uint32
 
 // One lane: wait for barrier `ep`: on the one counter, or on the group's
 // release word, which holds the barrier number and the flags raised before it,
-// so that every workgroup leaves it with the same answer.
+// so that every workgroup leaves it with the same answer.  The word is loaded
+// after the clock, so a wave that was paused beyond the limit still sees a
+// barrier that ended meanwhile.
 __device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t ep, uint64_t limit) {
   const uint64_t t0 = wall_clock64();
-  if (p.ngrp == 1) {
-    for (;;) {
+  for (;;) {
+    const bool over = wall_clock64() - t0 > limit;
+    if (p.ngrp == 1) {
       const uint64_t v = AGENT_LOAD(&c->grp[0].v);
       if ((v & kCountMask) >= (uint64_t)ep * p.gsize) return ((v >> (ep & 1 ? 52 : 40)) & 0xfff) ? kWaitBad : kWaitOk;
-      if (wall_clock64() - t0 > limit) return kWaitEnd;
+    } else {
+      const uint64_t v = AGENT_LOAD(&c->rel[p.grp].v);
+      if ((v & ~(1ull << 63)) >= ep) return (v >> 63) ? kWaitBad : kWaitOk;
     }
-  }
-  for (;;) {
-    const uint64_t v = AGENT_LOAD(&c->rel[p.grp].v);
-    if ((v & ~(1ull << 63)) >= ep) return (v >> 63) ? kWaitBad : kWaitOk;
-    if (wall_clock64() - t0 > limit) return kWaitEnd;
+    if (over) return kWaitEnd;
   }
 }
 
@@ -254,6 +255,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // [(t + 1) % 3], which no lane reads or sets until sweep t + 1
   __shared__ int s_bad[3];
   __shared__ int s_res;
+  __shared__ int s_late;  // nonzero: the wait for a check's partials ran out
   __shared__ __align__(16) uint64_t s_part[kResMaxBlocks];  // a check's partials, staged for a late decision
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = A.n;
@@ -372,7 +374,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   };
   publish_prior(MODE == kResFrozen || (MODE == kResOuter && A.frozen));
   if (tid < 3) s_bad[tid] = 0;
-  if (tid == 0) s_res = 0;
+  if (tid == 0) s_res = s_late = 0;
   // the other control block is idle during this launch: cleared for the next one
   if (blockIdx.x == 0 && nb > 1)
     for (int i = tid; i < (int)(sizeof(ResCtl) / 8); i += LANES) ((uint64_t*)A.ctl_next)[i] = 0ull;
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     __syncthreads();
     if (s_res) return;
   }
-  bool lost = false;
+  bool lost = false;  // a wait of this workgroup ran out (all its waves agree)
   // the sum of check q's partials, formed by wave 0 and left in its word of
   // s_tot: from memory, or from the copy in s_part where `staged`.  True: a
   // wait ran out.
@@ -418,8 +420,9 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       while ((u[j] & kTagMask) != (q & kTagMask) && !late) {
+        const bool over = wall_clock64() - t0 > A.wait_limit;
         u[j] = AGENT_LOAD(&part[lane + 64 * j]);
-        late = wall_clock64() - t0 > A.wait_limit;
+        late = over && (u[j] & kTagMask) != (q & kTagMask);
       }
       v += __builtin_bit_cast(double, u[j] & ~(uint64_t)kTagMask);
     }
@@ -430,9 +433,9 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // the sum of the last check's partials (red: the waves' of one workgroup)
   auto total = [&](const double* red) -> double {
     if (nb == 1) return block_sum(red);
-    if (wave == 0 && sum_partials(seq, false)) s_res = kWaitEnd;
+    if (wave == 0 && sum_partials(seq, false)) s_late = 1;
     lds_barrier_r();
-    if (s_res == kWaitEnd) lost = true;
+    if (s_late) lost = true;
     return uni_r(s_tot[sum_word(seq)]);
   };
   // All workgroups: records stored before it are visible after it.  red
@@ -854,11 +857,19 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     prev_rel = prev_round >= 0 ? rel_of(prev_tot) : -1.0;
   };
 
+  // a workgroup that stopped waiting stores no result, and the host hears of it
+  // from whichever workgroup it was
+  auto give_up = [&]() -> bool {
+    if (lost && tid == 0) *A.lost = 1;
+    return lost;
+  };
+
   if constexpr (!OUTER) {
     constexpr bool HONLY = MODE == kResFrozen;
     const int M = A.max_iter;
     if constexpr (SERIAL) run_serial(A.tol, M, bnorm);
     else run(std::integral_constant<bool, HONLY>{}, A.tol, M, bnorm);
+    if (give_up()) return;
     // ---- results: the returned round and the state it leaves ---------------
     // the own aggregates are of rounds T = min(conv + 1, M) and T - 1
     const int ret = conv >= 0 ? conv : M;
@@ -884,7 +895,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     }
     if (blockIdx.x == 0 && tid == 0) {
       DevStatus st{};
-      st.done = lost ? 2 : 1;
+      st.done = 1;
       st.conv_round = conv;
       st.error = err;
       st.last_rel = last_rel;
@@ -1005,6 +1016,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       if (orel <= A.tol) oconv = 0;
       else if (!(orel <= kDivergeLimit)) oerr = kErrDiverged;
     }
+    if (give_up()) return;
     if (tail) A.x[A.inv ? A.inv[row] : row] = x;
     if (froze && A.coef_out) {  // later calls start from the frozen precisions
       if (tail) ((T*)A.inv_pt_out)[row] = ip;
@@ -1015,7 +1027,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     }
     if (blockIdx.x == 0 && tid == 0) {
       DevStatus st{};
-      st.done = lost ? 2 : 1;
+      st.done = 1;
       st.conv_round = oconv;
       st.error = oerr;
       st.pad = ierr;

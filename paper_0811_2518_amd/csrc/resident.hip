@@ -293,6 +293,7 @@ hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s) 
   a.agg[1] = c->agg_d[1];
   a.check_every = c->opts.check_every;
   a.st = c->st_small_d;
+  a.lost = (int32_t*)(c->st_small_d + 1);
   a.blk = p.blk_d;
   a.lane = p.lane_d;
   a.ncls = c->ncol;
@@ -311,7 +312,7 @@ hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s) 
   a.ctl = p.ctl_d + p.phase;
   a.ctl_next = p.ctl_d + (p.phase ^ 1);
   a.roll_limit = (uint64_t)p.khz * kResRollMs;
-  a.wait_limit = (uint64_t)p.khz * kResWaitMs;
+  a.wait_limit = c->aid[kAidWaitLimit] ? (uint64_t)c->aid[kAidWaitLimit] - 1 : (uint64_t)p.khz * kResWaitMs;
   const bool fp32 = c->opts.precision == GABP_FP32_REFINE;
   hipLaunchKernelGGL(res_kernel(fp32, p.lanes, p.K, mode), dim3(p.nb), dim3(p.lanes),
                      lds_bytes(c, p.rows_cap, p.lanes, p.K, mode), s, a);

@@ -957,14 +957,21 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
   }
   if (loop) c->frozen_valid = false;
   *c->st_small_h = DevStatus{};
+  const volatile int32_t* lost = (int32_t*)(c->st_small_h + 1);
+  *(int32_t*)(c->st_small_h + 1) = 0;
   reset_timing(c);
   GABP_HIP(c, launch_resident(c, a, honly, s));
   GABP_HIP(c, hipStreamSynchronize(s));
   const DevStatus st = *c->st_small_h;
-  c->res.clean = st.done == 1;
+  c->res.clean = st.done && !*lost;
+  if (*lost) {  // x and what later calls would start from are in part unwritten
+    *ran = true;
+    c->frozen_valid = false;
+    c->last_msg_round = -1;
+    return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
+  }
   if (!st.done) return GABP_OK;  // the chip was busy
   *ran = true;
-  if (st.done != 1) return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
   gabp_status r;
   if (outer) {
     if (st.pad2) {

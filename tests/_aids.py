@@ -4,6 +4,7 @@ import ctypes
 from paper_0811_2518_amd import binding
 
 SPREAD_TEAMS = 0  # nonzero: a batch's teams take their members from different XCDs
+WAIT_LIMIT = 1    # nonzero: limit of the resident solve's waits, in clock ticks plus one
 
 
 def set_aid(solver, which, value):

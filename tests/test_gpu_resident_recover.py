@@ -1,4 +1,4 @@
-"""The resident solve after a launch that did not run.
+"""The resident solve after a launch that did not run or whose workgroups gave up.
 
 A launch clears the barrier counters that the next one uses.  One that was recorded into a stream
 capture (a solve waits for its result, so the call ends in an error) or refused never runs, and
@@ -13,6 +13,8 @@ import torch
 import paper_0811_2518_amd as g
 import workloads
 from paper_0811_2518_amd import binding
+
+from _aids import WAIT_LIMIT, set_aid
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -63,3 +65,30 @@ def test_solve_after_a_refused_capture(name, layout, before):
                 _, i = s.solve(b, tol=1e-10, max_iter=2000, x=x)
                 assert torch.equal(x, want) and i["sweeps"] == wi["sweeps"]
         st.synchronize()
+
+
+@pytest.mark.parametrize("kw", [{}, {"layout": "serial"}, {"precision": "fp32"}], ids=["plain", "serial", "fp32"])
+@pytest.mark.parametrize("name", ["grid_97x61", "grid_181x173"])
+def test_a_workgroup_that_stops_waiting_is_reported(name, kw):
+    """Waits cut short by a tiny limit: whichever workgroup gives up, the call ends in an error or
+    with the very bits of a full solve, and the handle solves again afterwards."""
+    px, py = (97, 61) if name == "grid_97x61" else (181, 173)
+    p = workloads.grid2d_problem(px, py, 2)
+    s = g.Solver(p.row_ptr, p.col, p.val, device=DEV, **kw)
+    b = dev(p.b)
+    want = [s.solve(b, tol=1e-10, max_iter=2000)[0] for _ in range(2)]
+    s.close()
+    s = g.Solver(p.row_ptr, p.col, p.val, device=DEV, **kw)
+    seen = set()
+    for ticks in (0, 20, 50, 100, 150, 200, 300, 500, 1000, 10000):
+        for _ in range(3):
+            set_aid(s, WAIT_LIMIT, ticks + 1)
+            x, info = s.solve(b, tol=1e-10, max_iter=2000, check=False)
+            seen.add(info["status"])
+            assert info["status"] in (binding.OK, binding.E_HIP), info
+            if info["status"] == binding.OK:  # plain reuse: the first solve, or one on its frozen precisions
+                assert any(torch.equal(x, w) for w in want), ticks
+            set_aid(s, WAIT_LIMIT, 0)
+            x, info = s.solve(b, tol=1e-10, max_iter=2000)
+            assert any(torch.equal(x, w) for w in want), ticks
+    assert binding.E_HIP in seen  # no barrier ends within the first look at the clock
