@@ -280,7 +280,7 @@ struct ResLine {
 struct ResCtl {
   ResLine grp[8], root, rel[8];
   uint32_t state, pad[31];
-  uint64_t part[4][kResMaxBlocks];  // residual partials, tagged, by check number mod 4
+  uint64_t part[4][kResMaxBlocks];  // residual partials, tagged, by check number mod 4 (rules.h)
 };
 struct ResArgs {
   int32_t n, E;

@@ -111,14 +111,11 @@ __device__ __forceinline__ void st_rec(const RecBuf& b, int i, vec2<double> v) {
                                          kAgentPolicy);
 }
 
-// Partial sums travel without a wait between them and the barrier arrival: the
-// low three bits of a partial's mantissa (2^-49 of its value) carry the check's
-// sequence number mod 8, and a reader waits until they match.  Four sets by the
-// number mod 4: check s is read until the barrier after the one it was sent
-// with has ended, and a workgroup stores check s + 4 after that.
-constexpr uint32_t kTagMask = 7u;
+// A check's partial sum as it travels (rules.h).  Check s is read until the
+// barrier after the one it was sent with has ended, and a workgroup stores check
+// s + 4 into the same set of words after that.
 __device__ __forceinline__ uint64_t tag_partial(double v, uint32_t seq) {
-  return (__builtin_bit_cast(uint64_t, v) & ~(uint64_t)kTagMask) | (seq & kTagMask);
+  return pack_partial(__builtin_bit_cast(uint64_t, v), seq);
 }
 
 enum GridState : int { kGo = 1, kAbort = 2 };
@@ -383,7 +380,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     const double v = wsum_r(tail ? b64 * b64 : 0.0);
     if (lane == 0) s_red[0][wave] = v;
   }
-  uint32_t seq = 1;  // checks so far (the norm is the first): the partials' tag
+  uint32_t seq = kFirstCheck;  // number of the last check (the norm is the first)
   uint32_t ep = 1;   // grid barriers so far
   auto block_sum = [&](const double* red) -> double {
     return readlane_r(sum16(lane < NW ? red[lane] : 0.0), 15);
@@ -394,7 +391,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (wave == 0) {
       const double v = block_sum(s_red[0]);
       if (tid == 0) {
-        AGENT_STORE(&ctl->part[seq & 3][b], tag_partial(v, seq));
+        AGENT_STORE(&ctl->part[partial_set(seq)][b], tag_partial(v, seq));
         s_res = roll_call(ctl, gp, A.roll_limit) ? 0 : 1;
       }
     }
@@ -407,24 +404,24 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // wait ran out.
   auto sum_partials = [&](const uint32_t q, const bool staged) -> bool {
     constexpr int kPer = kResMaxBlocks / 64;
-    const uint64_t* part = ctl->part[q & 3];
+    const uint64_t* part = ctl->part[partial_set(q)];
     uint64_t u[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const int i = lane + 64 * j;
-      u[j] = i >= nb ? (q & kTagMask) : staged ? s_part[i] : AGENT_LOAD(&part[i]);
+      u[j] = i >= nb ? partial_tag(q) : staged ? s_part[i] : AGENT_LOAD(&part[i]);
     }
     const uint64_t t0 = wall_clock64();
     bool late = false;
     double v = 0.0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      while ((u[j] & kTagMask) != (q & kTagMask) && !late) {
+      while (!partial_sent(u[j], q) && !late) {
         const bool over = wall_clock64() - t0 > A.wait_limit;
         u[j] = AGENT_LOAD(&part[lane + 64 * j]);
-        late = over && (u[j] & kTagMask) != (q & kTagMask);
+        late = over && !partial_sent(u[j], q);
       }
-      v += __builtin_bit_cast(double, u[j] & ~(uint64_t)kTagMask);
+      v += __builtin_bit_cast(double, partial_bits(u[j]));
     }
     v = wsum_r(v);
     if (lane == 0) s_tot[sum_word(q)] = v;
@@ -455,7 +452,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (wave == 0) {
       const double v = red ? block_sum(red) : 0.0;
       if (tid == 0) {
-        if (red) AGENT_STORE(&ctl->part[seq & 3][b], tag_partial(v, seq));
+        if (red) AGENT_STORE(&ctl->part[partial_set(seq)][b], tag_partial(v, seq));
         bool any_bad = false;
         // (with one counter too the answer is awaited: polling at once delays the others' arrivals)
         if (grid_arrive(ctl, gp, ep, flag && *flag, &any_bad)) grid_release(ctl, gp, ep, any_bad);
@@ -700,7 +697,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
           if (wave == 0) {
             const __amdgpu_buffer_rsrc_t r =
                 __builtin_amdgcn_make_buffer_rsrc(ctl->part, 0, (int)sizeof(ctl->part), 0x00027000);
-            const int at = (int)((seq & 3) * sizeof(ctl->part[0]));
+            const int at = (int)(partial_set(seq) * sizeof(ctl->part[0]));
             for (int i = 0; i < nb; i += 128)
               __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(s_part + i), 16,
                                                        lane * 16, at + i * 8, 0, kAgentPolicy);

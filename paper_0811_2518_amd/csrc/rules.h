@@ -21,4 +21,19 @@ namespace gabp {
 constexpr int kSumWords = 2;
 GABP_HD constexpr uint32_t sum_word(uint32_t q) { return q & 1u; }
 
+// Partial sums of a check travel without a wait between them and the barrier
+// arrival: each word says itself whether it has arrived.  A partial is a sum of
+// squares, so its sign bit is free: it holds bit 2 of the check's number, and
+// the value keeps all its bits.  One bit is enough.  There are four sets of
+// words, taken by the check number mod 4; a set is written for check q only
+// after everyone has read check q - 4 from it, whose bit is the other one; and
+// a launch finds zeros, while its first four checks (numbers 4 to 7) carry a 1.
+constexpr uint32_t kFirstCheck = 4;
+constexpr uint64_t kSignBit = 1ull << 63;
+GABP_HD constexpr uint32_t partial_set(uint32_t q) { return q & 3u; }
+GABP_HD constexpr uint64_t partial_tag(uint32_t q) { return (uint64_t)((q >> 2) & 1u) << 63; }
+GABP_HD constexpr uint64_t pack_partial(uint64_t bits, uint32_t q) { return (bits & ~kSignBit) | partial_tag(q); }
+GABP_HD constexpr bool partial_sent(uint64_t word, uint32_t q) { return (word & kSignBit) == partial_tag(q); }
+GABP_HD constexpr uint64_t partial_bits(uint64_t word) { return word & ~kSignBit; }
+
 }  // namespace gabp

@@ -54,12 +54,50 @@ int sum_words() {
   return 0;
 }
 
+// A partial keeps every bit on its way, and a word that has not been written for
+// check q is never taken for check q's.
+int partials() {
+  uint64_t r = 88172645463325252ull;
+  auto carry = [](uint64_t bits) {
+    for (uint32_t q = kFirstCheck; q < kFirstCheck + 16; ++q) {
+      const uint64_t w = pack_partial(bits, q);
+      if (!partial_sent(w, q) || partial_bits(w) != bits) return false;
+    }
+    return true;
+  };
+  // zero, the smallest subnormal, one and its neighbours, the largest, infinity, a NaN
+  for (uint64_t bits : {0ull, 1ull, 0x3ff0000000000000ull, 0x3ff0000000000001ull, 0x3fefffffffffffffull,
+                        0x7fefffffffffffffull, 0x7ff0000000000000ull, 0x7ff8000000000000ull})
+    if (!carry(bits)) return 1;
+  for (int k = 0; k < 100000; ++k) {
+    r ^= r << 13;
+    r ^= r >> 7;
+    r ^= r << 17;
+    if (!carry(r & ~kSignBit)) {
+      std::printf("bits %016llx do not survive\n", (unsigned long long)(r & ~kSignBit));
+      return 1;
+    }
+  }
+  std::vector<uint64_t> set(4, 0);  // as a launch finds them
+  for (uint32_t q = kFirstCheck; q < kFirstCheck + 4096; ++q) {
+    uint64_t& w = set[partial_set(q)];
+    if (partial_sent(w, q)) {
+      std::printf("check %u is taken for sent before it was\n", q);
+      return 1;
+    }
+    w = pack_partial(r, q);
+    if (!partial_sent(w, q)) return 1;
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const char* name = argc > 1 ? argv[1] : "";
   int bad = 2;
   if (!std::strcmp(name, "sum_words")) bad = sum_words();
+  if (!std::strcmp(name, "partials")) bad = partials();
   if (!bad) std::printf("ok: %s\n", name);
   return bad;
 }

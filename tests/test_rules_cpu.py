@@ -24,3 +24,7 @@ def check(driver, name):
 
 def test_check_sums_are_never_overwritten_while_read(driver):
     check(driver, "sum_words")
+
+
+def test_partials_keep_their_bits_and_are_not_taken_early(driver):
+    check(driver, "partials")
