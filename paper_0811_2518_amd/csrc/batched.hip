@@ -54,6 +54,7 @@
 #include <vector>
 
 #include "gabp_internal.h"
+#include "rules.h"
 
 namespace gabp {
 
@@ -62,6 +63,7 @@ namespace {
 constexpr int kBT = 512;                // lanes per batched workgroup
 constexpr int kWave = 64;
 constexpr int kWaves = kBT / kWave;
+static_assert(kWaves == kTeamWaves, "the team rule counts waves of a workgroup");
 constexpr int kSlice = 64;              // rows per slice
 constexpr int kSortWindow = 512;        // rows sorted by degree together
 constexpr int kQSlots = 4;              // slots of a row loaded together (FP32 passes)
@@ -110,7 +112,6 @@ struct ItemInfo {
 };
 
 // Workgroups that run an item together.
-constexpr int kMaxTeam = 64;
 constexpr int kPhases = 7;               // team sizes 64, 32, ... 1
 constexpr int kTeamVals = 2 * kMaxGroup; // values of a team reduction
 constexpr uint64_t kRollMs = 1;          // roll call: longest wait for a workgroup to start
@@ -1058,19 +1059,6 @@ struct BatchState {
   std::vector<int32_t> key_nrhs;  // of the work list (empty: none yet)
 };
 
-// Members of the team that runs an item of the given cost, where an even share
-// of the work per workgroup is `share`: enough to bring it to half a share, at
-// most one wave per 64-lane unit of its passes.  Half a share: the items
-// behind the first then even out what the estimates miss (a quarter, half, one
-// share: 192 systems of up to 16384 rows 9.0, 8.0, 8.3 ms; 600 of up to 32768
-// rows 40, 43, 46 ms).  One unit per wave: with at least two or four, the 192
-// systems take 7.7 and 10.0 ms, 20 of them 1.1, 1.5 and 2.1 ms.
-int team_for(double cost, double share, int64_t units) {
-  int T = 1;
-  while (T < kMaxTeam && T * kWaves < units && cost / T > 0.5 * share) T *= 2;
-  return T;
-}
-
 // Phases of falling team size over items whose teams are `team` (sorted).
 PhaseList make_phases(const std::vector<int>& team, int grid) {
   PhaseList L{};
@@ -1318,7 +1306,7 @@ gabp_status batched_create(Ctx* c, int32_t num_sys, const int32_t* sys_row_off) 
     for (int s = 0; s < num_sys; ++s) total += cost(s);
     std::vector<int> team(num_sys);
     for (int s = 0; s < num_sys; ++s)
-      team[s] = team_for(cost(s), total / bs->grid_p, bs->sys_h[s].nsl / std::max(1, bs->sys_h[s].ncls));
+      team[s] = team_for(cost(s), total / bs->grid_p, bs->sys_h[s].nsl / std::max(1, bs->sys_h[s].ncls), bs->grid_p);
     std::vector<int32_t> order(num_sys);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
@@ -1381,7 +1369,7 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
       if (R.n == 0) continue;
       const int32_t k = nrhs[s];
       int32_t gmax = kMaxGroup;
-      while (gmax > 1 && unit(s) * gmax / team_for(unit(s) * gmax, 0.0, waves(s, gmax)) > cap) gmax >>= 1;
+      while (gmax > 1 && unit(s) * gmax / team_for(unit(s) * gmax, 0.0, waves(s, gmax), bs->grid_r) > cap) gmax >>= 1;
       for (int32_t j0 = 0; j0 < k;) {
         int32_t kg = gmax;
         while (kg > k - j0) kg >>= 1;
@@ -1401,7 +1389,7 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
         j0 += kg;
       }
     }
-    auto team = [&](const BItem& it) { return team_for(unit(it.sys) * it.kg, share, waves(it.sys, it.kg)); };
+    auto team = [&](const BItem& it) { return team_for(unit(it.sys) * it.kg, share, waves(it.sys, it.kg), bs->grid_r); };
     std::stable_sort(items.begin(), items.end(), [&](const BItem& a, const BItem& b) {
       const int ta = team(a), tb = team(b);
       return ta != tb ? ta > tb : unit(a.sys) * a.kg > unit(b.sys) * b.kg;

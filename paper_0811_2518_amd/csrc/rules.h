@@ -36,4 +36,20 @@ GABP_HD constexpr uint64_t pack_partial(uint64_t bits, uint32_t q) { return (bit
 GABP_HD constexpr bool partial_sent(uint64_t word, uint32_t q) { return (word & kSignBit) == partial_tag(q); }
 GABP_HD constexpr uint64_t partial_bits(uint64_t word) { return word & ~kSignBit; }
 
+// Members of the team that runs a batched item of the given cost, where an even
+// share of the work per workgroup is `share`: enough to bring it to half a
+// share, at most one wave per 64-lane unit of its passes, and never more than
+// the `grid` workgroups that are launched.  Half a share: the items behind the
+// first then even out what the estimates miss (a quarter, half, one share: 192
+// systems of up to 16384 rows 9.0, 8.0, 8.3 ms; 600 of up to 32768 rows 40, 43,
+// 46 ms).  One unit per wave: with at least two or four, the 192 systems take
+// 7.7 and 10.0 ms, 20 of them 1.1, 1.5 and 2.1 ms.
+constexpr int kMaxTeam = 64;
+constexpr int kTeamWaves = 8;  // waves of a batched workgroup
+inline int team_for(double cost, double share, int64_t units, int grid) {
+  int T = 1;
+  while (T < kMaxTeam && 2 * T <= grid && T * kTeamWaves < units && cost / T > 0.5 * share) T *= 2;
+  return T;
+}
+
 }  // namespace gabp

@@ -91,6 +91,23 @@ int partials() {
   return 0;
 }
 
+// Every team that an item can be given exists on the grid (one that does not would
+// leave the item to nobody), and teams are powers of two up to the largest.
+int teams() {
+  for (int grid = 1; grid <= 1100; ++grid)
+    for (int64_t units : {(int64_t)0, (int64_t)1, (int64_t)9, (int64_t)64, (int64_t)513, (int64_t)1 << 40})
+      for (double cost : {0.0, 1.0, 1e3, 1e30})
+        for (double share : {0.0, 1.0, 1e3}) {
+          const int T = team_for(cost, share, units, grid);
+          if (T < 1 || (T & (T - 1)) || T > kMaxTeam || grid / T < 1) {
+            std::printf("team of %d on a grid of %d\n", T, grid);
+            return 1;
+          }
+        }
+  // a large item on a large grid still gets the largest team, a small one none
+  return team_for(1e9, 1.0, 1 << 20, 1024) == kMaxTeam && team_for(0.4, 1.0, 1 << 20, 1024) == 1 ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -98,6 +115,7 @@ int main(int argc, char** argv) {
   int bad = 2;
   if (!std::strcmp(name, "sum_words")) bad = sum_words();
   if (!std::strcmp(name, "partials")) bad = partials();
+  if (!std::strcmp(name, "teams")) bad = teams();
   if (!bad) std::printf("ok: %s\n", name);
   return bad;
 }

@@ -28,3 +28,7 @@ def test_check_sums_are_never_overwritten_while_read(driver):
 
 def test_partials_keep_their_bits_and_are_not_taken_early(driver):
     check(driver, "partials")
+
+
+def test_no_team_is_larger_than_the_grid(driver):
+    check(driver, "teams")
