@@ -679,6 +679,10 @@ gabp_status gabp_set_test_aid(gabp_handle h, int32_t which, int64_t value) {
   return GABP_OK;
 }
 
+int64_t gabp_get_test_aid(gabp_handle h, int32_t which) {
+  return h && which >= 0 && which < kAids ? h->aid[which] : -1;
+}
+
 void gabp_destroy(gabp_handle h) {
   if (!h) return;
   gabp_ctx* c = h;

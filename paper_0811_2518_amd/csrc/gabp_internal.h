@@ -354,7 +354,9 @@ inline bool node_family(int layout) { return layout == kLayoutNode || layout == 
 enum TestAid : int {
   kAidSpreadTeams = 0,  // nonzero: a batch's teams take their members from different XCDs
   kAidWaitLimit = 1,    // nonzero: limit of the resident solve's waits, in clock ticks plus one
-  kAids = 2
+  kAidRollLimit = 2,    // nonzero: limit of the roll calls, in clock ticks plus one (one: they fail at once)
+  kAidAborted = 3,      // counts the solves that got no place on the chip for a resident launch
+  kAids = 4
 };
 
 // Everything a handle owns.  Device arrays are suffixed _d.
@@ -669,5 +671,6 @@ gabp_status batched_profile(Ctx* c, gabp_batch_profile* out);
 // The opaque handle type of the C ABI.
 struct gabp_ctx : public gabp::Ctx {};
 
-// For the tests alone, so not in gabp.h: sets a gabp::TestAid of a handle.
+// For the tests alone, so not in gabp.h: a gabp::TestAid of a handle.
 extern "C" gabp_status gabp_set_test_aid(gabp_handle h, int32_t which, int64_t value);
+extern "C" int64_t gabp_get_test_aid(gabp_handle h, int32_t which);

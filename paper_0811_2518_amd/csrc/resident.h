@@ -189,10 +189,11 @@ __device__ __forceinline__ int grid_wait(ResCtl* c, const GridPos& p, uint32_t e
 }
 
 // The roll call: the last arrival turns the state to kGo, a workgroup that has
-// waited too long to kAbort, whichever comes first.
+// waited too long to kAbort, whichever comes first.  With a limit of zero nobody
+// waits, and nobody arrives last before the first has given up.
 __device__ __forceinline__ bool roll_call(ResCtl* c, const GridPos& p, uint64_t limit) {
   bool any_bad = false;
-  if (grid_arrive(c, p, 1, false, &any_bad)) {
+  if (limit > 0 && grid_arrive(c, p, 1, false, &any_bad)) {
     uint32_t want = 0;
     __hip_atomic_compare_exchange_strong(&c->state, &want, (uint32_t)kGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);

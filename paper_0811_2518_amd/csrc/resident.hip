@@ -311,7 +311,7 @@ hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s) 
   p.phase ^= 1;
   a.ctl = p.ctl_d + p.phase;
   a.ctl_next = p.ctl_d + (p.phase ^ 1);
-  a.roll_limit = (uint64_t)p.khz * kResRollMs;
+  a.roll_limit = c->aid[kAidRollLimit] ? (uint64_t)c->aid[kAidRollLimit] - 1 : (uint64_t)p.khz * kResRollMs;
   a.wait_limit = c->aid[kAidWaitLimit] ? (uint64_t)c->aid[kAidWaitLimit] - 1 : (uint64_t)p.khz * kResWaitMs;
   const bool fp32 = c->opts.precision == GABP_FP32_REFINE;
   hipLaunchKernelGGL(res_kernel(fp32, p.lanes, p.K, mode), dim3(p.nb), dim3(p.lanes),

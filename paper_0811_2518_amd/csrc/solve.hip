@@ -970,7 +970,10 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
     c->last_msg_round = -1;
     return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
   }
-  if (!st.done) return GABP_OK;  // the chip was busy
+  if (!st.done) {  // the chip was busy
+    ++c->aid[kAidAborted];
+    return GABP_OK;
+  }
   *ran = true;
   gabp_status r;
   if (outer) {
@@ -1140,7 +1143,10 @@ gabp_status solve_outer(Ctx* c, const double* b, double* x, double tol, int32_t 
     // returned round's aggregate record (the single loop keeps them)
     cfg.x_at_end = !single && c->layout == kLayoutCompact;
     cfg.keep_held = (c->opts.flags & GABP_FLAG_REUSE_PRECISION) || c->gamma_used > 0.0;  // a freeze may follow
-    cfg.sparse_checks = true;  // the outer step, not the inner stop round, sets the accuracy
+    // The outer step, not the inner stop round, sets the accuracy.  Where the
+    // solve would be resident and only a busy chip has brought it here, every
+    // round is checked, as there: the result must not depend on the load.
+    cfg.sparse_checks = c->res.nb == 0;
     r = fp32 ? run_sweeps<float>(c, cfg) : run_sweeps<double>(c, cfg);
     if (r != GABP_OK) return r;
     if (c->run_seen_final && c->tev_used == 0) {  // the poller already waited for the final status

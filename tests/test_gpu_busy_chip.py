@@ -1,0 +1,76 @@
+"""Solves that get no place on the chip for their resident launch.
+
+The roll call is made to fail from the host (a limit of zero), as it does when other work holds
+the chip, and the solve takes the launch-per-sweep path.  Whether a chip is busy must not show in
+a result: x, the variances, the sweeps and the outer steps are those of the resident launch bit for
+bit, and later solves of the handle are untouched by the failed launch.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_0811_2518_amd as g
+import workloads
+
+from _aids import ABORTED, ROLL_LIMIT, get_aid, set_aid
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def dev(v):
+    return torch.from_numpy(np.ascontiguousarray(v)).to(DEV)
+
+
+PROBS = {
+    "grid_97x61": lambda: workloads.grid2d_problem(97, 61, 2),
+    "grid_181x173": lambda: workloads.grid2d_problem(181, 173, 3),
+    "er_30011": lambda: workloads.er_problem(30011, 8, 77),
+    "tree": lambda: workloads.random_tree(9777, 81),
+    "btb_3000": lambda: workloads.config5(n=3000, rows=6000),
+}
+MODES = {
+    "plain": ("grid_181x173", {"reuse_precision": False}),
+    "reuse": ("er_30011", {}),
+    "serial": ("grid_97x61", {"layout": "serial"}),
+    "fp32": ("er_30011", {"precision": "fp32", "reuse_precision": False}),
+    # the residual collapses when the messages have met, which no rate of decay predicts
+    "fp32_tree": ("tree", {"precision": "fp32", "reuse_precision": False}),
+    "fp32_reuse": ("grid_181x173", {"precision": "fp32"}),
+    "fp32_serial": ("grid_97x61", {"precision": "fp32", "layout": "serial"}),
+    "loaded_fp32": ("btb_3000", {"precision": "fp32", "gamma": -1.0, "inner_tol": 1e-2, "max_outer": 5000}),
+    "loaded_fp64": ("btb_3000", {"gamma": -1.0, "inner_tol": 1e-2, "max_outer": 5000, "reuse_precision": False}),
+    "single_fp64": ("btb_3000", {"gamma": -1.0, "inner_tol": 1e-3, "single_loop": True}),
+    "single_fp32": ("btb_3000", {"gamma": -1.0, "inner_tol": 1e-3, "single_loop": True, "precision": "fp32",
+                                 "max_outer": 5000}),
+}
+
+
+@pytest.mark.parametrize("mode", sorted(MODES))
+def test_results_do_not_depend_on_the_load(mode):
+    name, kw = MODES[mode]
+    p = PROBS[name]()
+    rng = np.random.default_rng(9)
+    bs = [dev(p.b), dev(rng.standard_normal(p.n)), dev(rng.standard_normal(p.n))]
+    var = "gamma" not in kw and kw.get("precision") != "fp32"
+
+    def run(limits):
+        s = g.Solver(p.row_ptr, p.col, p.val, device=DEV, **kw)
+        out = []
+        for b, limit in zip(bs, limits):
+            set_aid(s, ROLL_LIMIT, limit)
+            before = get_aid(s, ABORTED)
+            got = s.solve(b, tol=1e-9, max_iter=200000, var=var)
+            assert (get_aid(s, ABORTED) > before) == (limit == 1)
+            out.append(got)
+        s.close()
+        return out
+
+    want = run((0, 0, 0))
+    for limits in ((1, 1, 1), (1, 0, 1), (0, 1, 0)):
+        for got, ref in zip(run(limits), want):
+            assert torch.equal(got[0], ref[0]), limits
+            assert all(got[1][k] == ref[1][k] for k in ("sweeps", "outer_iters", "converged", "status")), limits
+            assert got[1]["rel_residual"] == pytest.approx(ref[1]["rel_residual"], rel=1e-12), limits
+            if var:
+                assert torch.equal(got[2], ref[2]), limits
