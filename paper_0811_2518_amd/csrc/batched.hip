@@ -809,11 +809,11 @@ __device__ __forceinline__ bool roll_call_b(BatchCtl* c, int k, uint64_t limit) 
 // The persistent loop of kernel k (0: precision, 1: right-hand sides): the
 // phases in turn, items of a phase until its queue is empty.  one(q) and
 // many(q, team) run item q alone and as a member of a team.
-template <typename One, typename Many>
+template <bool TEAMS, typename One, typename Many>
 __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& P, int k, Shared& sh, One one,
                                            Many many) {
   bool teams = false;
-  if (P.teams) {
+  if (TEAMS && P.teams) {  // (P.teams is set where TEAMS is; without the test more registers spill)
     if (threadIdx.x == 0) sh.item = roll_call_b(A.ctl, k, A.roll_limit) ? 1 : 0;
     __syncthreads();
     teams = __builtin_amdgcn_readfirstlane(sh.item) != 0;
@@ -827,7 +827,7 @@ __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& 
   for (int p = 0; p < P.n; ++p) {
     const PhaseRec ph = P.ph[p];
     uint32_t* queue = &A.ctl->queue[k][p];
-    if (ph.team > 1 && teams) {
+    if (TEAMS && ph.team > 1 && teams) {
       const int tid_ = rank / ph.team;
       if ((tid_ + 1) * ph.team > G) continue;  // not a full team
       Team tm;
@@ -869,29 +869,46 @@ __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& 
 // (colour-serial 0.82 s), 80 (three) 1.04 s (0.73 s) and 64 (four) 1.05 s
 // (0.69 s); 256-lane workgroups with five per CU took 1.34 s (0.83 s).  With
 // four per CU the chip runs near its memory bandwidth, so the few spilled
-// registers cost nothing measurable.
-template <bool SER>
+// registers cost nothing measurable.  With the code for teams beside it k_brhs
+// spills about 30 of them instead of 6 (colour-serial 4), so a batch in which
+// no item is split runs kernels without that code (TEAMS false).  (4096 equal
+// systems of 1000 rows, 4 right-hand sides: 15.6 ms either way.)
+template <bool SER, bool TEAMS>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(8))) void k_bprec(BatchArgs A) {
   __shared__ Shared sh;
-  run_phases(
+  run_phases<TEAMS>(
       A, A.pph, 0, sh,
       [&](int q) {
         Team tm{1, 0, nullptr, nullptr, 0, 0, 0};
         precision_item<SER, false>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
       },
-      [&](int q, Team& tm) { precision_item<SER, true>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm); });
+      [&](int q, Team& tm) {
+        if constexpr (TEAMS) precision_item<SER, true>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
+      });
 }
 
-template <bool SER>
+template <bool SER, bool TEAMS>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(8))) void k_brhs(BatchArgs A) {
   __shared__ Shared sh;
-  run_phases(
+  run_phases<TEAMS>(
       A, A.rph, 1, sh,
       [&](int q) {
         Team tm{1, 0, nullptr, nullptr, 0, 0, 0};
         rhs_item<SER, false>(A, uniform_item(A.items[q]), q, sh, tm);
       },
-      [&](int q, Team& tm) { rhs_item<SER, true>(A, uniform_item(A.items[q]), q, sh, tm); });
+      [&](int q, Team& tm) {
+        if constexpr (TEAMS) rhs_item<SER, true>(A, uniform_item(A.items[q]), q, sh, tm);
+      });
+}
+
+using BatchKernel = void (*)(BatchArgs);
+BatchKernel kernel_p(bool serial, bool teams) {
+  if (teams) return serial ? k_bprec<true, true> : k_bprec<false, true>;
+  return serial ? k_bprec<true, false> : k_bprec<false, false>;
+}
+BatchKernel kernel_r(bool serial, bool teams) {
+  if (teams) return serial ? k_brhs<true, true> : k_brhs<false, true>;
+  return serial ? k_brhs<true, false> : k_brhs<false, false>;
 }
 
 __global__ void k_reset_ctl(uint64_t* p, int64_t words) {
@@ -1259,13 +1276,10 @@ gabp_status batched_create(Ctx* c, int32_t num_sys, const int32_t* sys_row_off) 
   int dev = 0, ncu = 0, per_p = 0, per_r = 0;
   GABP_HIP(c, hipGetDevice(&dev));
   GABP_HIP(c, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  if (bs->serial) {
-    GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_p, k_bprec<true>, kBT, 0));
-    GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_r, k_brhs<true>, kBT, 0));
-  } else {
-    GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_p, k_bprec<false>, kBT, 0));
-    GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_r, k_brhs<false>, kBT, 0));
-  }
+  // (the kernels with teams, whose workgroups must all reside at once; those
+  // without take no more registers or LDS)
+  GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_p, kernel_p(bs->serial, true), kBT, 0));
+  GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_r, kernel_r(bs->serial, true), kBT, 0));
   bs->grid_p = std::max(1, ncu * std::max(1, per_p));
   bs->grid_r = std::max(1, ncu * std::max(1, per_r));
   int khz = 0;
@@ -1465,13 +1479,8 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   const int gp = bs->pph.teams ? bs->grid_p : std::max(1, std::min(bs->grid_p, S));
   const int gr = bs->rph.teams ? bs->grid_r : std::max(1, std::min<int>(bs->grid_r, (int)bs->items.size()));
   bs->launched_grid = gr;
-  if (bs->serial) {
-    hipLaunchKernelGGL(k_bprec<true>, dim3(gp), dim3(kBT), 0, st, a);
-    hipLaunchKernelGGL(k_brhs<true>, dim3(gr), dim3(kBT), 0, st, a);
-  } else {
-    hipLaunchKernelGGL(k_bprec<false>, dim3(gp), dim3(kBT), 0, st, a);
-    hipLaunchKernelGGL(k_brhs<false>, dim3(gr), dim3(kBT), 0, st, a);
-  }
+  hipLaunchKernelGGL(kernel_p(bs->serial, bs->pph.teams), dim3(gp), dim3(kBT), 0, st, a);
+  hipLaunchKernelGGL(kernel_r(bs->serial, bs->rph.teams), dim3(gr), dim3(kBT), 0, st, a);
   GABP_HIP(c, hipGetLastError());
   std::vector<ItemInfo> ii(bs->items.size()), pi(S);
   GABP_HIP(c, hipMemcpyAsync(ii.data(), bs->infos_d, sizeof(ItemInfo) * ii.size(), hipMemcpyDeviceToHost, st));
