@@ -67,7 +67,6 @@ static_assert(kWaves == kTeamWaves, "the team rule counts waves of a workgroup")
 constexpr int kSlice = 64;              // rows per slice
 constexpr int kSortWindow = 512;        // rows sorted by degree together
 constexpr int kQSlots = 4;              // slots of a row loaded together (FP32 passes)
-constexpr int kMaxGroup = 8;            // right-hand sides per work item (1, 2, 4 or 8)
 constexpr float kPrecTol = 4e-7f;       // precision phase: relative change of P~ to stop at
 constexpr float kPrecStall = 2e-5f;     // ... or below this, once it stops halving (FP32 rounding floor)
 constexpr int kPrecStallSweeps = 8;
@@ -1366,24 +1365,21 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
     // Work items, largest teams and costliest first.  The work of one
     // right-hand side of a system is taken as (slots + rows) per sweep times
     // the system's relative sweep count.  A system's right-hand sides are
-    // grouped in 8, 4, 2 or 1, the largest group whose item, split over the
-    // largest team it can have, stays within a third of an even share of the
-    // whole batch per workgroup, so that no item is long next to the makespan.
+    // grouped in at most 8 (group_for).
     auto unit = [&](int s) { return (double)(bs->sys_h[s].S + bs->sys_h[s].n) * bs->sys_weight[s]; };
     auto waves = [&](int s, int kg) {  // 64-lane units of a pass (of a colour class)
       return (int64_t)bs->sys_h[s].nsl * kg / std::max(1, bs->sys_h[s].ncls);
     };
     double total = 0.0;
     for (int s = 0; s < S; ++s) total += unit(s) * nrhs[s];
-    const double share = std::max(1.0, total / std::max(1, bs->grid_r)), cap = share / 3.0;
+    const double share = std::max(1.0, total / std::max(1, bs->grid_r));
     std::vector<BItem> items;
     int64_t oh = 0, onk = 0, ox = 0;
     for (int s = 0; s < S; ++s) {
       const SysRec& R = bs->sys_h[s];
       if (R.n == 0) continue;
       const int32_t k = nrhs[s];
-      int32_t gmax = kMaxGroup;
-      while (gmax > 1 && unit(s) * gmax / team_for(unit(s) * gmax, 0.0, waves(s, gmax), bs->grid_r) > cap) gmax >>= 1;
+      const int32_t gmax = group_for(unit(s), share, R.nsl, std::max(1, R.ncls), bs->grid_r);
       for (int32_t j0 = 0; j0 < k;) {
         int32_t kg = gmax;
         while (kg > k - j0) kg >>= 1;

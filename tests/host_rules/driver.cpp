@@ -108,6 +108,34 @@ int teams() {
   return team_for(1e9, 1.0, 1 << 20, 1024) == kMaxTeam && team_for(0.4, 1.0, 1 << 20, 1024) == 1 ? 0 : 1;
 }
 
+// An item that no team shares is at most a third of an even share (or a single
+// right-hand side), one that a team shares likewise per workgroup of the largest
+// team it can have, and the group is the largest such one.
+int groups() {
+  const double share = 1000.0;
+  for (int grid : {1, 2, 7, 256, 1024})
+    for (int64_t nsl : {(int64_t)1, (int64_t)16, (int64_t)100, (int64_t)4000})
+      for (int64_t ncls : {(int64_t)1, (int64_t)2, (int64_t)9})
+        for (double unit = 0.5; unit < 1e7; unit *= 1.07) {
+          auto per_workgroup = [&](int g) {
+            const int64_t units = nsl * g / ncls;
+            const bool alone = team_for(unit * g, share, units, grid) == 1;
+            return unit * g / (alone ? 1 : team_for(unit * g, 0.0, units, grid));
+          };
+          const int g = group_for(unit, share, nsl, ncls, grid);
+          bool ok = g == 1 || g == 2 || g == 4 || g == 8;
+          ok = ok && (g == 1 || per_workgroup(g) <= share / 3.0);
+          for (int bigger = 2 * g; ok && bigger <= kMaxGroup; bigger *= 2) ok = per_workgroup(bigger) > share / 3.0;
+          if (!ok) {
+            std::printf("group of %d: unit %g, %lld slices in %lld classes, grid %d\n", g, unit, (long long)nsl,
+                        (long long)ncls, grid);
+            return 1;
+          }
+        }
+  // alone at 8 right-hand sides just above a third of a share: 4
+  return group_for(0.342 * share / 8, share, 40, 1, 1024) == 4 ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -116,6 +144,7 @@ int main(int argc, char** argv) {
   if (!std::strcmp(name, "sum_words")) bad = sum_words();
   if (!std::strcmp(name, "partials")) bad = partials();
   if (!std::strcmp(name, "teams")) bad = teams();
+  if (!std::strcmp(name, "groups")) bad = groups();
   if (!bad) std::printf("ok: %s\n", name);
   return bad;
 }

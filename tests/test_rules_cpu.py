@@ -32,3 +32,7 @@ def test_partials_keep_their_bits_and_are_not_taken_early(driver):
 
 def test_no_team_is_larger_than_the_grid(driver):
     check(driver, "teams")
+
+
+def test_groups_of_right_hand_sides(driver):
+    check(driver, "groups")
