@@ -230,6 +230,12 @@ __device__ View sys_view(const BatchArgs& A, int s) {
   return V;
 }
 
+// How a workgroup runs an item: alone; as a member of a team; or alone, but
+// with the sums of squares formed as a team of T would form them, member by
+// member, so that the stops of an item do not depend on whether the chip had
+// room for its team.
+enum Run : int { kAlone = 0, kTeam = 1, kMembers = 2 };
+
 // A team's view of one workgroup.
 struct Team {
   int T, m;          // members, and which of them this workgroup is
@@ -284,13 +290,15 @@ struct Red {
 // that a neighbour at or beyond it belongs to a later class).  Each wave walks
 // its own units (slice, part of the right-hand sides); the caller
 // synchronises the workgroup after the pass.
-template <int KIND, bool SER, bool TEAM>
+template <int KIND, bool SER, int RUN>
 __device__ void pass(const BatchArgs& A, const View& V, const Team& tm, int t, int slo, int shi, int rhi, Red& rd) {
+  constexpr bool TEAM = RUN == kTeam;
+  constexpr bool MEMBER = TEAM || (RUN == kMembers && KIND == kKSpmv);  // the slices of one member
   constexpr bool MULTI = KIND == kKH || KIND == kKSpmv;
   constexpr int kQ = KIND == kKSpmv ? 4 : kQSlots;  // FP64 slots hold twice the registers
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = uni((int32_t)(threadIdx.x / kWave)) + (TEAM ? tm.m * kWaves : 0);
-  const int waves = TEAM ? tm.T * kWaves : kWaves;
+  const int wave = uni((int32_t)(threadIdx.x / kWave)) + (MEMBER ? tm.m * kWaves : 0);
+  const int waves = MEMBER ? tm.T * kWaves : kWaves;
   const int lgk = MULTI ? V.lgk : 0;
   const int kgE = 1 << lgk;
   const int R = kWave >> lgk;  // rows per unit
@@ -558,6 +566,39 @@ __device__ void reduce_max2(Shared& sh, Team& tm, float a, float b, int kg) {
   __syncthreads();
 }
 
+// The sum of member m's lanes, into vm[m]; and the team's sum of vm, as reduce_sum
+// of a team forms it.
+__device__ void member_sum(Shared& sh, double* vm, int m, double v, int kg) {
+  for (int off = kWave / 2; off >= kg; off >>= 1) v += __shfl_xor(v, off, kWave);
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  if (lane < kg) sh.sm[w][lane] = v;
+  __syncthreads();
+  if ((int)threadIdx.x < kg) {
+    double acc = 0.0;
+    for (int q = 0; q < kWaves; ++q) acc += sh.sm[q][threadIdx.x];
+    vm[m * kMaxGroup + threadIdx.x] = acc;
+  }
+  __syncthreads();
+}
+__device__ void members_total(Shared& sh, const double* vm, int T, int kg) {
+  if (T == 1) {
+    if ((int)threadIdx.x < kg) sh.tot[threadIdx.x] = vm[threadIdx.x];
+  } else {
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int j = threadIdx.x % kMaxGroup, mm = threadIdx.x / kMaxGroup;
+    double acc = j < kg && mm < T ? vm[mm * kMaxGroup + j] : 0.0;
+    for (int off = kMaxGroup; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+    if (lane < kMaxGroup) sh.sm[w][lane] = acc;
+    __syncthreads();
+    if (threadIdx.x < kMaxGroup) {
+      double tot = 0.0;
+      for (int q = 0; q < kWaves; ++q) tot += sh.sm[q][threadIdx.x];
+      sh.tot[threadIdx.x] = tot;
+    }
+  }
+  __syncthreads();
+}
+
 template <bool TEAM>
 __device__ void reduce_sum(Shared& sh, Team& tm, double v, int kg) {
   for (int off = kWave / 2; off >= kg; off >>= 1) v += __shfl_xor(v, off, kWave);
@@ -598,8 +639,9 @@ __device__ __forceinline__ void class_range(const BatchArgs& A, int cls0, int q,
 }
 
 // ---- phase 1: the precision phase of one system -----------------------------
-template <bool SER, bool TEAM>
+template <bool SER, int RUN>
 __device__ void precision_item(const BatchArgs& A, int s, Shared& sh, Team& tm) {
+  constexpr bool TEAM = RUN == kTeam;
   const View V = sys_view(A, s);
   const SysRec R = A.sys[s];
   const int cls0 = uni(R.cls0), ncls = uni(R.ncls);
@@ -617,11 +659,11 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh, Team& tm) 
       for (int q = 0; q < ncls; ++q) {
         int slo, shi, rhi;
         class_range(A, cls0, q, V, slo, shi, rhi);
-        pass<kKP, true, TEAM>(A, V, tm, tp, slo, shi, rhi, rd);
+        pass<kKP, true, RUN>(A, V, tm, tp, slo, shi, rhi, rd);
         team_barrier<TEAM>(tm);
       }
     } else {
-      pass<kKP, false, TEAM>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
+      pass<kKP, false, RUN>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
     }
     reduce_max2<TEAM>(sh, tm, rd.dmax, 0.f, 1);  // also orders this round's aggregates before the next pass
     const float ch = __uint_as_float(sh.fmx[0]);
@@ -643,10 +685,10 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh, Team& tm) 
     for (int q = 0; q < ncls; ++q) {
       int slo, shi, rhi;
       class_range(A, cls0, q, V, slo, shi, rhi);
-      pass<kKFreeze, true, TEAM>(A, V, tm, tp, slo, shi, V.n, rd);
+      pass<kKFreeze, true, RUN>(A, V, tm, tp, slo, shi, V.n, rd);
     }
   } else {
-    pass<kKFreeze, false, TEAM>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
+    pass<kKFreeze, false, RUN>(A, V, tm, tp, V.sl0, V.sl0 + V.nsl, V.n, rd);
   }
   reduce_max2<TEAM>(sh, tm, rd.bad ? 1.f : 0.f, 0.f, 1);
   if (threadIdx.x == 0 && tm.m == 0) {
@@ -662,8 +704,9 @@ __device__ void precision_item(const BatchArgs& A, int s, Shared& sh, Team& tm) 
 }
 
 // ---- phase 2: FP64 refinement of one item ----------------------------------
-template <bool SER, bool TEAM>
-__device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh, Team& tm) {
+template <bool SER, int RUN>
+__device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh, double* vm, Team& tm) {
+  constexpr bool TEAM = RUN == kTeam;
   const int tid = threadIdx.x;
   View V = sys_view(A, I.sys);
   const SysRec R = A.sys[I.sys];
@@ -686,15 +729,23 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh,
 
   // x = 0, the correction's right-hand side r = b, and ||b|| per right-hand side
   const int q0 = tid + (TEAM ? tm.m * kBT : 0), qs = TEAM ? tm.T * kBT : kBT;
-  double bpart = 0.0;
-  for (int64_t q = q0; q < nk; q += qs) {
-    const int i = (int)(q >> V.lgk);
-    const double bv = V.B[(int64_t)(A.umap[V.r0 + i] - V.r0) * V.k + V.j0 + jj];
-    tst<TEAM>(V.xint + q, 0.0);
-    tst<TEAM>(V.r32 + q, (float)bv);
-    bpart += bv * bv;
+  auto start = [&](int first, int step) {
+    double bpart = 0.0;
+    for (int64_t q = first; q < nk; q += step) {
+      const int i = (int)(q >> V.lgk);
+      const double bv = V.B[(int64_t)(A.umap[V.r0 + i] - V.r0) * V.k + V.j0 + jj];
+      tst<TEAM>(V.xint + q, 0.0);
+      tst<TEAM>(V.r32 + q, (float)bv);
+      bpart += bv * bv;
+    }
+    return bpart;
+  };
+  if constexpr (RUN == kMembers) {
+    for (int m = 0; m < tm.T; ++m) member_sum(sh, vm, m, start(tid + m * kBT, tm.T * kBT), kg);
+    members_total(sh, vm, tm.T, kg);
+  } else {
+    reduce_sum<TEAM>(sh, tm, start(q0, qs), kg);
   }
-  reduce_sum<TEAM>(sh, tm, bpart, kg);
   if (tid < kg) sh.bn[tid] = sqrt(sh.tot[tid]);
   __syncthreads();
 
@@ -709,11 +760,11 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh,
         for (int q = 0; q < ncls; ++q) {
           int slo, shi, rhi;
           class_range(A, cls0, q, V, slo, shi, rhi);
-          pass<kKH, true, TEAM>(A, V, tm, t, slo, shi, rhi, rd);
+          pass<kKH, true, RUN>(A, V, tm, t, slo, shi, rhi, rd);
           team_barrier<TEAM>(tm);
         }
       } else {
-        pass<kKH, false, TEAM>(A, V, tm, t, V.sl0, V.sl0 + V.nsl, V.n, rd);
+        pass<kKH, false, RUN>(A, V, tm, t, V.sl0, V.sl0 + V.nsl, V.n, rd);
       }
       reduce_max2<TEAM>(sh, tm, rd.dmax, rd.xmax, kg);
       bool done = t >= 2;
@@ -732,9 +783,19 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh,
         tst<TEAM>(V.xint + q, tld<TEAM>(V.xint + q) + (double)(tld<TEAM>(hT + q) * V.invPt[q >> V.lgk]));
       team_barrier<TEAM>(tm);
     }
-    Red rd{0.f, 0.f, 0.0, 0};
-    pass<kKSpmv, false, TEAM>(A, V, tm, 0, V.sl0, V.sl0 + V.nsl, V.n, rd);
-    reduce_sum<TEAM>(sh, tm, rd.r2, kg);
+    if constexpr (RUN == kMembers) {
+      for (tm.m = 0; tm.m < tm.T; ++tm.m) {
+        Red rd{0.f, 0.f, 0.0, 0};
+        pass<kKSpmv, false, RUN>(A, V, tm, 0, V.sl0, V.sl0 + V.nsl, V.n, rd);
+        member_sum(sh, vm, tm.m, rd.r2, kg);
+      }
+      tm.m = 0;
+      members_total(sh, vm, tm.T, kg);
+    } else {
+      Red rd{0.f, 0.f, 0.0, 0};
+      pass<kKSpmv, false, RUN>(A, V, tm, 0, V.sl0, V.sl0 + V.nsl, V.n, rd);
+      reduce_sum<TEAM>(sh, tm, rd.r2, kg);
+    }
     ++outer;
     relmax = 0.0;
     for (int j = 0; j < kg; ++j) {
@@ -765,7 +826,7 @@ __device__ void rhs_item(const BatchArgs& A, const BItem& I, int it, Shared& sh,
     inf.status = status != GABP_OK ? status : (converged ? GABP_OK : GABP_NOT_CONVERGED);
     inf.rel = relmax;
     inf.psweeps = A.pinfos[I.sys].psweeps;
-    inf.pad = tm.T;
+    inf.pad = TEAM ? tm.T : 1;
     inf.t0 = t_start;
     inf.t1 = wall_clock64();
     A.infos[it] = inf;
@@ -790,7 +851,8 @@ __device__ __forceinline__ BItem uniform_item(const BItem& x) {
 // workgroup of the launch is running, false after the time limit.
 __device__ __forceinline__ bool roll_call_b(BatchCtl* c, int k, uint64_t limit) {
   uint32_t want = 0;
-  if (__hip_atomic_fetch_add(&c->rolled[k], (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x)
+  if (limit > 0 &&  // with a limit of zero nobody arrives last before the first has given up
+      __hip_atomic_fetch_add(&c->rolled[k], (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x)
     __hip_atomic_compare_exchange_strong(&c->state[k], &want, kRollGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t t0 = wall_clock64();
@@ -806,8 +868,9 @@ __device__ __forceinline__ bool roll_call_b(BatchCtl* c, int k, uint64_t limit) 
 }
 
 // The persistent loop of kernel k (0: precision, 1: right-hand sides): the
-// phases in turn, items of a phase until its queue is empty.  one(q) and
-// many(q, team) run item q alone and as a member of a team.
+// phases in turn, items of a phase until its queue is empty.  many(q, team) runs
+// item q as a member of a team; one(q, T) alone, where a team of T would have
+// run it had the chip had room (1: none).
 template <bool TEAMS, typename One, typename Many>
 __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& P, int k, Shared& sh, One one,
                                            Many many) {
@@ -856,7 +919,7 @@ __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& 
         const int q = __builtin_amdgcn_readfirstlane(sh.item);
         __syncthreads();
         if (q >= ph.count) break;
-        one(ph.first + q);
+        one(ph.first + q, ph.team);
       }
     }
   }
@@ -869,7 +932,7 @@ __device__ __forceinline__ void run_phases(const BatchArgs& A, const PhaseList& 
 // (0.69 s); 256-lane workgroups with five per CU took 1.34 s (0.83 s).  With
 // four per CU the chip runs near its memory bandwidth, so the few spilled
 // registers cost nothing measurable.  With the code for teams beside it k_brhs
-// spills about 30 of them instead of 6 (colour-serial 4), so a batch in which
+// spills about 40 of them instead of 6 (colour-serial 4), so a batch in which
 // no item is split runs kernels without that code (TEAMS false).  (4096 equal
 // systems of 1000 rows, 4 right-hand sides: 15.6 ms either way.)
 template <bool SER, bool TEAMS>
@@ -877,26 +940,27 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(8))) void k
   __shared__ Shared sh;
   run_phases<TEAMS>(
       A, A.pph, 0, sh,
-      [&](int q) {
+      [&](int q, int) {
         Team tm{1, 0, nullptr, nullptr, 0, 0, 0};
-        precision_item<SER, false>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
+        precision_item<SER, kAlone>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
       },
       [&](int q, Team& tm) {
-        if constexpr (TEAMS) precision_item<SER, true>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
+        if constexpr (TEAMS) precision_item<SER, kTeam>(A, __builtin_amdgcn_readfirstlane(A.porder[q]), sh, tm);
       });
 }
 
 template <bool SER, bool TEAMS>
 __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(8))) void k_brhs(BatchArgs A) {
   __shared__ Shared sh;
+  __shared__ double vm[TEAMS ? kMaxTeam * kMaxGroup : 1];  // sums of the members that one workgroup stands for
   run_phases<TEAMS>(
       A, A.rph, 1, sh,
-      [&](int q) {
-        Team tm{1, 0, nullptr, nullptr, 0, 0, 0};
-        rhs_item<SER, false>(A, uniform_item(A.items[q]), q, sh, tm);
+      [&](int q, int T) {
+        Team tm{TEAMS ? T : 1, 0, nullptr, nullptr, 0, 0, 0};
+        rhs_item<SER, TEAMS ? kMembers : kAlone>(A, uniform_item(A.items[q]), q, sh, vm, tm);
       },
       [&](int q, Team& tm) {
-        if constexpr (TEAMS) rhs_item<SER, true>(A, uniform_item(A.items[q]), q, sh, tm);
+        if constexpr (TEAMS) rhs_item<SER, kTeam>(A, uniform_item(A.items[q]), q, sh, vm, tm);
       });
 }
 
@@ -1459,7 +1523,7 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   a.tred = bs->tred_d;
   a.pph = bs->pph;
   a.rph = bs->rph;
-  a.roll_limit = (uint64_t)bs->clock_khz * kRollMs;
+  a.roll_limit = c->aid[kAidRollLimit] ? (uint64_t)c->aid[kAidRollLimit] - 1 : (uint64_t)bs->clock_khz * kRollMs;
   a.spread = (int32_t)c->aid[kAidSpreadTeams];
   a.B = B;
   a.X = X;
@@ -1503,6 +1567,7 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
       hi = std::max(hi, ii[q].t1);
       const double ms = (double)(ii[q].t1 - ii[q].t0) / bs->clock_khz;
       busy += ms * std::max(1, ii[q].pad);
+      c->aid[kAidLargestTeam] = std::max<int64_t>(q ? c->aid[kAidLargestTeam] : 0, ii[q].pad);
       if (ms > longest) {
         longest = ms;
         arg = q;

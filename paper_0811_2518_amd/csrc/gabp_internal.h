@@ -356,7 +356,8 @@ enum TestAid : int {
   kAidWaitLimit = 1,    // nonzero: limit of the resident solve's waits, in clock ticks plus one
   kAidRollLimit = 2,    // nonzero: limit of the roll calls, in clock ticks plus one (one: they fail at once)
   kAidAborted = 3,      // counts the solves that got no place on the chip for a resident launch
-  kAids = 4
+  kAidLargestTeam = 4,  // workgroups of the largest team of the last batched solve
+  kAids = 5
 };
 
 // Everything a handle owns.  Device arrays are suffixed _d.

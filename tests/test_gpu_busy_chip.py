@@ -12,7 +12,7 @@ import torch
 import paper_0811_2518_amd as g
 import workloads
 
-from _aids import ABORTED, ROLL_LIMIT, get_aid, set_aid
+from _aids import ABORTED, LARGEST_TEAM, ROLL_LIMIT, get_aid, set_aid
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -74,3 +74,36 @@ def test_results_do_not_depend_on_the_load(mode):
             assert got[1]["rel_residual"] == pytest.approx(ref[1]["rel_residual"], rel=1e-12), limits
             if var:
                 assert torch.equal(got[2], ref[2]), limits
+
+
+BATCHES = {
+    "one_er": lambda: ([workloads.er_problem(40001, 8, 1, ratio=1.1)], [1]),
+    "one_grid3d": lambda: ([workloads.grid3d_problem(24, 2)], [8]),
+    "mixed": lambda: ([workloads.grid2d_problem(121, 101, 6, ratio=1.1), workloads.er_problem(9001, 12, 7),
+                       workloads.grid3d_problem(13, 8)] + [workloads.grid2d_problem(9 + q % 5, 8, 20 + q) for q in range(40)],
+                      [3, 7, 1] + [1 + q % 5 for q in range(40)]),
+}
+
+
+@pytest.mark.parametrize("layout", ["auto", "serial"])
+@pytest.mark.parametrize("name", sorted(BATCHES))
+def test_batches_do_not_depend_on_the_load(name, layout):
+    probs, ks = BATCHES[name]()
+    bt = workloads.batch_of(probs, ks, seed=54)
+    s = g.BatchedSolver(bt.sys_row_off, bt.row_ptr, bt.col, bt.val, device=DEV, layout=layout)
+    rng = np.random.default_rng(11)
+    B = [dev(bt.B)] + [dev(rng.standard_normal(len(bt.B))) for _ in range(3)]
+
+    def run(limit):
+        out = []
+        for b in B:
+            set_aid(s, ROLL_LIMIT, limit)
+            X, infos, st = s.solve(bt.nrhs, bt.rhs_off, b, tol=1e-10, max_iter=20000)
+            assert st == 0 and (get_aid(s, LARGEST_TEAM) > 1) == (limit == 0)
+            out.append((X, [(i["sweeps"], i["outer_iters"], i["rel_residual"]) for i in infos]))
+        return out
+
+    want = run(0)
+    for limit in (1, 0):
+        for (X, infos), (Xw, iw) in zip(run(limit), want):
+            assert torch.equal(X, Xw) and infos == iw, limit
