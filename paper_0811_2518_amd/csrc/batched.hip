@@ -51,8 +51,10 @@
 #include <algorithm>
 #include <cmath>
 #include <numeric>
+#include <optional>
 #include <vector>
 
+#include "chip_gate.h"
 #include "gabp_internal.h"
 #include "rules.h"
 
@@ -1133,6 +1135,7 @@ struct BatchState {
   int64_t hcap = 0, nkcap = 0, xcap = 0;
   int grid_p = 0, grid_r = 0;
   int launched_grid = 0;
+  int dev = 0, ncu = 0;
   bool serial = false;
   double clock_khz = 0.0;
   gabp_batch_profile prof{};
@@ -1343,6 +1346,8 @@ gabp_status batched_create(Ctx* c, int32_t num_sys, const int32_t* sys_row_off) 
   // without take no more registers or LDS)
   GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_p, kernel_p(bs->serial, true), kBT, 0));
   GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_r, kernel_r(bs->serial, true), kBT, 0));
+  bs->dev = dev;
+  bs->ncu = ncu;
   bs->grid_p = std::max(1, ncu * std::max(1, per_p));
   bs->grid_r = std::max(1, ncu * std::max(1, per_r));
   int khz = 0;
@@ -1534,6 +1539,8 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   a.max_iter = std::max(1, max_iter);
   // control blocks cleared (a kernel, not a memset), the precision phase, then
   // the right-hand sides; with teams every workgroup that can be resident
+  std::optional<ChipPlace> place;  // teams need the whole chip, and two kernels run after each other
+  if (bs->pph.teams || bs->rph.teams) place.emplace(chip_gate(bs->dev), bs->ncu + 1, bs->ncu, kChipPatience);
   hipLaunchKernelGGL(k_reset_ctl, dim3((unsigned)std::min<int64_t>((bs->ctl_words + 255) / 256, 256)), dim3(256), 0, st,
                      (uint64_t*)bs->ctl_d, bs->ctl_words);
   const int gp = bs->pph.teams ? bs->grid_p : std::max(1, std::min(bs->grid_p, S));
@@ -1541,11 +1548,13 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   bs->launched_grid = gr;
   hipLaunchKernelGGL(kernel_p(bs->serial, bs->pph.teams), dim3(gp), dim3(kBT), 0, st, a);
   hipLaunchKernelGGL(kernel_r(bs->serial, bs->rph.teams), dim3(gr), dim3(kBT), 0, st, a);
+  if (place) place->issued();
   GABP_HIP(c, hipGetLastError());
   std::vector<ItemInfo> ii(bs->items.size()), pi(S);
   GABP_HIP(c, hipMemcpyAsync(ii.data(), bs->infos_d, sizeof(ItemInfo) * ii.size(), hipMemcpyDeviceToHost, st));
   GABP_HIP(c, hipMemcpyAsync(pi.data(), bs->pinfo_d, sizeof(ItemInfo) * S, hipMemcpyDeviceToHost, st));
   GABP_HIP(c, hipStreamSynchronize(st));
+  place.reset();
   // load-balance profile of the launch
   {
     gabp_batch_profile& pf = bs->prof;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -335,6 +336,7 @@ using ResKernel = void (*)(ResArgs);
 ResKernel res_kernel32(int lanes, int K, int mode);
 struct ResPlan {
   int mode = 0, K = 0, lanes = 0, nb = 0, rows_cap = 0, phase = 0, khz = 0;
+  int dev = 0, ncu = 0, need = 0;  // the chip, and the compute units that a launch takes up
   int2* blk_d = nullptr;
   int2* lane_d = nullptr;
   int2* cls_tab_d = nullptr;
@@ -644,6 +646,9 @@ ResPlanHost plan_resident_serial(const std::vector<int32_t>& off_ptr, int32_t n,
 // which has nothing to choose then
 gabp_status setup_resident(Ctx* c);
 hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s);
+class ChipGate;
+ChipGate& chip_gate(int dev);                   // of a device
+constexpr std::chrono::milliseconds kChipPatience{2000};  // longest wait for a turn at it
 // a solve with b, x and var in the caller's row order; *ran is false (and
 // nothing has been written) when it has to take the launch-per-sweep path: no
 // plan, a small system, or a launch that could not get the chip

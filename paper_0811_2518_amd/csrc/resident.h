@@ -29,7 +29,8 @@
 //     workgroup polled by all; up to 64 workgroups one counter is the fastest
 //     (1.0 us at 32 workgroups, 1.4 against 1.5 us at 64).
 // The workgroups must all be resident at once for the barrier to end.  The
-// host launches no more of them than the device holds, and the first barrier
+// host launches no more of them than the device holds and lets the process's
+// threads launch in turn (chip_gate.h), and the first barrier
 // is a roll call with a time limit: if the device is busy with other work and
 // not every workgroup has started in time, the launch ends without touching
 // its outputs and the host takes the launch-per-sweep path instead.  Once the

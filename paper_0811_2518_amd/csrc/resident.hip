@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "chip_gate.h"
 #include "resident.h"
 
 namespace gabp {
@@ -239,6 +240,7 @@ gabp_status setup_resident(Ctx* c) {
                                   blocks == 1 || c->nparts == 0 ? none : c->part_start);
     }
   if (pl.blk.empty()) return GABP_OK;
+  int most = INT32_MAX;  // workgroups that a CU holds
   for (int m : {mode, (int)kResFrozen}) {
     if (m == kResFrozen && (mode != kResJoint || !(c->opts.flags & GABP_FLAG_REUSE_PRECISION))) break;
     const void* f = (const void*)res_kernel(fp32, pl.lanes, K, m);
@@ -247,6 +249,7 @@ gabp_status setup_resident(Ctx* c) {
     int per = 0;
     GABP_HIP(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, pl.lanes, lds));
     if ((int64_t)per * ncu < (int64_t)pl.blk.size()) return GABP_OK;
+    most = std::min(most, per);
   }
   // one allocation: control blocks (zero), workgroups, lanes, class tables
   const size_t nblk = pl.blk.size(), o_lane = 2 * sizeof(ResCtl) + sizeof(int2) * nblk;
@@ -274,7 +277,16 @@ gabp_status setup_resident(Ctx* c) {
   c->res.cls_tab_d = (int2*)((char*)base + o_tab);
   c->res.cls_start_d = (int32_t*)((char*)base + o_cls);
   c->res.khz = khz;
+  c->res.dev = dev;
+  c->res.ncu = ncu;
+  c->res.need = (c->res.nb + most - 1) / most;
   return GABP_OK;
+}
+
+ChipGate& chip_gate(int dev) {
+  constexpr unsigned kDevices = 64;  // devices beyond share a gate
+  static ChipGate* gates = new ChipGate[kDevices];  // kept: threads may solve until the process ends
+  return gates[(unsigned)dev % kDevices];
 }
 
 hipError_t launch_resident(Ctx* c, ResArgs a, bool frozen_plain, hipStream_t s) {

@@ -8,8 +8,10 @@
 #include <cstdio>
 #include <cstdlib>
 #include <fstream>
+#include <optional>
 #include <sstream>
 
+#include "chip_gate.h"
 #include "gabp_internal.h"
 
 namespace gabp {
@@ -956,12 +958,20 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
     }
   }
   if (loop) c->frozen_valid = false;
+  std::optional<ChipPlace> place;  // one workgroup waits for nobody
+  if (c->res.nb > 1) place.emplace(chip_gate(c->res.dev), c->res.need, c->res.ncu, kChipPatience);
+  if (place && !place->in()) {
+    ++c->aid[kAidAborted];
+    return GABP_OK;
+  }
   *c->st_small_h = DevStatus{};
   const volatile int32_t* lost = (int32_t*)(c->st_small_h + 1);
   *(int32_t*)(c->st_small_h + 1) = 0;
   reset_timing(c);
   GABP_HIP(c, launch_resident(c, a, honly, s));
+  if (place) place->issued();
   GABP_HIP(c, hipStreamSynchronize(s));
+  place.reset();
   const DevStatus st = *c->st_small_h;
   c->res.clean = st.done && !*lost;
   if (*lost) {  // x and what later calls would start from are in part unwritten

@@ -1,9 +1,17 @@
 // Checks of the rules in csrc/rules.h, on the CPU.  One check per command-line
 // name; exits 0 when it holds.
+#include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <mutex>
+#include <random>
+#include <thread>
 #include <vector>
 
+#include "chip_gate.h"
 #include "rules.h"
 
 using namespace gabp;
@@ -136,6 +144,85 @@ int groups() {
   return group_for(0.342 * share / 8, share, 40, 1, 1024) == 4 ? 0 : 1;
 }
 
+// Launches that wait for each other's places are never inside together: all but
+// one of those inside fit on the chip, one that asks for more than the chip is
+// inside alone, threads enter in order, and one that gives up holds nobody up.
+int gate() {
+  using std::chrono::milliseconds;
+  const milliseconds forever(60000);
+  const int64_t room = 256;
+  {  // in any mix, seen through what the threads know to be inside
+    ChipGate g;
+    std::mutex m;
+    std::vector<int64_t> inside;
+    std::atomic<int> bad{0};
+    auto work = [&](unsigned seed) {
+      std::mt19937 r(seed);
+      const int64_t needs[] = {1, 31, 124, 200, room, room + 1};
+      for (int k = 0; k < 300; ++k) {
+        const int64_t need = needs[r() % 6];
+        ChipPlace p(g, need, room, forever);
+        if (!p.in()) ++bad;
+        {
+          std::lock_guard<std::mutex> lk(m);
+          inside.push_back(need);
+          int64_t sum = 0, most = 0;
+          for (int64_t v : inside) {
+            sum += v;
+            most = std::max(most, v);
+          }
+          if (sum - most > room || (most > room && inside.size() > 1)) ++bad;
+        }
+        if (r() % 4) p.issued();
+        if (r() % 3 == 0) std::this_thread::yield();
+        std::lock_guard<std::mutex> lk(m);
+        inside.erase(std::find(inside.begin(), inside.end(), need));
+      }
+    };
+    std::vector<std::thread> t;
+    for (unsigned i = 0; i < 12; ++i) t.emplace_back(work, i);
+    for (auto& x : t) x.join();
+    if (bad) {
+      std::printf("%d launches inside that cannot all end\n", bad.load());
+      return 1;
+    }
+  }
+  {  // one beyond the chip, and only behind launches that have been issued; then in order
+    ChipGate g;
+    auto a = std::make_unique<ChipPlace>(g, room, room, forever);
+    if (ChipPlace(g, room, room, milliseconds(20)).in()) return 1;  // a is not issued yet
+    a->issued();
+    auto b = std::make_unique<ChipPlace>(g, room, room, milliseconds(20));
+    if (!b->in()) return 1;
+    b->issued();
+    if (ChipPlace(g, 1, room, milliseconds(20)).in()) return 1;  // a second one beyond it
+    std::mutex m;
+    std::vector<int> order;
+    std::vector<std::thread> t;
+    for (int i = 0; i < 5; ++i) {
+      t.emplace_back([&, i] {
+        // the third gives up while it waits
+        ChipPlace p(g, i == 1 ? room + 1 : room, room, i == 2 ? milliseconds(1) : forever);
+        std::lock_guard<std::mutex> lk(m);
+        if (p.in()) order.push_back(i);
+      });
+      std::this_thread::sleep_for(milliseconds(150));  // in line before the next
+    }
+    a.reset();
+    b.reset();
+    for (auto& x : t) x.join();
+    // each enters before the next may; they note it one after the other but for the issue of two at once
+    std::vector<int> sorted = order;
+    std::sort(sorted.begin(), sorted.end());
+    if (sorted != std::vector<int>({0, 1, 3, 4}) || order[0] != 0 || order[1] != 1) {
+      std::printf("order of %zu threads\n", order.size());
+      return 1;
+    }
+    if (!ChipPlace(g, room + 1, room, milliseconds(0)).in()) return 1;  // everything was given back
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -145,6 +232,7 @@ int main(int argc, char** argv) {
   if (!std::strcmp(name, "partials")) bad = partials();
   if (!std::strcmp(name, "teams")) bad = teams();
   if (!std::strcmp(name, "groups")) bad = groups();
+  if (!std::strcmp(name, "gate")) bad = gate();
   if (!bad) std::printf("ok: %s\n", name);
   return bad;
 }

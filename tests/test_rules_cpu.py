@@ -1,4 +1,5 @@
-"""The rules that kernels and host code share (csrc/rules.h), checked on the CPU by a host build."""
+"""The rules that kernels and host code share (csrc/rules.h) and the gate that resident launches pass
+(csrc/chip_gate.h), checked on the CPU by a host build."""
 import os
 import subprocess
 
@@ -10,7 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("rules") / "driver")
-    r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "paper_0811_2518_amd", "csrc"),
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-pthread", "-I", os.path.join(ROOT, "paper_0811_2518_amd", "csrc"),
                         os.path.join(ROOT, "tests", "host_rules", "driver.cpp"), "-o", exe],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
@@ -36,3 +37,7 @@ def test_no_team_is_larger_than_the_grid(driver):
 
 def test_groups_of_right_hand_sides(driver):
     check(driver, "groups")
+
+
+def test_launches_that_wait_for_each_other_enter_in_turn(driver):
+    check(driver, "gate")
