@@ -56,7 +56,6 @@
 
 #include "chip_gate.h"
 #include "gabp_internal.h"
-#include "rules.h"
 
 namespace gabp {
 
@@ -1540,7 +1539,10 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   // control blocks cleared (a kernel, not a memset), the precision phase, then
   // the right-hand sides; with teams every workgroup that can be resident
   std::optional<ChipPlace> place;  // teams need the whole chip, and two kernels run after each other
-  if (bs->pph.teams || bs->rph.teams) place.emplace(chip_gate(bs->dev), bs->ncu + 1, bs->ncu, kChipPatience);
+  const bool teams = bs->pph.teams || bs->rph.teams;
+  const bool skip = teams && c->busy.skip();
+  if (skip) a.roll_limit = 0;  // no team, and no wait for one
+  else if (teams) place.emplace(chip_gate(bs->dev), bs->ncu + 1, bs->ncu, kChipPatience);
   hipLaunchKernelGGL(k_reset_ctl, dim3((unsigned)std::min<int64_t>((bs->ctl_words + 255) / 256, 256)), dim3(256), 0, st,
                      (uint64_t*)bs->ctl_d, bs->ctl_words);
   const int gp = bs->pph.teams ? bs->grid_p : std::max(1, std::min(bs->grid_p, S));
@@ -1564,8 +1566,10 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
     uint64_t lo = ~0ull, hi = 0, plo = ~0ull, phi = 0;
     double busy = 0.0, longest = -1.0;
     size_t arg = 0;
+    int team_p = 1, team_r = 1;  // largest that ran
     for (int s = 0; s < S; ++s) {
       if (bs->sys_h[s].n == 0) continue;
+      team_p = std::max(team_p, pi[s].pad);
       plo = std::min(plo, pi[s].t0);
       phi = std::max(phi, pi[s].t1);
       busy += (double)(pi[s].t1 - pi[s].t0) / bs->clock_khz * std::max(1, pi[s].pad);
@@ -1576,13 +1580,20 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
       hi = std::max(hi, ii[q].t1);
       const double ms = (double)(ii[q].t1 - ii[q].t0) / bs->clock_khz;
       busy += ms * std::max(1, ii[q].pad);
-      c->aid[kAidLargestTeam] = std::max<int64_t>(q ? c->aid[kAidLargestTeam] : 0, ii[q].pad);
+      team_r = std::max(team_r, ii[q].pad);
       if (ms > longest) {
         longest = ms;
         arg = q;
       }
       pf.inner_sweeps += ii[q].sweeps;
     }
+    if (teams && !skip) {
+      const bool none = (bs->pph.teams && team_p == 1) || (bs->rph.teams && team_r == 1);
+      if (none) c->busy.failed();
+      else c->busy.succeeded();
+      c->aid[kAidAborted] += none;
+    }
+    c->aid[kAidLargestTeam] = team_r;
     const uint64_t first = std::min(lo, plo);
     pf.makespan_ms = ii.empty() ? 0.0 : (double)(hi - first) / bs->clock_khz;
     pf.busy_ms = busy;

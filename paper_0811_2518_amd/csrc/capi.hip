@@ -676,6 +676,7 @@ gabp_status gabp_get_props(gabp_handle h, gabp_props* p) {
 gabp_status gabp_set_test_aid(gabp_handle h, int32_t which, int64_t value) {
   if (!h || which < 0 || which >= kAids) return fail(h, GABP_E_ARG, "test aid");
   h->aid[which] = value;
+  if (which == kAidRollLimit) h->busy = Backoff{};  // the next launch tries the new limit
   return GABP_OK;
 }
 

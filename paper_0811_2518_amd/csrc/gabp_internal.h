@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/gabp.h"
+#include "rules.h"
 
 namespace gabp {
 
@@ -357,7 +358,7 @@ enum TestAid : int {
   kAidSpreadTeams = 0,  // nonzero: a batch's teams take their members from different XCDs
   kAidWaitLimit = 1,    // nonzero: limit of the resident solve's waits, in clock ticks plus one
   kAidRollLimit = 2,    // nonzero: limit of the roll calls, in clock ticks plus one (one: they fail at once)
-  kAidAborted = 3,      // counts the solves that got no place on the chip for a resident launch
+  kAidAborted = 3,      // counts the launches that found no place on the chip
   kAidLargestTeam = 4,  // workgroups of the largest team of the last batched solve
   kAids = 5
 };
@@ -478,6 +479,7 @@ struct Ctx {
   double* lsum_d = nullptr;           // [n] residual part of the earlier classes
   ResPlan res;                        // resident solve (nb = 0: the system does not fit)
 
+  Backoff busy;                       // after launches (resident, batched teams) that found no place
   int64_t aid[kAids] = {0};           // test aids
 
   // batched

@@ -59,7 +59,6 @@
 #include <type_traits>
 
 #include "gabp_internal.h"
-#include "rules.h"
 #include "wave.h"
 
 #pragma clang fp contract(off)

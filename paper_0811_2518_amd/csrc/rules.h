@@ -2,6 +2,7 @@
 // host tests can include them without a device compiler.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 
 #ifdef __HIPCC__
@@ -69,5 +70,17 @@ inline int group_for(double unit, double share, int64_t nsl, int64_t ncls, int g
   }
   return g;
 }
+
+// A handle whose launch found no place on the chip does not try again at once:
+// it leaves out 1, 2, 4, ... 64 calls after each failure in a row, so that a chip
+// that stays out of reach (another process, a stream with few compute units)
+// costs at most the limit of one roll call in 65 solves, and a single failure
+// one call on the slower path.
+struct Backoff {
+  int wait = 0, left = 0;
+  bool skip() { return left > 0 && left-- > 0; }
+  void failed() { left = wait = std::min(64, std::max(1, 2 * wait)); }
+  void succeeded() { wait = 0; }
+};
 
 }  // namespace gabp

@@ -958,12 +958,15 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
     }
   }
   if (loop) c->frozen_valid = false;
+  if (c->busy.skip()) return GABP_OK;
   std::optional<ChipPlace> place;  // one workgroup waits for nobody
   if (c->res.nb > 1) place.emplace(chip_gate(c->res.dev), c->res.need, c->res.ncu, kChipPatience);
-  if (place && !place->in()) {
+  auto no_place = [c] {
+    c->busy.failed();
     ++c->aid[kAidAborted];
     return GABP_OK;
-  }
+  };
+  if (place && !place->in()) return no_place();
   *c->st_small_h = DevStatus{};
   const volatile int32_t* lost = (int32_t*)(c->st_small_h + 1);
   *(int32_t*)(c->st_small_h + 1) = 0;
@@ -980,10 +983,8 @@ gabp_status solve_resident(Ctx* c, const double* b, double* x, double* var, doub
     c->last_msg_round = -1;
     return fail(c, GABP_E_HIP, "resident solve: a workgroup stopped answering");
   }
-  if (!st.done) {  // the chip was busy
-    ++c->aid[kAidAborted];
-    return GABP_OK;
-  }
+  if (!st.done) return no_place();
+  c->busy.succeeded();
   *ran = true;
   gabp_status r;
   if (outer) {

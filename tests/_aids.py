@@ -6,7 +6,7 @@ from paper_0811_2518_amd import binding
 SPREAD_TEAMS = 0  # nonzero: a batch's teams take their members from different XCDs
 WAIT_LIMIT = 1    # nonzero: limit of the resident solve's waits, in clock ticks plus one
 ROLL_LIMIT = 2    # nonzero: limit of the roll calls, in clock ticks plus one (one: they fail at once)
-ABORTED = 3       # counts the solves that got no place on the chip for a resident launch
+ABORTED = 3       # counts the launches that found no place on the chip
 LARGEST_TEAM = 4  # workgroups of the largest team of the last batched solve
 
 

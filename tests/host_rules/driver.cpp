@@ -223,6 +223,25 @@ int gate() {
   return 0;
 }
 
+// Failures in a row are tried 1, 2, 4, ... 64 calls apart, and a success starts
+// anew.
+int backoff() {
+  Backoff b;
+  std::vector<int> tried;
+  for (int call = 0; call < 400; ++call)
+    if (!b.skip()) {
+      tried.push_back(call);
+      b.failed();
+    }
+  if (tried != std::vector<int>({0, 2, 5, 10, 19, 36, 69, 134, 199, 264, 329, 394})) return 1;
+  while (b.skip()) {
+  }
+  b.succeeded();
+  if (b.skip()) return 1;
+  b.failed();
+  return b.skip() && !b.skip() ? 0 : 1;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -233,6 +252,7 @@ int main(int argc, char** argv) {
   if (!std::strcmp(name, "teams")) bad = teams();
   if (!std::strcmp(name, "groups")) bad = groups();
   if (!std::strcmp(name, "gate")) bad = gate();
+  if (!std::strcmp(name, "backoff")) bad = backoff();
   if (!bad) std::printf("ok: %s\n", name);
   return bad;
 }

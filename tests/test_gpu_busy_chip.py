@@ -107,3 +107,33 @@ def test_batches_do_not_depend_on_the_load(name, layout):
     for limit in (1, 0):
         for (X, infos), (Xw, iw) in zip(run(limit), want):
             assert torch.equal(X, Xw) and infos == iw, limit
+
+
+def test_a_chip_out_of_reach_is_tried_ever_more_rarely():
+    """Each try spins for the limit of a roll call, so failures in a row are tried 1, 2, 4, ... calls
+    apart; the calls between give the same result, and a success starts anew."""
+    p = PROBS["grid_97x61"]()
+    bt = workloads.batch_of([workloads.er_problem(30001, 8, 1, ratio=1.1)], [1], seed=55)
+    s = g.Solver(p.row_ptr, p.col, p.val, device=DEV, reuse_precision=False)
+    sb = g.BatchedSolver(bt.sys_row_off, bt.row_ptr, bt.col, bt.val, device=DEV)
+    b, B = dev(p.b), dev(bt.B)
+
+    def one():
+        return s.solve(b, tol=1e-10, max_iter=2000)[0]
+
+    def batch():
+        return sb.solve(bt.nrhs, bt.rhs_off, B, tol=1e-10, max_iter=20000)[0]
+
+    for h, solve in ((s, one), (sb, batch)):
+        want = solve()
+        assert get_aid(h, ABORTED) == 0
+        set_aid(h, ROLL_LIMIT, 1)
+        tried = []
+        for _ in range(22):
+            before = get_aid(h, ABORTED)
+            assert torch.equal(solve(), want)
+            tried.append(get_aid(h, ABORTED) - before)
+        assert [k for k, v in enumerate(tried) if v] == [0, 2, 5, 10, 19]
+        set_aid(h, ROLL_LIMIT, 0)
+        n = get_aid(h, ABORTED)
+        assert torch.equal(solve(), want) and get_aid(h, ABORTED) == n

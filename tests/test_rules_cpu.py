@@ -41,3 +41,7 @@ def test_groups_of_right_hand_sides(driver):
 
 def test_launches_that_wait_for_each_other_enter_in_turn(driver):
     check(driver, "gate")
+
+
+def test_failed_launches_are_tried_ever_more_rarely(driver):
+    check(driver, "backoff")
