@@ -250,13 +250,10 @@ struct SmallArgs {
   const double* a;          // [E]
   const double* diag;       // [n]
   const double* rhs;        // [n]
-  const double* rhs_norm;   // device scalar ||rhs||_2 (nullable: formed in the kernel)
   double tol;               // <= 0: exactly max_iter sweeps
   int32_t max_iter;
   int32_t check_every;
   DevStatus* st;            // written once, at the end (as the finish kernels leave it)
-  double* xout[2];          // nullable: x of the returned round into [round & 1]
-  double* ptout[2];         // nullable: P~ of the returned round into [round & 1]
   double* x_direct;         // nullable: x of the returned round
   double* var_direct;       // nullable: 1 / P~ of the returned round
   void* cin_out;            // nullable: [2][E] {P, h} incoming messages by round parity

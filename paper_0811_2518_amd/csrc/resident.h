@@ -216,7 +216,7 @@ enum ResMode : int {
   kResFrozen = 1,  // mean-only sweeps on the handle's frozen precisions
   kResOuter = 2,   // refinement / loading loop around inner solves
   kResLoop = 3,    // the single loop: plain sweeps with damped feedback of the means
-  kResOuterLoop = 4,  // refinement around single-loop inner solves
+  kResOuterLoop = 4,  // refinement around single-loop inner solves (FP32)
   kResRefine = 5,  // kResOuter without frozen precisions (fewer registers)
   kResSerial = 6,  // colour-serial sweeps: the classes in turn, a grid barrier after each
   kResSerialOuter = 7  // refinement / loading loop around colour-serial inner solves

@@ -156,7 +156,6 @@ ResKernel kernel64(int mode) {
       case kResFrozen: return k_resident<double, LANES, K, kResFrozen>;
       case kResOuter: return k_resident<double, LANES, K, kResOuter>;
       case kResLoop: return k_resident<double, LANES, K, kResLoop>;
-      case kResOuterLoop: return k_resident<double, LANES, K, kResOuterLoop>;
       default: return k_resident<double, LANES, K, kResJoint>;
     }
   }

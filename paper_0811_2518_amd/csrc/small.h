@@ -124,8 +124,6 @@ __device__ __forceinline__ void store_row(const SmallArgs& A, int row, int ret, 
                                           double o2P, double o2h) {
   const bool prev = ret == T - 1;
   const double P = prev ? o2P : o1P, h = prev ? o2h : o1h;
-  if (A.xout[ret & 1]) A.xout[ret & 1][row] = h / P;
-  if (A.ptout[ret & 1]) A.ptout[ret & 1][row] = P;
   if (A.x_direct) A.x_direct[row] = h / P;
   if (A.var_direct) A.var_direct[row] = 1.0 / P;
   if (A.agg_out[0]) {
@@ -186,7 +184,7 @@ __device__ __forceinline__ void small_loop(const SmallArgs& A, const int n, cons
   }
   store_parts(own ? br * br : 0.0, s_red);
   __syncthreads();
-  SmallStop stop(A, uni_r(A.rhs_norm ? *A.rhs_norm : sqrt(sum_parts(s_red))));
+  SmallStop stop(A, uni_r(sqrt(sum_parts(s_red))));
   int T = 0;                                   // the last round whose aggregates were formed
   bool ck = stop.exact ? stop.M == 0 : true;   // the next sweep checks the last round
   bool pending = false;                        // a check whose partials have crossed the last barrier

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kSB) void k_small_rows(SmallArgs A) {
   // the row's aggregates of the last two rounds and its mean of the last (round 0: the prior)
   double o1P = dr, o1h = br, o2P = 0.0, o2h = 0.0, x1 = br / dr;
   if (own) gX[tid] = x1;
-  SmallStop stop(A, uni_r(A.rhs_norm ? *A.rhs_norm : sqrt(sum_parts(s_red))));
+  SmallStop stop(A, uni_r(sqrt(sum_parts(s_red))));
   __syncthreads();
   if (on) {
 #pragma unroll

@@ -624,10 +624,11 @@ gabp_status run_serial(Ctx* c, const RunCfg& cfg) {
   return finish_run(c, poll);
 }
 
-// The whole plain FP64 iteration in one launch (small.hip), leaving the
-// state of the multi-launch compact path: the means (and P~) of the returned
-// round by parity, the incoming messages of the last two rounds and the
-// aggregates of the last three, and the status the finish kernels would leave.
+// The whole plain FP64 iteration in one launch (small.hip): x and the variances
+// of the returned round go to the caller, the status to pinned memory as the
+// finish kernels would leave it and, where something reads them later, the
+// incoming messages and the aggregates of the last two rounds to the handle, as
+// the multi-launch compact path leaves them.
 gabp_status run_small(Ctx* c, const RunCfg& cfg, double* x, double* var) {
   SmallArgs a{};
   a.n = c->n;
@@ -638,7 +639,6 @@ gabp_status run_small(Ctx* c, const RunCfg& cfg, double* x, double* var) {
   a.a = c->a64_d;
   a.diag = (const double*)cfg.diag;
   a.rhs = (const double*)cfg.rhs;
-  a.rhs_norm = nullptr;  // ||b|| formed in the kernel
   a.max_deg = c->max_degree;
   a.x_direct = x;
   a.var_direct = var;
