@@ -118,6 +118,8 @@ __device__ __forceinline__ uint64_t tag_partial(double v, uint32_t seq) {
   return pack_partial(__builtin_bit_cast(uint64_t, v), seq);
 }
 
+constexpr int kErrLost = 1 << 30;  // beside the kErr* bits of a run, never stored
+
 enum GridState : int { kGo = 1, kAbort = 2 };
 enum WaitResult : int { kWaitOk = 0, kWaitBad = 1, kWaitEnd = 2 };
 
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     __syncthreads();
     if (s_res) return;
   }
-  bool lost = false;  // a wait of this workgroup ran out (all its waves agree)
+  int err = 0;  // of the run; kErrLost: a wait of this workgroup ran out (all its waves agree)
   // the sum of check q's partials, formed by wave 0 and left in its word of
   // s_tot: from memory, or from the copy in s_part where `staged`.  True: a
   // wait ran out.
@@ -433,7 +435,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     if (nb == 1) return block_sum(red);
     if (wave == 0 && sum_partials(seq, false)) s_late = 1;
     lds_barrier_r();
-    if (s_late) lost = true;
+    if (s_late) err |= kErrLost;
     return uni_r(s_tot[sum_word(seq)]);
   };
   // All workgroups: records stored before it are visible after it.  red
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     }
     lds_barrier_r();
     asm volatile("" ::: "memory");
-    if (s_res == kWaitEnd) lost = true;
+    if (s_res == kWaitEnd) err |= kErrLost;
     return s_res == kWaitBad;
   };
   const double bnorm = uni_r(sqrt(total(s_red[0])));
@@ -474,7 +476,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   const int ce = max(1, A.check_every);
   // result of a run of sweeps (kept for the caller of the run)
   double last_rel = -1.0, prev_rel = -1.0;
-  int last_round = -1, prev_round = -1, conv = -1, err = 0;
+  int last_round = -1, prev_round = -1, conv = -1;
 
   // Colour-serial sweeps (serial.hip) on the system with right-hand side `rhs`:
   // a slot holds the outgoing message of its row's last update (mP0, mH0), the
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     bool pending = false;
     conv = last_round = prev_round = -1;
     last_rel = prev_rel = -1.0;
-    err = 0;
+    err &= kErrLost;
     int nbar = 0;        // barriers of this run: the flag word in use
     double lsum = 0.0;   // the row's residual part of the earlier classes, from the last sweep
     for (int t = 1;; ++t) {
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
         pending = false;
         if (rel <= tol) conv = t - 2;
         else if (!(rel <= kDivergeLimit)) err |= kErrDiverged;
-        if (conv >= 0 || err || lost) break;
+        if (conv >= 0 || err) break;
       }
       const bool fin = t == M + 1;  // the residual of sweep M alone, every row at once
       const bool ck = exact ? fin : (t >= 2 && t <= M + 1 && in_set(t - 1));
@@ -618,9 +620,9 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
           pending = true;
         }
         if (grid_barrier(send ? s_red[t & 1] : nullptr, &s_bad[nbar % 3])) err |= kErrNonfinite;
-        if (err || lost) break;
+        if (err) break;
       }
-      if (err || lost) break;
+      if (err) break;
     }
   };
 
@@ -647,7 +649,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     double last_tot = 0.0, prev_tot = 0.0;
     bool pending = false;  // a check whose partials are on their way
     conv = last_round = prev_round = -1;
-    err = 0;
+    err &= kErrLost;
     // Early or late decisions.  Adding up the partials before the update makes
     // every wave wait for one; while no stop is in sight wave 0 only stages
     // them in LDS, adds them up while the barrier of the same sweep is under
@@ -707,7 +709,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
           decide(total(s_red[p1]), t - 2);
         }
       }
-      if (conv >= 0 || err || lost || !live) return true;
+      if (conv >= 0 || err || !live) return true;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         const V2 l = s_agg[p1 * cap + (cr[k] < 0 ? ~cr[k] : 0)];
@@ -831,7 +833,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       }
       const bool any_bad = grid_barrier(ck ? s_red[pn] : nullptr, &s_bad[t % 3], late);
       if (LATE && late) {
-        if (lost) return true;
+        if (err) return true;
         decide(uni_r(s_tot[sum_word(late)]), t - 2);
         if (conv >= 0 || err) {
           if (upd && tail) {  // the sweep taken back
@@ -845,7 +847,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
         }
       }
       if (any_bad) err |= kErrNonfinite;
-      return err != 0 || lost;  // a non-finite message ends the solve
+      return err != 0;  // a non-finite message ends the solve
     };
     for (int t = 1;; t += 2) {
       if (sweep(std::true_type{}, t)) break;
@@ -858,6 +860,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
   // a workgroup that stopped waiting stores no result, and the host hears of it
   // from whichever workgroup it was
   auto give_up = [&]() -> bool {
+    const bool lost = (err & kErrLost) != 0;
     if (lost && tid == 0) *A.lost = 1;
     return lost;
   };
@@ -914,7 +917,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
     double orel = bnorm > 0.0 ? 1.0 : bnorm;
     if (orel <= A.tol) oconv = 0;
     else if (!(orel <= kDivergeLimit)) oerr = kErrDiverged;
-    while (oconv < 0 && !oerr && !lost && outer < A.max_outer && sweeps < A.max_iter) {
+    while (oconv < 0 && !oerr && !err && outer < A.max_outer && sweeps < A.max_iter) {
       const int M = max(0, min(A.inner_max, A.max_iter - sweeps));
       const bool will_freeze = MODE == kResOuter && A.want_freeze && !frozen;
       if constexpr (MODE == kResOuter) {
@@ -925,7 +928,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       } else {
         run(std::false_type{}, A.inner_tol, M, rnorm);
       }
-      if (err || lost) {
+      if (err) {
         ierr = err;
         break;
       }
@@ -969,7 +972,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
         s_xo[lrow] = x;
       }
       grid_barrier(nullptr, nullptr);
-      if (lost) break;
+      if (err) break;
       // r = b - A x in FP64, the products subtracted in CSR order
       double xg[K];
 #pragma unroll
@@ -1008,7 +1011,7 @@ __global__ __launch_bounds__(LANES) void k_resident(ResArgs A) {
       ++seq;
       grid_barrier(s_red[2], nullptr);
       rnorm = uni_r(sqrt(total(s_red[2])));
-      if (lost) break;
+      if (err) break;
       ++outer;
       orel = bnorm > 0.0 ? rnorm / bnorm : rnorm;
       if (orel <= A.tol) oconv = 0;
