@@ -1542,7 +1542,11 @@ gabp_status batched_solve(Ctx* c, const int32_t* nrhs, const int64_t* rhs_off, c
   const bool teams = bs->pph.teams || bs->rph.teams;
   const bool skip = teams && c->busy.skip();
   if (skip) a.roll_limit = 0;  // no team, and no wait for one
-  else if (teams) place.emplace(chip_gate(bs->dev), bs->ncu + 1, bs->ncu, kChipPatience);
+  if (teams && !skip) {
+    ChipGate& gate = chip_gate(bs->dev);
+    if (gate.shared()) GABP_HIP(c, hipStreamSynchronize(st));
+    place.emplace(gate, bs->ncu + 1, bs->ncu, kChipPatience);
+  }
   hipLaunchKernelGGL(k_reset_ctl, dim3((unsigned)std::min<int64_t>((bs->ctl_words + 255) / 256, 256)), dim3(256), 0, st,
                      (uint64_t*)bs->ctl_d, bs->ctl_words);
   const int gp = bs->pph.teams ? bs->grid_p : std::max(1, std::min(bs->grid_p, S));

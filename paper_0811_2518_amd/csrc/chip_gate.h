@@ -13,7 +13,9 @@
 // second case it also waits until the others have been issued, so as not to take
 // their places.  A call of several kernels that each want the whole chip asks for
 // more than there is: it enters when nothing is inside and keeps others out.
-// Threads enter in the order of their calls.  Other processes and other kernels
+// Threads enter in the order of their calls.  Where several threads use the gate,
+// a thread waits for the earlier work of its stream before it enters, not inside.
+// Other processes and other kernels
 // are not seen here; for these the roll calls have their limits.
 //
 // Solves per thread in turn on streams of their own, ms a solve without / with
@@ -27,6 +29,7 @@
 #include <condition_variable>
 #include <cstdint>
 #include <mutex>
+#include <thread>
 
 namespace gabp {
 
@@ -36,6 +39,7 @@ class ChipGate {
   // may itself be waiting for work of a thread that stands here).
   bool enter(int64_t need, int64_t room, std::chrono::milliseconds patience) {
     std::unique_lock<std::mutex> lk(m_);
+    note_thread();
     Waiter me;
     Waiter** at = &line_;
     while (*at) at = &(*at)->next;
@@ -54,6 +58,12 @@ class ChipGate {
     cv_.notify_all();
     return in;
   }
+  // Whether more than one thread has come here, this one included.
+  bool shared() {
+    std::lock_guard<std::mutex> lk(m_);
+    note_thread();
+    return shared_;
+  }
   void issued() {
     std::lock_guard<std::mutex> lk(m_);
     --unissued_;
@@ -69,11 +79,18 @@ class ChipGate {
   struct Waiter {  // on the waiting thread's stack
     Waiter* next = nullptr;
   };
+  void note_thread() {
+    const std::thread::id me = std::this_thread::get_id();
+    if (first_ == std::thread::id()) first_ = me;
+    else if (first_ != me) shared_ = true;
+  }
   std::mutex m_;
   std::condition_variable cv_;
   Waiter* line_ = nullptr;
   int64_t used_ = 0;
   int unissued_ = 0;
+  std::thread::id first_;
+  bool shared_ = false;
 };
 
 // A place inside, given back when the solve ends, however it ends.

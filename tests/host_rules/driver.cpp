@@ -151,6 +151,12 @@ int gate() {
   using std::chrono::milliseconds;
   const milliseconds forever(60000);
   const int64_t room = 256;
+  {  // one thread alone has nobody to keep waiting
+    ChipGate g;
+    if (g.shared() || !ChipPlace(g, room, room, forever).in() || g.shared()) return 1;
+    std::thread([&] { g.shared(); }).join();
+    if (!g.shared()) return 1;
+  }
   {  // in any mix, seen through what the threads know to be inside
     ChipGate g;
     std::mutex m;

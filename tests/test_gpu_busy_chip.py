@@ -5,6 +5,9 @@ the chip, and the solve takes the launch-per-sweep path.  Whether a chip is busy
 a result: x, the variances, the sweeps and the outer steps are those of the resident launch bit for
 bit, and later solves of the handle are untouched by the failed launch.
 """
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -137,3 +140,56 @@ def test_a_chip_out_of_reach_is_tried_ever_more_rarely():
         set_aid(h, ROLL_LIMIT, 0)
         n = get_aid(h, ABORTED)
         assert torch.equal(solve(), want) and get_aid(h, ABORTED) == n
+
+
+def test_a_thread_whose_stream_is_busy_keeps_nobody_waiting():
+    """A thread's solve stands behind 0.6 s of other work of its stream (one lane, so it takes no
+    room on the chip).  A batch and a solve of another thread finish meanwhile."""
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)
+    start.record()
+    torch.cuda._sleep(10_000_000)
+    end.record()
+    end.synchronize()
+    cycles = int(10_000_000 * 600.0 / start.elapsed_time(end))
+    p = PROBS["grid_181x173"]()
+    bt = workloads.batch_of([workloads.er_problem(30001, 8, 1, ratio=1.1)], [1], seed=56)
+    sa, sb = torch.cuda.Stream(), torch.cuda.Stream()
+    a = g.Solver(p.row_ptr, p.col, p.val, device=DEV, reuse_precision=False, stream=sa)
+    b = g.Solver(p.row_ptr, p.col, p.val, device=DEV, reuse_precision=False, stream=sb)
+    bb = g.BatchedSolver(bt.sys_row_off, bt.row_ptr, bt.col, bt.val, device=DEV, stream=sb)
+    rhs, B = dev(p.b), dev(bt.B)
+    xa, xb, X = torch.empty_like(rhs), torch.empty_like(rhs), torch.empty_like(B)
+    a.solve(rhs, tol=1e-10, max_iter=2000, x=xa)
+    b.solve(rhs, tol=1e-10, max_iter=2000, x=xb)
+    bb.solve(bt.nrhs, bt.rhs_off, B, tol=1e-10, max_iter=20000, X=X)
+    torch.cuda.synchronize()
+    errors, done, queued = [], threading.Event(), threading.Event()
+
+    def first(wait):
+        try:
+            with torch.cuda.stream(sa):
+                if wait:
+                    torch.cuda._sleep(cycles)
+                queued.set()
+                a.solve(rhs, tol=1e-10, max_iter=2000, x=xa)
+        except Exception as e:  # reported by the main thread
+            errors.append(e)
+        done.set()
+
+    t = threading.Thread(target=first, args=(False,))  # now two threads have used the chip
+    t.start()
+    t.join()
+    done.clear()
+    queued.clear()
+    t = threading.Thread(target=first, args=(True,))
+    t.start()
+    queued.wait()
+    time.sleep(0.02)  # inside its solve by now
+    with torch.cuda.stream(sb):
+        b.solve(rhs, tol=1e-10, max_iter=2000, x=xb)
+        bb.solve(bt.nrhs, bt.rhs_off, B, tol=1e-10, max_iter=20000, X=X)
+    early = not done.is_set()
+    t.join()
+    assert not errors, errors
+    assert early and torch.equal(xa, xb)
