@@ -172,12 +172,18 @@ typedef struct {
  * every row, runs every sweep, check and stop decision inside one launch of
  * 1024 lanes, with the messages in registers and the aggregates in LDS.  A
  * larger compact or colour-serial system whose messages fit the registers of
- * the chip (rows of at most 96 slots) runs the whole solve, with its inner
- * solves and outer steps if it has any, in one launch of resident workgroups.
- * All paths perform the same operations; x, the variances and the messages
- * agree bit for bit, the reported residual up to its summation order.  (Inner
- * solves of the launch-per-sweep refinement may skip checks of rounds far
- * above their predicted stop; the resident ones check every round.) */
+ * the chip (rows of at most 96 slots in FP64, 128 in FP32 refinement) runs the
+ * whole solve, with its inner solves and outer steps if it has any, in one
+ * launch of resident workgroups; where the chip has no room for that launch,
+ * the solve takes the launch-per-sweep path, with the same result.
+ * All paths perform the same operations: for a matrix whose stored halves agree
+ * exactly (A_ij = A_ji), x, the variances and the messages agree bit for bit,
+ * the reported residual up to its summation order.  Where the halves differ
+ * within the 1e-12 that is allowed, the one-workgroup launch forms a message
+ * once, from the entry of the slot that receives it; the other paths form it
+ * again at the slot that sends it, from that slot's entry.  (With this flag the inner solves of the FP32 refinement may skip checks of rounds
+ * far above their predicted stop; without it, on a system that fits the chip,
+ * they check every round.) */
 #define GABP_FLAG_MULTI_LAUNCH 32
 
 /* Test aid for the compact layout (ignored by the other layouts; implies one
@@ -417,8 +423,9 @@ gabp_status gabp_create_batched(int32_t num_sys, const int32_t *sys_row_off,
  * coefficients, and runs the FP64 refinement loop on each (FP64 residual,
  * FP32 h-only inner sweeps until the largest change of the correction is at
  * most opts.inner_tol times its largest magnitude, at most opts.max_outer
- * outer steps).  An item that would outlast an even share of the batch is run
- * by a team of up to 64 workgroups.  Returns the worst status over systems.  A tighter inner_tol
+ * outer steps).  An item that would outlast half an even share of the batch is
+ * run by a team of up to 64 workgroups, or where the chip has no room for the
+ * teams by a single one, with the same result.  Returns the worst status over systems.  A tighter inner_tol
  * than gabp_default_opts' 1e-5 saves outer steps here: on the 4096-system
  * benchmark batch 2e-6 is the fastest of 1e-4 ... 1e-6.
  */

@@ -22,13 +22,15 @@
 // accesses and wait for each other at team barriers, which end because every
 // workgroup of the launch is resident: a roll call with a time limit finds
 // out, and if it fails (the chip is busy with other work) every item is run by
-// a single workgroup.  The second kernel starts when the first has finished
-// (stream order), so the frozen coefficients are complete and visible.
+// a single workgroup, with the same bits.  The second kernel starts when the
+// first has finished (stream order), so the frozen coefficients are complete and
+// visible.
 // Measured against a workgroup per item (synchronous / colour-serial): 192
-// uneven systems of 64 to 16384 rows with 1 to 16 right-hand sides each 25.4 ->
-// 8.0 / 16.9 -> 9.7 ms (the longest item took 22.8 of the 25.4), 20 such
-// systems 5.0 -> 1.1 ms, 1500 of up to 65536 rows 413 -> 313 / 306 -> 246 ms
-// (precision phase 21.3 -> 5.4 ms).
+// uneven systems of 64 to 16384 rows with 1 to 16 right-hand sides each 22.3 ->
+// 8.3 / 16.6 -> 9.6 ms (the longest item took 19.5 of the 22.3), 20 such
+// systems 5.2 -> 1.75 / 4.4 -> 3.7 ms, 600 of up to 32768 rows 87 -> 43 / 55 -> 36
+// ms, 1500 of up to 65536 rows 304 -> 188 / 199 -> 149 ms (precision phase 17 ->
+// 5.4 / 20 -> 6.7 ms).
 //
 // Layout.  At create, each system's rows are renumbered: inside each segment
 // (the whole system; with the colour-serial schedule, each colour class) the

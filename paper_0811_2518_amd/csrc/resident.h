@@ -30,17 +30,19 @@
 //     (1.0 us at 32 workgroups, 1.4 against 1.5 us at 64).
 // The workgroups must all be resident at once for the barrier to end.  The
 // host launches no more of them than the device holds and lets the process's
-// threads launch in turn (chip_gate.h), and the first barrier
-// is a roll call with a time limit: if the device is busy with other work and
-// not every workgroup has started in time, the launch ends without touching
-// its outputs and the host takes the launch-per-sweep path instead.  Once the
-// roll call has succeeded every workgroup is running, so later waits end.
+// threads launch in turn (chip_gate.h), and the first barrier is a roll call with
+// a time limit: if the device is busy with other work and not every workgroup
+// has started in time, the launch ends without touching its outputs and the host
+// takes the launch-per-sweep path instead, with the same result, and leaves out
+// a growing number of tries (rules.h).  Once the roll call has succeeded every
+// workgroup is running, so later waits end; they have a limit all the same, and
+// a workgroup that reaches it stores nothing and reports an error.
 //
 // Measured against a launch per sweep and its finish kernel, whole solves to
-// 1e-10: 181 x 173 grid with variances 669 -> 265 us, G(n, 4n) with n = 30011
-// on frozen precisions 350 -> 154 us, 64^3 grid forward and adjoint 6.65 ->
+// 1e-10: 181 x 173 grid with variances 669 -> 267 us, G(n, 4n) with n = 30011
+// on frozen precisions 350 -> 156 us, 64^3 grid forward and adjoint 6.65 ->
 // 1.71 ms (a checked mean-only sweep of its 1.5 M slots takes 5.4 us instead
-// of 24), 29 x 23 grid on frozen precisions 1004 -> 196 us in one workgroup.
+// of 24), 29 x 23 grid on frozen precisions 1004 -> 198 us in one workgroup.
 // The loops of inner solves also lose the host's status reads (20-30 us each)
 // and the launches between the phases: FP32 + refinement on G(n, 4n) with n =
 // 130003 596 -> 355 us, the double loop on B^T B + 0.1 I with n = 30000 50.5 ->
@@ -49,9 +51,10 @@
 // Colour-serial sweeps end a class with a grid barrier instead of a launch:
 // 47^3 grid to 1e-10 (66 sweeps of 2 classes) 1.33 ms -> 756 us.
 //
-// The arithmetic is that of the compact and serial sweep kernels operation for operation
-// (products and sums separately rounded): x, the variances and the messages
-// equal theirs bit for bit; only the residual norm is summed in another order.
+// The arithmetic is that of the compact and serial sweep kernels operation for
+// operation (products and sums separately rounded): x, the variances and the
+// messages equal theirs bit for bit; only the residual norm is summed in another
+// order, in full FP64 (the words that carry its partial sums lose no bit, rules.h).
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -209,7 +209,14 @@ int handle_mode(const Ctx* c) {
 // waves per CU is bound by the latency of its dependent divisions and exchanges
 // (measured at 256 / 512 / 1024 lanes, checked FP64 sweeps whose stop decision
 // falls before the update: 181 x 173 grid 4.58
-// / 4.93 / 5.65 us, G(n, 4n) with n = 30011 6.94 / 8.27 / 12.5 us).
+// / 4.93 / 5.65 us, G(n, 4n) with n = 30011 6.94 / 8.27 / 12.5 us).  At 1024 lanes
+// the 128 registers do not hold everything: the FP64 loops on frozen precisions
+// spill 120 of them (512 lanes: 13), the FP64 single loop 17, the plain FP64 solve
+// 2, the FP32 loops 11 (K = 6) and 37 (K = 8).  They are still ahead of a launch per
+// sweep: the FP64 double loop on B^T B + 0.1 I with n = 52000 6.4 against 10.7 ms for
+// 60 outer steps and the single loop 6.9 against 11.1, the FP32 double loop with n =
+// 56000 5.5 against 9.8; with loading 0.1 the 60^3 grid 4.1 against 10.7 ms in FP64
+// and 2.6 against 8.2 in FP32; the plain solve of that grid 1.05 against 2.69 ms.
 gabp_status setup_resident(Ctx* c) {
   c->res = ResPlan{};
   const int mode = handle_mode(c);
